@@ -413,6 +413,15 @@ dpf_status dpf_mlp_train_step(float* d_state, void* d_blob, const float* d_X, co
 dpf_status dpf_feature_stats(const float* d_X, int64_t n, int32_t cols, int32_t ld, float* d_mean,
                              float* d_std, float std_floor, void* hip_stream);
 
+/* The same with caller-owned scratch (dpf_feature_stats_scratch_bytes bytes,
+ * 8-byte aligned, uninitialised), which lets the rows be split over the
+ * whole GPU: the form to use for a large n.  Calls that overlap need a
+ * scratch each. */
+size_t dpf_feature_stats_scratch_bytes(int64_t n, int32_t cols);
+dpf_status dpf_feature_stats_ws(const float* d_X, int64_t n, int32_t cols, int32_t ld, float* d_mean,
+                                float* d_std, float std_floor, void* d_scratch, size_t scratch_bytes,
+                                void* hip_stream);
+
 /* d_out [n][ld_out] = (X - mean) / std in the first `cols` columns (FP32,
  * IEEE division), 0 in the others (the network's zero-padded inputs). */
 dpf_status dpf_standardize(const float* d_X, int64_t n, int32_t cols, int32_t ld, const float* d_mean,

@@ -35,7 +35,7 @@ EXPORTS = [
     "dpf_mlp_pack", "dpf_mlp_train_step", "dpf_learned_run", "dpf_tile_classes", "dpf_set_tiling",
     "dpf_estimate_rb", "dpf_systematic_noalloc", "dpf_set_lookahead_companions", "dpf_set_prediction",
     "dpf_predicted_observation", "dpf_feature_stats", "dpf_standardize", "dpf_permutation",
-    "dpf_gather_rows",
+    "dpf_gather_rows", "dpf_feature_stats_scratch_bytes", "dpf_feature_stats_ws",
 ]
 
 
@@ -115,6 +115,8 @@ def lib():
         "dpf_mlp_train_step": (_i32, [_vp, _vp, _vp, _vp, _i32, ctypes.c_float, _i32, _vp, _sz, _vp, _vp,
                                       _vp]),
         "dpf_feature_stats": (_i32, [_vp, ctypes.c_int64, _i32, _i32, _vp, _vp, ctypes.c_float, _vp]),
+        "dpf_feature_stats_scratch_bytes": (_sz, [ctypes.c_int64, _i32]),
+        "dpf_feature_stats_ws": (_i32, [_vp, ctypes.c_int64, _i32, _i32, _vp, _vp, ctypes.c_float, _vp, _sz, _vp]),
         "dpf_standardize": (_i32, [_vp, ctypes.c_int64, _i32, _i32, _vp, _vp, _vp, _i32, _vp]),
         "dpf_permutation": (_i32, [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int64, _vp, _vp]),
         "dpf_gather_rows": (_i32, [_vp, ctypes.c_int64, _i32, _i32, _vp, _i32, _vp, _i32, _vp]),

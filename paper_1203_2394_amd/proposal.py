@@ -8,7 +8,7 @@ x_t^(k)) teach the mixture density network q(x_t | features) to stand in
 for that proposal.  Training minimises the mixture negative log-likelihood
 with Adam, all on the library's BF16 matrix-core kernels; the feature
 statistics, the standardisation, the per-epoch shuffle and the batch gather
-are library calls too (dpf_feature_stats, dpf_standardize, dpf_permutation,
+are library calls too (dpf_feature_stats_ws, dpf_standardize, dpf_permutation,
 dpf_gather_rows), PyTorch only holding the device buffers.
 
 The evaluation runs the look-ahead DPF and the learned step (with its ESS
@@ -66,14 +66,15 @@ def generate_pairs(spec, n_pairs, N=256, M=256, T=200, n_filters=20, data_seed=1
 
 def feature_stats(X):
     """Mean and sample standard deviation of each raw feature (floor 1e-3),
-    computed on the device (dpf_feature_stats)."""
+    computed on the device (dpf_feature_stats_ws)."""
     torch = _torch()
     X = X.contiguous()
     n, cols = X.shape
     mean = torch.empty(cols, dtype=torch.float32, device=X.device)
     std = torch.empty(cols, dtype=torch.float32, device=X.device)
-    _check(lib().dpf_feature_stats(_ptr(X), int(n), int(cols), int(cols), _ptr(mean), _ptr(std), 1e-3,
-                                   _stream_ptr(X.device)))
+    ws = torch.empty(lib().dpf_feature_stats_scratch_bytes(int(n), int(cols)), dtype=torch.uint8, device=X.device)
+    _check(lib().dpf_feature_stats_ws(_ptr(X), int(n), int(cols), int(cols), _ptr(mean), _ptr(std), 1e-3, _ptr(ws),
+                                      ws.numel(), _stream_ptr(X.device)))
     return mean.cpu().numpy(), std.cpu().numpy()
 
 

@@ -103,3 +103,42 @@ def test_gather_rows_bit_exact_and_nan_outside():
     assert np.array_equal(d[ok, :cols], src[idx[ok], :cols])
     assert np.all(np.isnan(d[~ok, :cols]))
     assert np.all(d[:, cols:] == 0)
+
+
+# rows around the chunk rules of the split statistics: fewer than one chunk, its edges, the most chunks with a ragged
+# last one; columns beyond one column tile, padded rows
+@pytest.mark.parametrize("n,cols,ld", [(2, 1, 1), (63, 3, 5), (64, 26, 26), (65, 26, 32), (129, 33, 40),
+                                       (1024 * 64, 26, 26), (1024 * 64 + 1, 26, 26), (200003, 7, 9)])
+def test_feature_stats_split_over_the_gpu(n, cols, ld):
+    g = np.random.default_rng(n)
+    X = (g.normal(size=(n, ld)) * g.uniform(0.1, 5, size=ld) + g.normal(size=ld) * 300).astype(np.float32)
+    X[:, cols - 1] = 2.5  # a constant column: standard deviation floored
+    d = torch.from_numpy(X).cuda()
+    L = dpf.lib()
+    nb = L.dpf_feature_stats_scratch_bytes(n, cols)
+    out = []
+    for fill in (0, 255):  # the scratch's content does not matter
+        ws = torch.full((nb,), fill, dtype=torch.uint8, device="cuda")
+        m, s = torch.empty(cols, device="cuda"), torch.empty(cols, device="cuda")
+        _check(L.dpf_feature_stats_ws(_p(d), n, cols, ld, _p(m), _p(s), ctypes.c_float(1e-3), _p(ws), nb, _s()))
+        out.append((m.cpu().numpy(), s.cpu().numpy()))
+    X64 = X[:, :cols].astype(np.float64)
+    # FP64 sums rounded once to FP32: half a unit in the last place, and a little for the two summation orders
+    assert np.allclose(out[0][0], X64.mean(axis=0), rtol=2.0 ** -24 * 1.01, atol=0)
+    assert np.allclose(out[0][1], np.maximum(X64.std(axis=0, ddof=1), np.float32(1e-3)), rtol=2.0 ** -24 * 1.01, atol=0)
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert L.dpf_feature_stats_ws(_p(d), n, cols, ld, _p(m), _p(s), ctypes.c_float(1e-3), _p(ws), nb - 8, _s()) == 1
+
+
+def test_feature_stats_of_non_finite_columns():
+    X = torch.randn(5000, 3, device="cuda")
+    X[77, 0], X[4000, 1] = float("inf"), float("nan")
+    L = dpf.lib()
+    m, s, m2, s2 = (torch.empty(3, device="cuda") for _ in range(4))
+    ws = torch.empty(L.dpf_feature_stats_scratch_bytes(5000, 3), dtype=torch.uint8, device="cuda")
+    _check(L.dpf_feature_stats(_p(X), 5000, 3, 3, _p(m), _p(s), ctypes.c_float(1e-3), _s()))
+    _check(L.dpf_feature_stats_ws(_p(X), 5000, 3, 3, _p(m2), _p(s2), ctypes.c_float(1e-3), _p(ws), ws.numel(), _s()))
+    for mm, ss in ((m, s), (m2, s2)):
+        mm, ss = mm.cpu().numpy(), ss.cpu().numpy()
+        assert np.isposinf(mm[0]) and np.isnan(mm[1]) and np.isfinite(mm[2])
+        assert ss[0] == ss[1] == np.float32(1e-3) and np.isfinite(ss[2])  # an undefined deviation takes the floor
