@@ -892,51 +892,45 @@ extern "C" size_t dpf_state_bytes(const dpf_handle* h) {
          (size_t)h->L.NMT * 4;
 }
 
+// Workgroups a state copy is split over: 16 per CU, at most one per outer
+// particle of a group.
+constexpr int kStateIoBlocks = 4096;
+
 static dpf_status state_io(dpf_handle* h, char* ext, int dir) {
   if (dir == 1) h->rb_ready = false;
-  const int F = h->F;
-  const size_t tb = state_time_bytes(F);
-  float* ex = (float*)(ext + tb);
-  float* ez = ex + (size_t)h->L.NT * h->dx;
-  float* el = ez + (size_t)h->L.NMT * h->dz;
-  const unsigned char* cur = at<unsigned char>(h, h->L.cur);
-  const long long* ioff = at<long long>(h, h->L.ioff);
-  const long long* oo64 = at<long long>(h, h->L.ooff64);
-  const int B = 256;
-  const long long nx = (long long)h->L.NT * h->dx, nz = h->L.NMT * h->dz, nl = h->L.NMT;
-  if (dir == 0) {
-    const int words = (int)(tb / 4);
-    hipLaunchKernelGGL(k_export_time, dim3((words + 255) / 256), dim3(256), 0, h->stream, at<int>(h, h->L.tcur),
-                       (int*)ext, F, words);
-    LAUNCH_CHECK("k_export_time");
-  }
-  hipLaunchKernelGGL(k_state_copy_x, dim3((unsigned)((nx + B - 1) / B)), dim3(B), 0, h->stream, ex,
-                     at<float>(h, h->L.x0), at<float>(h, h->L.x1), cur, oo64, F, h->L.NT, h->dx, dir);
-  if (h->algo == DPF_ALGO_LOOKAHEAD) {
-    const int* i0 = at<int>(h, h->L.ind0);
-    const int* i1 = at<int>(h, h->L.ind1);
-    const int* oo = at<int>(h, h->L.ooff);
-    const int* fm = at<int>(h, h->L.fM);
-    hipLaunchKernelGGL(k_state_copy_cloud, dim3((unsigned)((nz + B - 1) / B)), dim3(B), 0, h->stream, ez,
-                       at<float>(h, h->L.z0), at<float>(h, h->L.z1), i0, i1, cur, ioff, oo, fm, F,
-                       h->L.NMT, h->dz, dir);
-    hipLaunchKernelGGL(k_state_copy_cloud, dim3((unsigned)((nl + B - 1) / B)), dim3(B), 0, h->stream, el,
-                       at<float>(h, h->L.l0), at<float>(h, h->L.l1), i0, i1, cur, ioff, oo, fm, F,
-                       h->L.NMT, 1, dir);
-  } else {
-    hipLaunchKernelGGL(k_state_copy, dim3((unsigned)((nz + B - 1) / B)), dim3(B), 0, h->stream, ez,
-                       at<float>(h, h->L.z0), at<float>(h, h->L.z1), cur, ioff, F, h->L.NMT, h->dz, dir);
-    hipLaunchKernelGGL(k_state_copy, dim3((unsigned)((nl + B - 1) / B)), dim3(B), 0, h->stream, el,
-                       at<float>(h, h->L.l0), at<float>(h, h->L.l1), cur, ioff, F, h->L.NMT, 1, dir);
-  }
-  LAUNCH_CHECK("state copy");
+  StateIo a;
+  a.ext = ext;
+  a.tb = state_time_bytes(h->F);
+  a.x[0] = at<float>(h, h->L.x0);
+  a.x[1] = at<float>(h, h->L.x1);
+  a.z[0] = at<float>(h, h->L.z0);
+  a.z[1] = at<float>(h, h->L.z1);
+  a.lam[0] = at<float>(h, h->L.l0);
+  a.lam[1] = at<float>(h, h->L.l1);
+  a.ind[0] = at<int>(h, h->L.ind0);
+  a.ind[1] = at<int>(h, h->L.ind1);
+  a.tcur = at<int>(h, h->L.tcur);
+  a.cur = at<unsigned char>(h, h->L.cur);
+  a.flags = at<uint32_t>(h, h->L.flags);
+  a.loglik = at<double>(h, h->L.loglik);
+  a.rgroups = at<int2>(h, h->L.rgroups);
+  a.ginfo = at<int4>(h, h->L.ginfo);
+  a.fM = at<int>(h, h->L.fM);
+  a.ioff = at<long long>(h, h->L.ioff);
+  a.F = h->F;
+  a.NT = h->L.NT;
+  a.dx = h->dx;
+  a.dz = h->dz;
+  a.NMT = h->L.NMT;
+  int shares = (kStateIoBlocks + h->L.n_rgroups - 1) / h->L.n_rgroups;
+  if (shares > kResGroup) shares = kResGroup;
+  const dim3 grid(h->L.n_rgroups, shares);
+  if (dir == 0)
+    hipLaunchKernelGGL(k_state_io<false>, grid, dim3(kBlock), 0, h->stream, a);
+  else
+    hipLaunchKernelGGL(k_state_io<true>, grid, dim3(kBlock), 0, h->stream, a);
+  LAUNCH_CHECK("k_state_io");
   if (dir == 1) h->mom_valid = false;
-  if (dir == 1) {
-    hipLaunchKernelGGL(k_import_time, dim3((F + 255) / 256), dim3(256), 0, h->stream, (const int*)ext,
-                       at<int>(h, h->L.tcur), at<unsigned char>(h, h->L.cur), at<uint32_t>(h, h->L.flags),
-                       at<double>(h, h->L.loglik), F);
-    LAUNCH_CHECK("k_import_time");
-  }
   return DPF_OK;
 }
 
