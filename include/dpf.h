@@ -403,6 +403,15 @@ dpf_status dpf_mlp_train_step(float* d_state, void* d_blob, const float* d_X, co
                               float lr, int32_t adam_t, void* d_train_ws, size_t ws_bytes, float* d_loss,
                               float* d_grad, void* hip_stream);
 
+/* n_batches training steps in a row (adam_t = adam_t0 + 1, ...), the rows of
+ * batch b taken in place from the set d_X [n_rows][32], d_xt [n_rows][2] by the
+ * indices d_idx [n_batches * B] (device; an index outside the set gives a row
+ * of NaNs): the same values as gathering each batch and calling
+ * dpf_mlp_train_step.  d_loss [n_batches] may be NULL. */
+dpf_status dpf_mlp_train_batches(float* d_state, void* d_blob, const float* d_X, const float* d_xt, int64_t n_rows,
+                                 const int32_t* d_idx, int32_t n_batches, int32_t B, float lr, int32_t adam_t0,
+                                 void* d_train_ws, size_t ws_bytes, float* d_loss, void* hip_stream);
+
 /* ---- the training set of the learned proposal (pairs the look-ahead DPF
  * generates; training-loop plumbing, not the filter's arithmetic) ---- */
 

@@ -36,6 +36,7 @@ EXPORTS = [
     "dpf_estimate_rb", "dpf_systematic_noalloc", "dpf_set_lookahead_companions", "dpf_set_prediction",
     "dpf_predicted_observation", "dpf_feature_stats", "dpf_standardize", "dpf_permutation",
     "dpf_gather_rows", "dpf_feature_stats_scratch_bytes", "dpf_feature_stats_ws",
+    "dpf_mlp_train_batches",
 ]
 
 
@@ -114,6 +115,8 @@ def lib():
         "dpf_mlp_pack": (_i32, [_vp, _vp, _vp, _vp, _vp, _sz, _vp]),
         "dpf_mlp_train_step": (_i32, [_vp, _vp, _vp, _vp, _i32, ctypes.c_float, _i32, _vp, _sz, _vp, _vp,
                                       _vp]),
+        "dpf_mlp_train_batches": (_i32, [_vp, _vp, _vp, _vp, ctypes.c_int64, _vp, _i32, _i32, ctypes.c_float, _i32,
+                                         _vp, _sz, _vp, _vp]),
         "dpf_feature_stats": (_i32, [_vp, ctypes.c_int64, _i32, _i32, _vp, _vp, ctypes.c_float, _vp]),
         "dpf_feature_stats_scratch_bytes": (_sz, [ctypes.c_int64, _i32]),
         "dpf_feature_stats_ws": (_i32, [_vp, ctypes.c_int64, _i32, _i32, _vp, _vp, ctypes.c_float, _vp, _sz, _vp]),
@@ -571,6 +574,17 @@ class MLP:
         mean NLL."""
         self.adam_t += 1
         return self._step(X, xt, lr, self.adam_t, want_grad, loss)
+
+    def train_batches(self, X, xt, idx, lr=1e-3, loss=None):
+        """Adam steps on the consecutive batches of row indices idx [k batch]
+        (int32, on the device) into the set (X [n][32], xt [n][2]); loss: an
+        optional device tensor for the k batches' mean NLLs."""
+        k = idx.numel() // self.batch
+        _check(lib().dpf_mlp_train_batches(_ptr(self.state), _ptr(self.blob), _ptr(X), _ptr(xt), int(X.shape[0]),
+                                           _ptr(idx), k, self.batch, float(lr), self.adam_t, _ptr(self._ws),
+                                           self._ws.numel(), _ptr(loss), self._stream()))
+        self.adam_t += k
+        self._keep = (X, xt, idx, loss)
 
     def loss_and_grad(self, X, xt):
         """Mean NLL and its gradient at the current parameters (no update)."""

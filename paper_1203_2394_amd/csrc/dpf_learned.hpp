@@ -119,8 +119,8 @@ __global__ __launch_bounds__(kBlock) void k_mlp_fwd_state(StepArgs a) {
   constexpr int NF = Mdl::DX + Mdl::DY + 2 * Mdl::DZ;
   static_assert(NF <= kMlpIn, "features do not fit the input layer");
   __shared__ MlpShared sh;
-  MlpFrags fr;
-  mlp_load_frags(a.mlp, fr);
+  MlpFrags<4> fr;
+  mlp_load_blob<4, true>(a.mlp, fr);
   const int row0 = blockIdx.x * kMlpRows;
   const int nrows = min(kMlpRows, a.NT - row0);
   const float* fmean = reinterpret_cast<const float*>(a.mlp + MlpBlobLayout::fmean);
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_fwd_state(StepArgs a) {
     sh.x0[e / kMlpIn][e % kMlpIn] = f2bf(fv[q]);
   }
   __syncthreads();
-  mlp_rows<false>(fr, sh, row0, nrows, a.mdn, MlpTrainOut{});
+  mlp_rows(fr, sh, row0, nrows, a.mdn);
   __syncthreads();
   if (threadIdx.x < nrows) {
     const int g = row0 + threadIdx.x;

@@ -717,7 +717,9 @@ extern "C" dpf_status dpf_set_proposal(dpf_handle* h, const void* d_blob, size_t
   if (bytes != MlpBlobLayout::bytes) return fail(DPF_EINVAL, "blob has %zu bytes, expected %zu", bytes,
                                                  (size_t)MlpBlobLayout::bytes);
   if (!(ess_frac >= 0.0 && ess_frac <= 1.0)) return fail(DPF_EINVAL, "ess_frac must lie in [0, 1]");
-  HIP_TRY(hipMemcpyAsync(h->ws + h->L.mlp, d_blob, bytes, hipMemcpyDeviceToDevice, h->stream));
+  hipLaunchKernelGGL(k_mlp_to_handle, dim3(kMlpHid * kMlpHid / kBlock), dim3(kBlock), 0, h->stream,
+                     (const unsigned char*)d_blob, at<unsigned char>(h, h->L.mlp));
+  LAUNCH_CHECK("k_mlp_to_handle");
   h->has_proposal = true;
   h->ess_frac = ess_frac;
   return queue_moments(h, nullptr, nullptr);
@@ -1094,42 +1096,41 @@ extern "C" dpf_status dpf_segmented_systematic(const double* d_w, int32_t S, int
 }
 
 // ---------------------------------------------------------------- network
-// Training workspace (batch B, a multiple of 32): the transposed BF16
-// weights first (fixed offsets, written by dpf_mlp_pack and the Adam
+// Training workspace (batch B, a multiple of 32): the training copies of the
+// BF16 weights first (fixed offsets, written by dpf_mlp_pack and the Adam
 // kernel), then the activations, gradients and partial sums of one step.
 struct TrainWs {
-  size_t w2t, w3t, out, a1, a2, x0t, h1t, h2t, gb, gt, da2t, da1t, wp1, wp2, wp3, b1p, b2p, b3p, lossp, total;
-  int chunks, tiles, groups;
+  size_t w1, w2, w3, w2t, w3t, x0t, h1t, h2t, gt, da2t, da1t, b1p, b2p, b3p, lossp, total;
+  int tiles;
 };
 
 static TrainWs train_layout(int B) {
   TrainWs w;
   size_t c = 0;
-  w.chunks = (B + kWgChunk - 1) / kWgChunk;
   w.tiles = (B + kMlpRows - 1) / kMlpRows;
-  w.groups = (B + kBlock - 1) / kBlock;
   const size_t b = (size_t)B;
+  w.w1 = carve(c, (size_t)kMlpHid * kMlpIn * 2);
+  w.w2 = carve(c, (size_t)kMlpHid * kMlpHid * 2);
+  w.w3 = carve(c, (size_t)kMlpOut * kMlpHid * 2);
   w.w2t = carve(c, (size_t)kMlpHid * kMlpHid * 2);
   w.w3t = carve(c, (size_t)kMlpHid * kMlpOut * 2);
-  w.out = carve(c, b * kMlpOut * 4);
-  w.a1 = carve(c, b * kMlpHid * 4);
-  w.a2 = carve(c, b * kMlpHid * 4);
   w.x0t = carve(c, b * kMlpIn * 2);
   w.h1t = carve(c, b * kMlpHid * 2);
   w.h2t = carve(c, b * kMlpHid * 2);
-  w.gb = carve(c, b * kMlpOut * 2);
   w.gt = carve(c, b * kMlpOut * 2);
   w.da2t = carve(c, b * kMlpHid * 2);
   w.da1t = carve(c, b * kMlpHid * 2);
-  w.wp1 = carve(c, (size_t)w.chunks * kMlpHid * kMlpIn * 4);
-  w.wp2 = carve(c, (size_t)w.chunks * kMlpHid * kMlpHid * 4);
-  w.wp3 = carve(c, (size_t)w.chunks * kMlpOut * kMlpHid * 4);
   w.b1p = carve(c, (size_t)w.tiles * kMlpHid * 4);
   w.b2p = carve(c, (size_t)w.tiles * kMlpHid * 4);
-  w.b3p = carve(c, (size_t)w.groups * kMlpOut * 4);
-  w.lossp = carve(c, (size_t)w.groups * 8);
+  w.b3p = carve(c, (size_t)w.tiles * kMlpOut * 4);
+  w.lossp = carve(c, (size_t)w.tiles * 8);
   w.total = c;
   return w;
+}
+
+static MlpTrainWeights train_weights(const TrainWs& w, char* ws) {
+  return MlpTrainWeights{(bf16_t*)(ws + w.w1), (bf16_t*)(ws + w.w2), (bf16_t*)(ws + w.w3), (bf16_t*)(ws + w.w2t),
+                         (bf16_t*)(ws + w.w3t)};
 }
 
 constexpr int kMaxTrainBatch = 1 << 20;
@@ -1150,8 +1151,8 @@ extern "C" dpf_status dpf_mlp_pack(const float* d_params, const float* d_fmean, 
     return fail(DPF_EINVAL, "training workspace too small");
   char* ws = (char*)d_train_ws;
   hipLaunchKernelGGL(k_mlp_pack, dim3((MlpParamLayout::n + 255) / 256), dim3(256), 0, (hipStream_t)hip_stream,
-                     d_params, d_fmean, d_fstd, (unsigned char*)d_blob, ws ? (bf16_t*)(ws + w.w2t) : nullptr,
-                     ws ? (bf16_t*)(ws + w.w3t) : nullptr);
+                     d_params, d_fmean, d_fstd, (unsigned char*)d_blob,
+                     ws ? train_weights(w, ws) : MlpTrainWeights{});
   LAUNCH_CHECK("k_mlp_pack");
   return DPF_OK;
 }
@@ -1160,85 +1161,97 @@ extern "C" dpf_status dpf_mlp_forward(const void* d_blob, const float* d_X, int3
                                       void* hip_stream) {
   if (!d_blob || (!d_X && B) || (!d_out && B) || B < 0) return fail(DPF_EINVAL, "bad arguments");
   if (B == 0) return DPF_OK;
-  hipLaunchKernelGGL(k_mlp_fwd_x<false>, dim3((B + kMlpRows - 1) / kMlpRows), dim3(kBlock), 0,
-                     (hipStream_t)hip_stream, (const unsigned char*)d_blob, d_X, B, d_out, MlpTrainOut{});
+  hipLaunchKernelGGL(k_mlp_fwd_x, dim3((B + kMlpRows - 1) / kMlpRows), dim3(kBlock), 0,
+                     (hipStream_t)hip_stream, (const unsigned char*)d_blob, d_X, B, d_out);
   LAUNCH_CHECK("k_mlp_fwd_x");
   return DPF_OK;
 }
 
-extern "C" dpf_status dpf_mlp_train_step(float* d_state, void* d_blob, const float* d_X, const float* d_xt,
-                                         int32_t B, float lr, int32_t adam_t, void* d_train_ws, size_t ws_bytes,
-                                         float* d_loss, float* d_grad, void* hip_stream) {
+// One training step: the batch's forward and backward pass, the weight
+// gradients, Adam.  idx (optional): the batch's rows of X and xt.
+static dpf_status train_step(float* d_state, void* d_blob, const float* d_X, const float* d_xt, const int32_t* d_idx,
+                             int64_t n_src, int32_t B, float lr, int32_t adam_t, void* d_train_ws, size_t ws_bytes,
+                             float* d_loss, float* d_grad, hipStream_t s) {
   if (!d_state || !d_blob || !d_X || !d_xt || !d_train_ws) return fail(DPF_EINVAL, "null buffer");
   if (B < 32 || B % 32 != 0 || B > kMaxTrainBatch)
     return fail(DPF_EINVAL, "batch %d must be a positive multiple of 32 up to %d", B, kMaxTrainBatch);
   if (adam_t < 0) return fail(DPF_EINVAL, "adam_t = %d", adam_t);
   const TrainWs w = train_layout(B);
   if (ws_bytes < w.total) return fail(DPF_EINVAL, "training workspace has %zu bytes, needs %zu", ws_bytes, w.total);
-  hipStream_t s = (hipStream_t)hip_stream;
   char* ws = (char*)d_train_ws;
   unsigned char* blob = (unsigned char*)d_blob;
-  MlpTrainOut tr;
-  tr.a1 = (float*)(ws + w.a1);
-  tr.a2 = (float*)(ws + w.a2);
-  tr.x0t = (bf16_t*)(ws + w.x0t);
-  tr.h1t = (bf16_t*)(ws + w.h1t);
-  tr.h2t = (bf16_t*)(ws + w.h2t);
-  tr.B = B;
-  float* out = (float*)(ws + w.out);
-  hipLaunchKernelGGL(k_mlp_fwd_x<true>, dim3(w.tiles), dim3(kBlock), 0, s, blob, d_X, B, out, tr);
-  LAUNCH_CHECK("k_mlp_fwd_x");
-  hipLaunchKernelGGL(k_mdn_grad<2>, dim3(w.groups), dim3(kBlock), 0, s, out, d_xt, B, (bf16_t*)(ws + w.gb),
-                     (bf16_t*)(ws + w.gt), (float*)(ws + w.b3p), (double*)(ws + w.lossp));
-  LAUNCH_CHECK("k_mdn_grad");
-  MlpBwdArgs bw;
-  bw.gb = (const bf16_t*)(ws + w.gb);
-  bw.a1 = tr.a1;
-  bw.a2 = tr.a2;
-  bw.W3t = (const bf16_t*)(ws + w.w3t);
-  bw.W2t = (const bf16_t*)(ws + w.w2t);
-  bw.da2t = (bf16_t*)(ws + w.da2t);
-  bw.da1t = (bf16_t*)(ws + w.da1t);
-  bw.b2_part = (float*)(ws + w.b2p);
-  bw.b1_part = (float*)(ws + w.b1p);
-  bw.B = B;
-  hipLaunchKernelGGL(k_mlp_bwd, dim3(w.tiles), dim3(kBlock), 0, s, bw);
-  LAUNCH_CHECK("k_mlp_bwd");
-  WgArgs wg;
-  wg.job[0] = WgJob{bw.da1t, tr.x0t, (float*)(ws + w.wp1), kMlpHid, kMlpIn};
-  wg.job[1] = WgJob{bw.da2t, tr.h1t, (float*)(ws + w.wp2), kMlpHid, kMlpHid};
-  wg.job[2] = WgJob{(const bf16_t*)(ws + w.gt), tr.h2t, (float*)(ws + w.wp3), kMlpOut, kMlpHid};
-  for (int j = 0; j < 3; ++j) wg.blocks[j] = (wg.job[j].M / 32) * (wg.job[j].N / 32);
-  wg.B = B;
-  wg.chunks = w.chunks;
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3(wg.blocks[0] + wg.blocks[1] + wg.blocks[2], w.chunks), dim3(kBlock), 0, s,
-                     wg);
-  LAUNCH_CHECK("k_mlp_wgrad");
+  MlpTrainArgs t;
+  t.blob = blob;
+  t.X = d_X;
+  t.xt = d_xt;
+  t.idx = (const int*)d_idx;
+  t.n_src = n_src;
+  const MlpTrainWeights tw = train_weights(w, ws);
+  t.W1 = tw.W1;
+  t.W2 = tw.W2;
+  t.W3 = tw.W3;
+  t.W3t = tw.W3t;
+  t.W2t = tw.W2t;
+  t.x0t = (bf16_t*)(ws + w.x0t);
+  t.h1t = (bf16_t*)(ws + w.h1t);
+  t.h2t = (bf16_t*)(ws + w.h2t);
+  t.gt = (bf16_t*)(ws + w.gt);
+  t.da2t = (bf16_t*)(ws + w.da2t);
+  t.da1t = (bf16_t*)(ws + w.da1t);
+  t.b1_part = (float*)(ws + w.b1p);
+  t.b2_part = (float*)(ws + w.b2p);
+  t.b3_part = (float*)(ws + w.b3p);
+  t.loss_part = (double*)(ws + w.lossp);
+  t.B = B;
+  hipLaunchKernelGGL(k_mlp_train<2>, dim3(w.tiles), dim3(kTrainThreads), 0, s, t);
+  LAUNCH_CHECK("k_mlp_train");
   AdamArgs ad;
   ad.p = d_state;
   ad.m = d_state + MlpParamLayout::n;
   ad.v = d_state + 2 * MlpParamLayout::n;
   ad.grad_out = d_grad;
   ad.blob = blob;
-  ad.W2t = (bf16_t*)(ws + w.w2t);
-  ad.W3t = (bf16_t*)(ws + w.w3t);
-  ad.wpart[0] = wg.job[0].part;
-  ad.wpart[1] = wg.job[1].part;
-  ad.wpart[2] = wg.job[2].part;
-  ad.chunks = w.chunks;
-  ad.b1_part = bw.b1_part;
-  ad.b2_part = bw.b2_part;
+  ad.tw = tw;
+  ad.At[0] = t.da1t;
+  ad.At[1] = t.da2t;
+  ad.At[2] = t.gt;
+  ad.Ht[0] = t.x0t;
+  ad.Ht[1] = t.h1t;
+  ad.Ht[2] = t.h2t;
+  ad.b1_part = t.b1_part;
+  ad.b2_part = t.b2_part;
   ad.tiles = w.tiles;
-  ad.b3_part = (const float*)(ws + w.b3p);
-  ad.groups = w.groups;
-  ad.loss_part = (const double*)(ws + w.lossp);
+  ad.b3_part = t.b3_part;
+  ad.loss_part = t.loss_part;
   ad.loss = d_loss;
   ad.B = B;
   ad.lr = lr;
   ad.bc1 = (float)(1.0 - pow(0.9, (double)adam_t));
   ad.bc2 = (float)(1.0 - pow(0.999, (double)adam_t));
   ad.update = adam_t > 0 ? 1 : 0;
-  hipLaunchKernelGGL(k_mlp_adam, dim3((MlpParamLayout::n + 255) / 256), dim3(256), 0, s, ad);
-  LAUNCH_CHECK("k_mlp_adam");
+  hipLaunchKernelGGL(k_mlp_wgrad_adam, dim3(kAdamGrid), dim3(kWgThreads), 0, s, ad);
+  LAUNCH_CHECK("k_mlp_wgrad_adam");
+  return DPF_OK;
+}
+
+extern "C" dpf_status dpf_mlp_train_step(float* d_state, void* d_blob, const float* d_X, const float* d_xt,
+                                         int32_t B, float lr, int32_t adam_t, void* d_train_ws, size_t ws_bytes,
+                                         float* d_loss, float* d_grad, void* hip_stream) {
+  return train_step(d_state, d_blob, d_X, d_xt, nullptr, 0, B, lr, adam_t, d_train_ws, ws_bytes, d_loss, d_grad,
+                    (hipStream_t)hip_stream);
+}
+
+extern "C" dpf_status dpf_mlp_train_batches(float* d_state, void* d_blob, const float* d_X, const float* d_xt,
+                                            int64_t n_rows, const int32_t* d_idx, int32_t n_batches, int32_t B,
+                                            float lr, int32_t adam_t0, void* d_train_ws, size_t ws_bytes,
+                                            float* d_loss, void* hip_stream) {
+  if (!d_idx || n_rows < 0 || n_batches < 0 || adam_t0 < 0) return fail(DPF_EINVAL, "bad arguments");
+  if ((int64_t)adam_t0 + n_batches > 0x7fffffffLL) return fail(DPF_EINVAL, "too many steps");
+  for (int b = 0; b < n_batches; ++b) {
+    const dpf_status st = train_step(d_state, d_blob, d_X, d_xt, d_idx + (size_t)b * B, n_rows, B, lr,
+                                     adam_t0 + b + 1, d_train_ws, ws_bytes, d_loss ? d_loss + b : nullptr, nullptr,
+                                     (hipStream_t)hip_stream);
+    if (st != DPF_OK) return st;
+  }
   return DPF_OK;
 }

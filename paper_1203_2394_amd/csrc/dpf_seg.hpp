@@ -263,6 +263,15 @@ __device__ __forceinline__ double sys_point(int k, double u, double total, int n
   return b / (double)n_out;
 }
 
+// Workgroups are dealt to the eight XCDs in turn (workgroup b to XCD b % 8).
+// The tile of workgroup b when each XCD instead takes one contiguous run of
+// the n tiles: a bijection of [0, n).
+__device__ __forceinline__ int xcd_contiguous_tile(int b, int n) {
+  constexpr int kXcd = 8;
+  const int q = n / kXcd, r = n % kXcd, x = b % kXcd;
+  return x * q + min(x, r) + b / kXcd;
+}
+
 __device__ __forceinline__ bool finitef(float v) { return fabsf(v) <= 3.402823466e38f; }
 
 }  // namespace dpf

@@ -8,8 +8,9 @@ x_t^(k)) teach the mixture density network q(x_t | features) to stand in
 for that proposal.  Training minimises the mixture negative log-likelihood
 with Adam, all on the library's BF16 matrix-core kernels; the feature
 statistics, the standardisation, the per-epoch shuffle and the batch gather
-are library calls too (dpf_feature_stats_ws, dpf_standardize, dpf_permutation,
-dpf_gather_rows), PyTorch only holding the device buffers.
+are library calls too (dpf_feature_stats_ws, dpf_standardize,
+dpf_permutation, dpf_mlp_train_batches), PyTorch only holding the device
+buffers.
 
 The evaluation runs the look-ahead DPF and the learned step (with its ESS
 fallback) on the same fresh observation sequence and reports the RMSE of the
@@ -99,17 +100,11 @@ def train(X, xt, epochs=10, batch=4096, lr=1e-3, seed=0, verbose=False):
     if nb == 0:
         raise DPFError("need at least one batch of %d pairs" % batch)
     perm = torch.empty(n, dtype=torch.int32, device=device)
-    xb = torch.empty(batch, MLP_IN, dtype=torch.float32, device=device)
-    tb = torch.empty(batch, 2, dtype=torch.float32, device=device)
     lossv = torch.empty(max(nb, 1), dtype=torch.float32, device=device)
     losses = []
     for ep in range(epochs):
         _check(L.dpf_permutation(int(seed), int(ep), int(n), _ptr(perm), st))
-        for b in range(nb):
-            idx = perm[b * batch:(b + 1) * batch]
-            _check(L.dpf_gather_rows(_ptr(Xs), int(n), MLP_IN, MLP_IN, _ptr(idx), batch, _ptr(xb), MLP_IN, st))
-            _check(L.dpf_gather_rows(_ptr(xt), int(n), 2, 2, _ptr(idx), batch, _ptr(tb), 2, st))
-            mlp.train_step(xb, tb, lr=lr, loss=lossv[b:b + 1])
+        mlp.train_batches(Xs, xt, perm[:nb * batch], lr=lr, loss=lossv)
         losses.append(float(np.mean(lossv[:nb].cpu().numpy().astype(np.float64))))
         if verbose:
             print("epoch %d: mean NLL %.4f" % (ep, losses[-1]), flush=True)

@@ -568,3 +568,59 @@ def test_run_graph_follows_set_proposal():
     b.learned_step(Yall[T])
     assert np.array_equal(a.export_state().cpu().numpy(), b.export_state().cpu().numpy())
     assert torch.equal(a.copy_buffer(dpf.BUF_MDN), b.copy_buffer(dpf.BUF_MDN))
+
+
+@pytest.mark.parametrize("B,k,n", [(32, 3, 100), (96, 2, 5000), (544, 2, 1200), (4096, 1, 4096), (4128, 2, 9000)])
+def test_train_batches_equals_gathered_steps(B, k, n):
+    """Batches taken in place by index equal gathering them and stepping, bit
+    for bit (batches of one and several 512-row chunks, a ragged last chunk
+    and 256-row group), an index outside the set included."""
+    g = np.random.default_rng(B)
+    X = torch.from_numpy(g.normal(size=(n, 32)).astype(np.float32)).cuda()
+    xt = torch.from_numpy(g.normal(size=(n, 2)).astype(np.float32)).cuda()
+    idx = torch.from_numpy(g.integers(0, n, size=k * B).astype(np.int32)).cuda()
+    p = dpf.init_params(3, 26)
+    a = dpf.MLP(p, np.zeros(26), np.ones(26), batch=B)
+    b = dpf.MLP(p, np.zeros(26), np.ones(26), batch=B)
+    loss = torch.empty(k, device="cuda")
+    a.train_batches(X, xt, idx, lr=1e-2, loss=loss)
+    for q in range(k):
+        rows = idx[q * B:(q + 1) * B].long()
+        lb, _ = b.train_step(X[rows], xt[rows], lr=1e-2)
+        assert torch.equal(lb, loss[q:q + 1])
+    assert a.adam_t == b.adam_t == k
+    assert torch.equal(a.state, b.state) and torch.equal(a.blob, b.blob)
+    bad = idx[:B].clone()
+    bad[5] = n
+    a.train_batches(X, xt, bad, loss=loss[:1])
+    assert torch.isnan(loss[0])
+
+
+@pytest.mark.parametrize("B", [32, 512, 1056])
+def test_split_step_gradients_match_autograd(B):
+    """The fused step's loss and gradients (tiles of 16 rows, chunks of 512)
+    against FP64 autograd of the network with BF16-rounded operands."""
+    g = np.random.default_rng(B + 1)
+    X = torch.from_numpy(g.normal(size=(B, 32)).astype(np.float32)).cuda()
+    xt = torch.from_numpy(g.normal(size=(B, 2)).astype(np.float32)).cuda()
+    p = dpf.init_params(4, 26)
+    m = dpf.MLP(p, np.zeros(26), np.ones(26), batch=B)
+    loss, grad = m.loss_and_grad(X, xt)
+    rnd = lambda t: t + (t.to(torch.bfloat16).double() - t).detach()  # noqa: E731
+    v = torch.from_numpy(dpf.flatten_params(p)).double().requires_grad_(True)
+    W1, b1, W2, b2, W3, b3 = torch.split(v, [8192, 256, 65536, 256, 8192, 32])
+    gelu = lambda t: torch.nn.functional.gelu(t, approximate="tanh")  # noqa: E731
+    h = rnd(gelu(rnd(X.cpu().double()) @ rnd(W1).view(256, 32).t() + b1))
+    h = rnd(gelu(h @ rnd(W2).view(256, 256).t() + b2))
+    o = h @ rnd(W3).view(32, 256).t() + b3
+    mu, ls = o[:, 4:12].reshape(-1, 4, 2), o[:, 12:20].reshape(-1, 4, 2).clamp(np.log(1e-3), np.log(1e3))
+    e = (xt.cpu().double()[:, None, :] - mu) * torch.exp(-ls)
+    q = (-0.5 * e * e - ls - 0.5 * np.log(2 * np.pi)).sum(2)
+    L = -torch.logsumexp(torch.log_softmax(o[:, :4], 1) + q, 1).mean()
+    L.backward()
+    L = L.detach()
+    # the device rounds hidden gradients to BF16 as well: 2^-9 per rounding, up to seven on a chain
+    assert abs(float(loss) - float(L)) < 1e-3 * max(1.0, abs(float(L)))
+    gd = grad.cpu().double()
+    for a, b in zip(torch.split(gd, [8192, 256, 65536, 256, 8192, 32]), torch.split(v.grad, [8192, 256, 65536, 256, 8192, 32])):
+        assert float((a - b).norm()) <= 7 * 2.0 ** -9 * float(b.norm())
