@@ -62,6 +62,14 @@ enum Op {
   OP_LA_WEIGHTS_NESTED
 };
 
+// Kernels between two look-ahead new-cloud launches.
+enum EndOp { END_POST, END_FINISH, END_RUN_STATS, END_RESOLVE };
+struct StepEnd {
+  int took;   // bit of act that says a filter took the step (END_POST, END_FINISH)
+  int next;   // END_POST: also the next step's statistics; END_RESOLVE: also the finished step's estimates
+  int split;  // END_POST: END_FINISH or END_RESOLVE finishes the filters
+};
+
 // Extra arguments of OP_MOMENTS (feature rows for dpf_features).
 struct MomArgs {
   const float* y;
@@ -82,9 +90,8 @@ struct Engine {
   dpf_status (*rb)(const StepArgs& a, double* tmp, float* out, hipStream_t s);
   // plain DPF estimates (one workgroup per filter)
   dpf_status (*finalize)(const StepArgs& a, int F, hipStream_t s);
-  // look-ahead step end over n_rgroups resampling groups; split: group pass
-  // and a per-filter pass as two launches
-  dpf_status (*post)(const StepArgs& a, const int2* rgroups, int n_rgroups, int F, int next, int split,
+  // the kernels between look-ahead new clouds (EndOp)
+  dpf_status (*post)(int op, const StepArgs& a, const int2* rgroups, int n_rgroups, int F, const StepEnd& e,
                      hipStream_t s);
   bool yhat;  // the look-ahead pass can form the predicted observation
 };

@@ -127,26 +127,38 @@ static dpf_status engine_finalize(const StepArgs& a, int F, hipStream_t s) {
 }
 
 template <class Mdl, bool YH>
-static dpf_status engine_post_y(const StepArgs& a, const int2* rg, int n_rgroups, int F, int next, int split,
-                                hipStream_t s) {
+static dpf_status engine_step_end(int op, const StepArgs& a, const int2* rg, int n_rgroups, int F, const StepEnd& e,
+                                  hipStream_t s) {
   constexpr int DX = Mdl::DX, DZ = Mdl::DZ;
-  hipLaunchKernelGGL((k_post<DX, DZ, YH>), dim3(n_rgroups), dim3(kBlock), 0, s, a, rg, next, split);
-  LAUNCH_CHECK("k_post");
-  if (split) {
-    hipLaunchKernelGGL((k_post_end<DX, DZ, YH>), dim3(F), dim3(kWave), 0, s, a, next);
-    LAUNCH_CHECK("k_post_end");
+  switch (op) {
+    case END_POST:
+      hipLaunchKernelGGL((k_post<DX, DZ, YH>), dim3(n_rgroups), dim3(kBlock), 0, s, a, rg, e.took, e.next, e.split);
+      LAUNCH_CHECK("k_post");
+      break;
+    case END_FINISH:
+      hipLaunchKernelGGL((k_post_end<DX, DZ, YH>), dim3(F), dim3(kBlock), 0, s, a, e.took);
+      LAUNCH_CHECK("k_post_end");
+      break;
+    case END_RUN_STATS:
+      hipLaunchKernelGGL((k_run_stats<DX, DZ, YH>), dim3(n_rgroups), dim3(kBlock), 0, s, a, rg);
+      LAUNCH_CHECK("k_run_stats");
+      break;
+    case END_RESOLVE:
+      hipLaunchKernelGGL((k_resolve<DX, DZ, YH>), dim3(n_rgroups), dim3(kBlock), 0, s, a, rg, e.next);
+      LAUNCH_CHECK("k_resolve");
+      break;
   }
   return DPF_OK;
 }
 
 // (the predicted observation's partial sums when the step formed them)
 template <class Mdl>
-static dpf_status engine_post(const StepArgs& a, const int2* rg, int n_rgroups, int F, int next, int split,
+static dpf_status engine_post(int op, const StepArgs& a, const int2* rg, int n_rgroups, int F, const StepEnd& e,
                               hipStream_t s) {
   if constexpr (has_yhat<Mdl>()) {
-    if (a.yp != nullptr) return engine_post_y<Mdl, true>(a, rg, n_rgroups, F, next, split, s);
+    if (a.yp != nullptr) return engine_step_end<Mdl, true>(op, a, rg, n_rgroups, F, e, s);
   }
-  return engine_post_y<Mdl, false>(a, rg, n_rgroups, F, next, split, s);
+  return engine_step_end<Mdl, false>(op, a, rg, n_rgroups, F, e, s);
 }
 
 // The engine table entry of model Mdl with parameter derivation DERIVE.

@@ -11,10 +11,11 @@
 // x, z and lam are double-buffered; cur[f] says which copy holds the state of
 // filter f, so filters that sit a step out keep their state without a copy.
 //
-// A step is four launches: weights (one workgroup per tile of outer
-// particles), two small resampling kernels (one workgroup per group of 256
-// outer weights), and the new-cloud kernel, whose last workgroup per filter
-// also forms the estimates and advances the filter (no separate launch).
+// A look-ahead step on its own is the weights kernel, the group statistics of
+// the outer weights (filters of several resampling groups), the new-cloud
+// kernel and the step end; in a run the new-cloud kernel also computes the next
+// step's weights and the previous step's estimates, and only what the outer
+// resampling needs stands between two of them.
 //
 // Per-particle kernels run one 256-thread workgroup per tile of 256/SEG
 // consecutive outer particles of one filter (a "segment" of SEG lanes per
@@ -78,10 +79,21 @@ struct StepArgs {
   int NT;
   int advance;   // 1: a step (time advances, estimates); 0: initialisation
   uint64_t seed;
-  int* tcur;             // [F] time of the state (advanced by the statistics kernel)
-  unsigned char* cur;    // [F] bit 0: copy holding the state (flipped with the time);
-                         // bits 1, 2: copy 0 / copy 1 has identity cloud slots
-  unsigned char* act;    // [F] whether the filter takes the current step (set by the weights kernel)
+  // the filters' progress (a view): time of the state; bit 0 of cur: copy
+  // holding the state, bits 1, 2: copy 0 / copy 1 has identity cloud slots;
+  // bit 0 of act: the filter takes the current step (set by the weights
+  // kernel), bit 1: it took the previous one
+  int* tcur;
+  unsigned char* cur;
+  unsigned char* act;
+  // the view after the step, written by the new-cloud kernel of a look-ahead
+  // step (a run's steps alternate between two views, so that every workgroup
+  // of a launch reads one while its filters' first tiles write the other).
+  // Null: the view above already is the one after the step (the statistics
+  // kernel advanced it).
+  int* tcur_n;
+  unsigned char* cur_n;
+  unsigned char* act_n;
   const unsigned char* active;  // [F] or null
   const int* run_Tf;            // [F] or null: filter steps while tcur < min(run_Tf, run_T)
   int run_T;
@@ -95,6 +107,7 @@ struct StepArgs {
   int* anc;
   int* sel;      // [NT] selected candidate (look-ahead) / inner ancestor (plain)
   float* kpart;  // [NT][DZ] per-particle sum_j qbar z (plain: of the proposals)
+  const float* kpart_prev;  // the previous step's (a run alternates between two)
   double* gstat;  // [resampling groups + 64][4]: group max log w, sum, sum of squares (group scale)
   double* fstat;  // [F][4]: max log w, sum w, sum w^2, degenerate (0/1)
   float* ess;     // [F]
@@ -109,7 +122,9 @@ struct StepArgs {
   int dy;
   int dx, dz;
   int n_tiles;  // tiles of the class being launched (tile-looping kernels)
-  int anc_ready;  // outer ancestors already in anc
+  int anc_ready;  // outer ancestors of filters of several resampling groups already in anc
+  int n_head;     // head workgroups of a run's new-cloud launch, one per resampling group: the
+                  // previous step's estimates
   const int2* rgroups;  // (filter, group) of each resampling workgroup
   const int4* ginfo;    // per resampling group: its filter's (first outer index, N, first group, groups)
   int n_commit;         // learned-step commit workgroups at the head of the launch
@@ -1053,6 +1068,7 @@ struct ResResult {
   double total;  // sum of the weights exp(log w - m)
   double sumsq;  // sum of their squares
   bool deg;      // no finite log-weight: uniform weights were used
+  bool nonf;     // some log-weight is neither finite nor -inf (self_cdf; elsewhere the statistics' check)
 };
 
 // Ancestors res[j] of the points k0 + j, j < np (np <= 256), from the G group
@@ -1143,6 +1159,7 @@ __device__ ResResult resolve_points(const Src& src, int n, int n_out, double u, 
   r.total = total;
   r.sumsq = sumsq;
   r.deg = deg;
+  r.nonf = false;
   return r;
 }
 
@@ -1189,6 +1206,7 @@ __device__ int resolve_point_w0(const Src& src, int n, int n_out, double u, int 
   rr.total = total;
   rr.sumsq = want_sumsq ? seg_reduce_wave<OpAdd, kWave>(Q) : 0.0;
   rr.deg = deg;
+  rr.nonf = false;
   const double P = sys_point(k0, u, total, n_out);
   unsigned long long bm = __ballot(l < G && Binc > P);
   if (!bm) bm = __ballot(l < G && Binc >= total);
@@ -1235,6 +1253,81 @@ __device__ int resolve_point_w0(const Src& src, int n, int n_out, double u, int 
     idx = 4 * fl + __builtin_amdgcn_readlane(hit_eq, fl);
   }
   return base + idx;
+}
+
+// A filter of one resampling group (N <= 256): every wave that needs its
+// ancestors forms the whole cumulative sum itself from the log-weights, four
+// consecutive weights per lane -- no statistics launch, no barrier.  C: this
+// lane's cumulative weights.
+__device__ __forceinline__ ResResult self_cdf(const float* lw, int N, bool want_sumsq, double (&C)[4]) {
+  const int l = threadIdx.x & (kWave - 1);
+  float v[4];
+  float key = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = lw[min(4 * l + q, N - 1)];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (4 * l + q < N && finitef(v[q])) key = fmaxf(key, v[q]);
+  ResResult rr;
+  const float m = seg_reduce_wave<OpMax, kWave>(key);
+  rr.deg = !(m > -INFINITY);
+  rr.m = rr.deg ? 0.f : m;
+  double acc = 0.0, sq = 0.0, L[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double w = 4 * l + q < N ? (rr.deg ? 1.0 : (finitef(v[q]) ? (double)fast_exp(v[q] - m) : 0.0)) : 0.0;
+    acc += w;
+    sq += w * w;
+    L[q] = acc;
+  }
+  double ex;
+  const double incl = wave_scan_d(acc, ex);
+  rr.total = readlane_d(incl, kWave - 1);
+  rr.sumsq = 0.0;
+  rr.nonf = false;
+  if (want_sumsq) {
+    bool nf = false;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) nf |= !finitef(v[q]) && !(v[q] == -INFINITY);  // (clamped reads repeat the last)
+    rr.sumsq = seg_reduce_wave<OpAdd, kWave>(sq);
+    rr.nonf = __ballot(nf) != 0;
+  }
+  // (monotone, the last one the total)
+#pragma unroll
+  for (int q = 0; q < 4; ++q) C[q] = 4 * l + q >= N - 1 ? rr.total : fmin(ex + L[q], rr.total);
+  return rr;
+}
+
+// The first index whose cumulative weight exceeds P (else reaches the total);
+// P the same in every lane.
+__device__ __forceinline__ int self_point(const double (&C)[4], int N, double total, double P) {
+  const int l = threadIdx.x & (kWave - 1);
+  int hit = 4, hit_eq = 4;
+#pragma unroll
+  for (int q = 3; q >= 0; --q) {
+    if (4 * l + q < N && C[q] > P) hit = q;
+    if (4 * l + q < N && C[q] >= total) hit_eq = q;
+  }
+  const unsigned long long bm = __ballot(hit < 4);
+  const int h = bm ? hit : hit_eq;
+  const int fl = first_lane(bm ? bm : __ballot(hit_eq < 4));
+  return 4 * fl + __builtin_amdgcn_readlane(h, fl);
+}
+
+// The three offsets a new outer particle k's draws start from, U53 at (t, 0, 0)
+// of OUTER_U and at (t, k, 0) of `cand` and INNER_U, in every lane of its
+// segment: one Philox evaluation (lanes 0, 1, 2 of every quad take one each)
+// instead of three, all before the first of them is needed.  Two waves per
+// particle or more: each wave its own.
+struct OuterDraws {
+  double outer, cand, inner;
+};
+__device__ __forceinline__ OuterDraws outer_draws(Key key, int t, int k, uint32_t cand) {
+  const int q = threadIdx.x & 3;
+  const Words w = draw(key, (uint32_t)t, q == 0 ? 0u : (uint32_t)k, 0u,
+                       q == 0 ? (uint32_t)P_OUTER_U : (q == 1 ? cand : (uint32_t)P_INNER_U), 0u);
+  const double u = u53(w.w[0], w.w[1]);
+  return OuterDraws{dpp_d<0x00>(u, u), dpp_d<0x55>(u, u), dpp_d<0xAA>(u, u)};
 }
 
 // One systematic draw (offset u) over weights exp(e_j - max), j < M (non-
@@ -1321,7 +1414,7 @@ static __device__ void res_finish(const StepArgs& a, int f, int t, int N, const 
   a.loglik[f] += dl;
   uint32_t fl = r.deg ? (uint32_t)F_DEGENERATE_OUTER : 0u;
   const float* yp = a.Y + (long long)(t - 1) * a.y_tstride + (long long)f * a.dy;
-  bool nonf = false;
+  bool nonf = r.nonf;
 #pragma unroll 8
   for (int q = 0; q < a.dy; ++q) nonf |= !finitef(yp[q]);
   if (nonf) fl |= F_NONFINITE;
@@ -1346,7 +1439,7 @@ static __global__ __launch_bounds__(kBlock) void k_res_stats(StepArgs a, const i
   const int fbv = a.fb != nullptr ? a.fb[f] : 1;
   const int tc = a.tcur[f], cu = a.cur[f];
   asm volatile("" ::"v"(ac), "v"(fbv), "v"(tc), "v"(cu));
-  if (!ac) return;
+  if (!(ac & 1)) return;
   if (fbv == 0) {
     if (advance_time && rg.y == 0 && threadIdx.x == 0) {
       a.tcur[f] = tc + 1;
@@ -1498,27 +1591,146 @@ static __global__ __launch_bounds__((fin_block<DX, DZ>())) void k_finalize(StepA
 }
 
 // ------------------------------------------------------- look-ahead step end
-// One workgroup per resampling group of every filter (the grid of
-// k_res_stats):
-//  * the estimates of the step just taken, xhat = mean_k x_t^(k) and zhat =
-//    mean_k sum_j qbar z (eq:qbar), as per-group FP64 partial sums (wave
-//    sums, then the four waves in order) that the filter's last workgroup
-//    adds up in group order -- the same order in every path, so results
-//    do not depend on how the steps were launched;
-//  * in a look-ahead run (next = 1), whose new-cloud kernel has already
-//    computed the next step's outer log-weights: what k_res_stats does
-//    before an ordinary step -- the group statistics of those weights,
-//    the non-finite check, and (last workgroup) the time advance -- plus
-//    the filter's activity for the next step.
-// The last workgroup of a filter is found with a counter it resets.
-// YH: also the predicted observation yhat = (1/N) sum_i yp_i (one more
-// partial sum per group).
-template <int DX, int DZ, bool YH>
-__device__ __forceinline__ void post_finish(const StepArgs& a, int f, int rb, int G, int t, unsigned char cb,
-                                            int next, bool act_next, int nthreads);
+// The estimates of a step, xhat = mean_k x_t^(k) and zhat = mean_k sum_j qbar z
+// (eq:qbar), and the predicted observation yhat = (1/N) sum_i yp_i: FP64
+// partial sums per resampling group (wave sums, then the four waves in order)
+// added up in group order -- the same order in every path, so results do not
+// depend on how the steps were launched.
 
+// Partial sums of NV values per particle over one group: v[q] this thread's
+// (0 beyond the filter's end); thread q < NV returns the group's sum of value
+// q (others 0).
+template <int NV>
+__device__ __forceinline__ double est_partial(const double* v, double (*part)[NV]) {
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const double r = seg_reduce_wave<OpAdd, kWave>(v[q]);
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave][q] = r;
+  }
+  __syncthreads();
+  const int q = threadIdx.x;
+  return q < NV ? ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q] : 0.0;
+}
+
+// Estimate q of filter f (x's components, z's, then yhat) of the step that
+// ended at time t.
+template <int DX, int DZ>
+__device__ __forceinline__ void est_store(const StepArgs& a, int f, int t, int q, double e) {
+  if (q < DX) {
+    a.est_x[f * DX + q] = (float)e;
+    if (a.trace_x) a.trace_x[((long long)(t - 1) * a.n_filters + f) * DX + q] = (float)e;
+  } else if (q < DX + DZ) {
+    a.est_z[f * DZ + q - DX] = (float)e;
+    if (a.trace_z) a.trace_z[((long long)(t - 1) * a.n_filters + f) * DZ + q - DX] = (float)e;
+  } else {
+    a.est_y[f] = (float)e;
+    if (a.trace_y) a.trace_y[(long long)(t - 1) * a.n_filters + f] = (float)e;
+  }
+}
+
+// Sum over the filter's groups of partial q (rows of gpart have NV values).
+template <int NV>
+__device__ __forceinline__ double est_groups(const StepArgs& a, int rb, int G, int q) {
+  double e = 0.0;
+  // (unrolled: the loads of several groups in flight, added in order)
+#pragma unroll 16
+  for (int gg = 0; gg < G; ++gg) e += a.gpart[(long long)(rb + gg) * NV + q];
+  return e;
+}
+
+// Head workgroup of a run's new-cloud launch: while the launch's other
+// workgroups take step t + 1, the partial sums of one group's estimates of
+// step t (state copy and kpart of the previous launch, which this one does
+// not write) and of step t + 1's predicted observation (formed by the
+// previous launch).  A filter of one group is finished here, others by
+// k_run_stats.  A launch of its own for this took 7 us of a 40 us step, for
+// 4096 particles; next to the new clouds it costs nothing measurable.
 template <int DX, int DZ, bool YH>
-static __global__ __launch_bounds__(kBlock) void k_post(StepArgs a, const int2* rgroups, int next, int split) {
+__device__ __forceinline__ void est_head(const StepArgs& a, int b) {
+  constexpr int NV = DX + DZ + 1;
+  __shared__ double part[kBlock / kWave][NV];
+  const int2 rg = a.rgroups[b];
+  const int4 gi = a.ginfo[b];
+  const int f = rg.x, oo = gi.x, N = gi.y, rb = gi.z, G = gi.w;
+  const int act = a.act[f], t = a.tcur[f];
+  const unsigned char cb = a.cur[f];
+  const bool xz = act & 2, yh = YH && a.yp != nullptr && (act & 1);
+  if (!xz && !yh) return;
+  const int i = rg.y * kResGroup + threadIdx.x;
+  const int ic = min(i, N - 1);
+  const double w = 1.0 / N;
+  double v[NV];
+  const float* xs = a.x[copy_of(cb)];
+#pragma unroll
+  for (int d = 0; d < DX; ++d) v[d] = (double)xs[(long long)d * a.NT + oo + ic];
+#pragma unroll
+  for (int d = 0; d < DZ; ++d) v[DX + d] = (double)a.kpart_prev[(long long)(oo + ic) * DZ + d];
+  v[NV - 1] = yh ? (double)a.yp[oo + ic] : 0.0;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) v[q] = i < N ? w * v[q] : 0.0;
+  const double e = est_partial<NV>(v, part);
+  const int q = threadIdx.x;
+  if (q >= NV) return;
+  if (G > 1)
+    a.gpart[(long long)(rb + rg.y) * NV + q] = e;
+  else if (q < NV - 1 ? xz : yh)
+    est_store<DX, DZ>(a, f, q < NV - 1 ? t : t + 1, q, 0.0 + e);
+}
+
+// Statistics of the next step's outer log-weights, which the new-cloud kernel
+// has already computed (a run), for group g of filter f: gstat and the
+// non-finite check.  lw: this thread's weight (any value beyond the end).
+__device__ __forceinline__ void next_stats(const StepArgs& a, int f, int row, float lw, bool valid, ResScratch& sh) {
+  float mg;
+  double sg, qg;
+  res_group_stat_lw(lw, valid, mg, sg, qg, sh);
+  const float lv = valid ? lw : 0.f;
+  const int nonf = __syncthreads_or((!finitef(lv) && !(lv == -INFINITY)) ? 1 : 0);
+  if (threadIdx.x == 0) {
+    double* gs = a.gstat + 4LL * row;
+    gs[0] = (double)mg;
+    gs[1] = sg;
+    gs[2] = qg;
+    if (nonf) atomicOr(&a.flags[f], (uint32_t)F_NONFINITE);
+  }
+}
+
+// Between two new-cloud launches of a run (handles of up to
+// kPostFenceGroups groups, some filter with several): the next step's group
+// statistics, and, from the partial sums of the launch's head workgroups, the
+// estimates of the step before it and its predicted observation.
+// Latency-bound (4 us).
+template <int DX, int DZ, bool YH>
+static __global__ __launch_bounds__(kBlock) void k_run_stats(StepArgs a, const int2* rgroups) {
+  __shared__ ResScratch sh;
+  const int2 rg = rgroups[blockIdx.x];
+  const int4 gi = a.ginfo[blockIdx.x];
+  const int f = rg.x, g = rg.y;
+  const int oo = gi.x, N = gi.y, rb = gi.z, G = gi.w;
+  const int i = g * kResGroup + threadIdx.x;
+  // all loads in one memory round (clamped, masked below)
+  const float lwn = a.logw_next[oo + min(i, N - 1)];
+  const int act = a.act[f], t = a.tcur[f], act_n = a.act_n[f];
+  asm volatile("" ::"v"(lwn), "v"(act), "v"(t), "v"(act_n));
+  if (G > 1 && (act_n & 1)) next_stats(a, f, rb + g, lwn, i < N, sh);
+  constexpr int NV = DX + DZ + 1;
+  const int q = threadIdx.x;
+  if (g == 0 && G > 1 && q < NV) {
+    const bool on = q < NV - 1 ? (act & 2) : (YH && a.yp != nullptr && (act & 1));
+    if (on) est_store<DX, DZ>(a, f, q < NV - 1 ? t : t + 1, q, est_groups<NV>(a, rb, G, q));
+  }
+}
+
+// End of a look-ahead step taken on its own, of a learned step and of a run
+// (and of each step of a run of more than kPostFenceGroups groups; next: also
+// the next step's group statistics).  One workgroup per resampling group; a
+// filter's last workgroup (found with a counter it resets) adds up the
+// partials; with split, k_post_end or k_resolve does.  The view is the one
+// after the step; `took` the bit of act that says the filter took it.  When
+// tcur_n is given the view is copied there (the handle's own).
+template <int DX, int DZ, bool YH>
+static __global__ __launch_bounds__(kBlock) void k_post(StepArgs a, const int2* rgroups, int took, int next,
+                                                        int split) {
   constexpr int NV = DX + DZ + (YH ? 1 : 0);
   __shared__ ResScratch sh;
   __shared__ double part[kBlock / kWave][NV];
@@ -1542,98 +1754,77 @@ static __global__ __launch_bounds__(kBlock) void k_post(StepArgs a, const int2* 
 #pragma unroll
   for (int d = 0; d < DZ; ++d) raw[DX + d] = a.kpart[(long long)(oo + ic) * DZ + d];
   if constexpr (YH) raw[NV - 1] = a.yp[oo + ic];
-  const float lwn = (next && a.logw_next != nullptr) ? a.logw_next[oo + ic] : 0.f;
-  const int tf = (next && a.run_Tf != nullptr) ? a.run_Tf[f] : 0x7fffffff;
+  const float lwn = next ? a.logw_next[oo + ic] : 0.f;
   const int act = a.act[f], t = a.tcur[f], cu = a.cur[f];  // t: the step just taken
-  asm volatile("" ::"v"(tf), "v"(act), "v"(t), "v"(cu));
-  if (!act) return;
-  const unsigned char cb = (unsigned char)cu;
-  if (copy_of(cb)) {
+  asm volatile("" ::"v"(act), "v"(t), "v"(cu));
+  if (a.tcur_n != nullptr && g == 0 && threadIdx.x == 0) {
+    a.tcur_n[f] = t;
+    a.cur_n[f] = (unsigned char)cu;
+    a.act_n[f] = (unsigned char)act;
+  }
+  if (!(act & took)) return;
+  if (copy_of((unsigned char)cu)) {
 #pragma unroll
     for (int d = 0; d < DX; ++d) raw[d] = xo[d];
   }
   const double w = 1.0 / N;
-  const bool act_next = next && t < min(tf, a.run_T);
   double v[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) v[q] = i < N ? w * (double)raw[q] : 0.0;
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    const double r = seg_reduce_wave<OpAdd, kWave>(v[q]);
-    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave][q] = r;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < NV; q += kBlock)
-    a.gpart[(long long)(rb + g) * NV + q] = ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q];
-  if (act_next) {
-    float mg;
-    double sg, qg;
-    res_group_stat_lw(lwn, i < N, mg, sg, qg, sh);
-    const float lv = i < N ? lwn : 0.f;
-    const int nonf = __syncthreads_or((!finitef(lv) && !(lv == -INFINITY)) ? 1 : 0);
-    if (threadIdx.x == 0) {
-      double* gs = a.gstat + 4LL * (rb + g);
-      gs[0] = (double)mg;
-      gs[1] = sg;
-      gs[2] = qg;
-      if (nonf) atomicOr(&a.flags[f], (uint32_t)F_NONFINITE);
-    }
-  }
-  if (split) return;  // k_post_end finishes the filters
+  const double e = est_partial<NV>(v, part);
+  if (threadIdx.x < NV) a.gpart[(long long)(rb + g) * NV + threadIdx.x] = e;
+  if (next && (act & 1) && G > 1) next_stats(a, f, rb + g, lwn, i < N, sh);
+  if (split) return;
   __threadfence();
   if (threadIdx.x == 0) last = atomicAdd(&a.fcount[f], 1) == G - 1;
   __syncthreads();
   if (!last) return;
   __threadfence();
   if (threadIdx.x == 0) a.fcount[f] = 0;
-  post_finish<DX, DZ, YH>(a, f, rb, G, t, cb, next, act_next, kBlock);
-}
-
-// Filter-level end of k_post: the estimates from the group partials (in
-// group order), the next step's activity and the time advance.
-template <int DX, int DZ, bool YH>
-__device__ __forceinline__ void post_finish(const StepArgs& a, int f, int rb, int G, int t, unsigned char cb,
-                                            int next, bool act_next, int nthreads) {
-  constexpr int NV = DX + DZ + (YH ? 1 : 0);
-  for (int q = threadIdx.x; q < NV; q += nthreads) {
-    double e = 0.0;
-    // (unrolled: the loads of several groups in flight, added in order)
-#pragma unroll 16
-    for (int gg = 0; gg < G; ++gg) e += a.gpart[(long long)(rb + gg) * NV + q];
-    if (q < DX) {
-      a.est_x[f * DX + q] = (float)e;
-      if (a.trace_x) a.trace_x[((long long)(t - 1) * a.n_filters + f) * DX + q] = (float)e;
-    } else if (q < DX + DZ) {
-      a.est_z[f * DZ + q - DX] = (float)e;
-      if (a.trace_z) a.trace_z[((long long)(t - 1) * a.n_filters + f) * DZ + q - DX] = (float)e;
-    } else {
-      a.est_y[f] = (float)e;
-      if (a.trace_y) a.trace_y[(long long)(t - 1) * a.n_filters + f] = (float)e;
-    }
-  }
-  if (threadIdx.x == 0 && next) {
-    a.act[f] = act_next ? 1 : 0;
-    if (act_next) {
-      a.tcur[f] = t + 1;
-      a.cur[f] = (unsigned char)(cb ^ 1);
-    }
-  }
+  if (threadIdx.x < NV) est_store<DX, DZ>(a, f, t, threadIdx.x, est_groups<NV>(a, rb, G, threadIdx.x));
 }
 
 // With many groups in a launch the cross-workgroup hand-off of k_post (a
 // device-scope fence per workgroup writes back the L2 of its XCD) costs more
 // than a kernel boundary: k_post runs split (groups only) and this kernel,
-// one 64-thread workgroup per filter, finishes the filters.
+// one workgroup per filter, finishes the filters.
 template <int DX, int DZ, bool YH>
-static __global__ __launch_bounds__(kWave) void k_post_end(StepArgs a, int next) {
+static __global__ __launch_bounds__(kBlock) void k_post_end(StepArgs a, int took) {
+  constexpr int NV = DX + DZ + (YH ? 1 : 0);
   const int f = blockIdx.x;
-  const int tf = (next && a.run_Tf != nullptr) ? a.run_Tf[f] : 0x7fffffff;
-  const int rb = a.finfo[f].rg_base;
-  asm volatile("" ::"v"(tf), "v"(rb));
-  const FilterView fv = load_filter(a, f);
-  if (!fv.act) return;
-  const bool act_next = next && fv.t < min(tf, a.run_T);
-  post_finish<DX, DZ, YH>(a, f, rb, fv.ngroup, fv.t, (unsigned char)fv.cur, next, act_next, kWave);
+  const int act = a.act[f], t = a.tcur[f];
+  const FilterInfo fi = a.finfo[f];
+  if (!(act & took)) return;
+  if (threadIdx.x < NV) est_store<DX, DZ>(a, f, t, threadIdx.x, est_groups<NV>(a, fi.rg_base, fi.ngroup, threadIdx.x));
+}
+
+// Outer ancestors of every group of 256 new particles of the step about to be
+// taken (the view before it), one workgroup per group, for the handles of many
+// groups: there each of the new-cloud kernel's workgroups resolving its own
+// few particles (a dozen barriers and FP64 scans each) cost more than this
+// launch (256 ragged filters of 256 to 4096 particles: 475 us per step, 428 with
+// it).  Filters of one group resolve in the new-cloud kernel.
+// finish: also the estimates of the step before (the partial sums of k_post).
+template <int DX, int DZ, bool YH>
+static __global__ __launch_bounds__(kBlock) void k_resolve(StepArgs a, const int2* rgroups, int finish) {
+  constexpr int NV = DX + DZ + (YH ? 1 : 0);
+  __shared__ ResScratch sh;
+  __shared__ int res[kBlock];
+  const int2 rg = rgroups[blockIdx.x];
+  const int4 gi = a.ginfo[blockIdx.x];
+  const int f = rg.x, g = rg.y;
+  const int oo = gi.x, N = gi.y, rb = gi.z, G = gi.w;
+  const int act = a.act[f], t = a.tcur[f];
+  asm volatile("" ::"v"(act), "v"(t));
+  if (finish && g == 0 && (act & 2) && threadIdx.x < NV)
+    est_store<DX, DZ>(a, f, t, threadIdx.x, est_groups<NV>(a, rb, G, threadIdx.x));
+  if (!(act & 1) || G == 1) return;
+  const int k0 = g * kResGroup, np = min(kResGroup, N - k0);
+  const Key key = make_key(a.seed, (uint32_t)f);
+  const double u = uniform53(key, (uint32_t)(t + 1), 0u, P_OUTER_U);
+  const ResResult rr = resolve_points(LogSrc{a.logw + oo}, N, N, u, k0, np, a.gstat + 4LL * rb, G, res, sh, g == 0);
+  if (g == 0 && threadIdx.x == 0) res_finish(a, f, t + 1, N, rr);
+  if (threadIdx.x < np) a.anc[oo + k0 + threadIdx.x] = res[threadIdx.x];
 }
 
 // ---------------------------------------------------------------- new cloud
@@ -1682,14 +1873,27 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   // the next step's horizon (look-ahead run)
   const int tf_next = (!PLAIN && a.ell_next != nullptr && a.run_Tf != nullptr) ? a.run_Tf[f] : 0x7fffffff;
   const FilterView fv = load_filter(a, f);
-  if (!fv.act) return;
-  // learned step with accepted proposals: committed by commit_group
-  if (!PLAIN && fv.fb == 0) return;
+  // the view holds the filter's progress before the step (act_n given) or after
+  const int before = a.act_n != nullptr ? 1 : 0;
+  const int t = fv.t + before;  // the step being taken (0 at initialisation)
+  const bool act = fv.act & 1;
+  const unsigned char cb = (unsigned char)(fv.cur ^ (act ? before : 0));
+  const int dst = copy_of(cb), src = dst ^ 1;
   // look-ahead run: this kernel also computes the next step's weights (Fig. 4
   // steps 1-2 at t + 1) for the filters that take it; y_{t+1} fetched early
-  const bool fuse = !PLAIN && a.ell_next != nullptr && fv.t < min(tf_next, a.run_T);
+  const bool next = !PLAIN && t < min(tf_next, a.run_T);
+  const bool fuse = next && a.ell_next != nullptr;
+  if (before && tile.z == 0 && threadIdx.x == 0) {
+    // the view after the step (the new clouds are in slot order)
+    a.tcur_n[f] = act ? t : fv.t;
+    a.cur_n[f] = act ? (unsigned char)(cb | (2 << dst)) : (unsigned char)fv.cur;
+    a.act_n[f] = act ? (unsigned char)(2 | (next ? 1 : 0)) : (unsigned char)0;
+  }
+  if (!act) return;
+  // learned step with accepted proposals: committed by commit_group
+  if (!PLAIN && fv.fb == 0) return;
   float yn[DY];
-  if (!PLAIN && a.ell_next != nullptr) load_y<Mdl>(a, f, min(fv.t, a.run_T - 1) + 1, yn);
+  if (!PLAIN && a.ell_next != nullptr) load_y<Mdl>(a, f, min(t, a.run_T - 1) + 1, yn);
   const int N = fv.N, M = fv.M;
   const int s = threadIdx.x / SEG;
   const int ls = threadIdx.x % SEG;
@@ -1697,10 +1901,10 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   const bool vk = k < N;
   const int oo = fv.oo;
   const long long io = fv.io;
-  const int t = fv.t;  // already advanced (0 at initialisation)
-  const unsigned char cb = (unsigned char)fv.cur;
-  const int dst = copy_of(cb), src = dst ^ 1;
   const Key key = make_key(a.seed, (uint32_t)f);
+  const OuterDraws ud = outer_draws(key, t, k, PLAIN ? P_DPF_ANC_U : P_CAND_U);
+  // filters of one resampling group form their outer cumulative sum here
+  const bool self = a.advance && fv.ngroup == 1;
 
   // With a wave or more per outer particle, the ancestor and the candidate
   // are single draws done by the segment's first wave with wave-wide scans.
@@ -1734,11 +1938,10 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     __shared__ float xw_sh[NSEG][DX];
     __shared__ int d1_sh[NSEG];
     const int G = fv.ngroup;
-    const bool resolve = a.advance && !a.anc_ready;
+    const bool resolve = a.advance && !a.anc_ready && !self;
     const bool blk = resolve && G > kWave;  // many groups: the whole workgroup resolves
     if (blk) {
-      const double u = uniform53(key, (uint32_t)t, 0u, P_OUTER_U);
-      const ResResult rr = resolve_points(LogSrc{a.logw + oo}, N, N, u, tile.y, min(NSEG, N - tile.y),
+      const ResResult rr = resolve_points(LogSrc{a.logw + oo}, N, N, ud.outer, tile.y, min(NSEG, N - tile.y),
                                           a.gstat + 4LL * a.finfo[f].rg_base, G, anc_sh, rsh, tile.z == 0);
       if (tile.z == 0 && threadIdx.x == 0) res_finish(a, f, t, N, rr);
     }
@@ -1748,13 +1951,17 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
 #pragma unroll
     for (int d = 0; d < DX; ++d) xpw[d] = xw[d] = 0.f;
     if (ls < kWave && vk) {
-      if (blk) {
+      const bool first = tile.z == 0 && s == 0;
+      if (self) {
+        double C[4];
+        const ResResult rr = self_cdf(a.logw + oo, N, first, C);
+        pw = self_point(C, N, rr.total, sys_point(k, ud.outer, rr.total, N));
+        if (first && ls == 0) res_finish(a, f, t, N, rr);
+      } else if (blk) {
         pw = anc_sh[s];
       } else if (resolve) {
         ResResult rr;
-        const double u = uniform53(key, (uint32_t)t, 0u, P_OUTER_U);
-        const bool first = tile.z == 0 && s == 0;
-        pw = resolve_point_w0(LogSrc{a.logw + oo}, N, N, u, k, gst, G, first, rr);
+        pw = resolve_point_w0(LogSrc{a.logw + oo}, N, N, ud.outer, k, gst, G, first, rr);
         if (first && ls == 0) res_finish(a, f, t, N, rr);
       } else {
         pw = a.advance ? a.anc[oo + k] : k;  // identity at initialisation
@@ -1779,8 +1986,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         }
       }
       // candidate (look-ahead) / inner ancestor (plain) over the parent's ell
-      const double uc = uniform53(key, (uint32_t)t, (uint32_t)k, PLAIN ? P_DPF_ANC_U : P_CAND_U);
-      cw = select_w0<(SEG * JPT + kWave - 1) / kWave>(a.ell + io + (long long)pw * M, M, uc, d1);
+      cw = select_w0<(SEG * JPT + kWave - 1) / kWave>(a.ell + io + (long long)pw * M, M, ud.cand, d1);
       // every lane of the wave computes the new x (same counters)
       float zc[DZ], nu[DX];
       if constexpr (kPreZ) {
@@ -1804,7 +2010,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         normals<DX>(key, (uint32_t)t, (uint32_t)pw, (uint32_t)cw, P_LA_X, nu);
       Mdl::fx(as_prm(a.prm), xpw, zc, nu, PLAIN ? t : t - 1, xw);
       if (ls == 0) {
-        if (!a.anc_ready) a.anc[oo + k] = pw;
+        if (!a.anc_ready || self) a.anc[oo + k] = pw;
         a.sel[oo + k] = cw;
 #pragma unroll
         for (int d = 0; d < DX; ++d) a.x[dst][(long long)d * a.NT + oo + k] = xw[d];
@@ -1848,20 +2054,34 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   } else {
   // ---- 0. outer ancestors of this tile's new particles -------------------
   // (resolved here, also for the learned step's fallback filters)
-  if (a.advance && !a.anc_ready) {
-    const int np = min(NSEG, N - tile.y);
-    const int G = a.finfo[f].ngroup;
-    const double u = uniform53(key, (uint32_t)t, 0u, P_OUTER_U);
-    const ResResult rr = resolve_points(LogSrc{a.logw + oo}, N, N, u, tile.y, np,
-                                        a.gstat + 4LL * a.finfo[f].rg_base, G, anc_sh, rsh, tile.z == 0);
-    if (tile.z == 0 && threadIdx.x == 0) res_finish(a, f, t, N, rr);
-  } else if (threadIdx.x < NSEG) {
-    const int kk = tile.y + threadIdx.x;
-    anc_sh[threadIdx.x] = a.advance ? (kk < N ? a.anc[oo + kk] : 0) : kk;  // identity at initialisation
+  p = 0;
+  if (self) {
+    // each wave its own particles'
+    double C[4];
+    const bool first = tile.z == 0 && threadIdx.x < kWave;
+    const ResResult rr = self_cdf(a.logw + oo, N, first, C);
+    constexpr int NSW = kWave / SEG;
+    const int s0 = s - s % NSW;
+#pragma unroll
+    for (int q = 0; q < NSW; ++q) {
+      const int kq = tile.y + s0 + q;
+      const int pq = kq < N ? self_point(C, N, rr.total, sys_point(kq, ud.outer, rr.total, N)) : 0;
+      if (s == s0 + q) p = pq;
+    }
+    if (first && threadIdx.x == 0) res_finish(a, f, t, N, rr);
+  } else {
+    if (a.advance && !a.anc_ready) {
+      const int np = min(NSEG, N - tile.y);
+      const ResResult rr = resolve_points(LogSrc{a.logw + oo}, N, N, ud.outer, tile.y, np, a.gstat + 4LL * tile.w,
+                                          fv.ngroup, anc_sh, rsh, tile.z == 0);
+      if (tile.z == 0 && threadIdx.x == 0) res_finish(a, f, t, N, rr);
+      __syncthreads();
+      p = vk ? anc_sh[s] : 0;
+    } else if (vk) {
+      p = a.advance ? a.anc[oo + k] : k;  // identity at initialisation
+    }
   }
-  __syncthreads();
-  p = vk ? anc_sh[s] : 0;
-  if (vk && ls == 0 && !a.anc_ready) a.anc[oo + k] = p;
+  if (vk && ls == 0 && (!a.anc_ready || self)) a.anc[oo + k] = p;
   pc = (PLAIN || ident_slots(cb, src)) ? p : a.ind[src][oo + p];
 #pragma unroll
   for (int d = 0; d < DX; ++d) xp[d] = a.x[src][(long long)d * a.NT + oo + p];
@@ -1890,13 +2110,12 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     cdf[s][r * SEG + ls] = carry + c;
     carry += tot;
   }
-  __syncthreads();
+  seg_lds_sync<SEG>();
   if (ls == 0) {
-    const double u = uniform53(key, (uint32_t)t, (uint32_t)k, PLAIN ? P_DPF_ANC_U : P_CAND_U);
-    csel[s] = vk ? cdf_search(cdf[s], M, sys_point(0, u, cdf[s][M - 1], 1)) : 0;
+    csel[s] = vk ? cdf_search(cdf[s], M, sys_point(0, ud.cand, cdf[s][M - 1], 1)) : 0;
     if (vk) a.sel[oo + k] = csel[s];
   }
-  __syncthreads();
+  seg_lds_sync<SEG>();
   c = csel[s];
 
   // ---- 2. the new outer particle ----------------------------------------
@@ -1917,14 +2136,14 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       for (int d = 0; d < DX; ++d) a.x[dst][(long long)d * a.NT + oo + k] = xw[d];
     }
   }
-  __syncthreads();
+  seg_lds_sync<SEG>();
 #pragma unroll
   for (int d = 0; d < DX; ++d) xn[d] = xs_sh[s][d];
 
   }
   // the new clouds are written in slot order: the slots of copy dst become
   // the identity
-  if (!PLAIN && tile.z == 0 && threadIdx.x == 0 && !ident_slots(cb, dst))
+  if (!PLAIN && !before && tile.z == 0 && threadIdx.x == 0 && !ident_slots(cb, dst))
     a.cur[f] = (unsigned char)(cb | (2 << dst));
   const float* zp = a.z[src] + (io + (long long)pc * M) * DZ;
   const float* ep = a.ell + io + (long long)p * M;
@@ -1967,7 +2186,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     carry += tot;
   }
   seg_lds_sync<SEG>();
-  const double u_in = uniform53(key, (uint32_t)t, (uint32_t)k, P_INNER_U);
+  const double u_in = ud.inner;
   const double tot2 = cdf[s][M - 1];
 
   // ---- 4. gather + propagate (+ measurement update in look-ahead mode) ---
@@ -2022,7 +2241,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         const float l0 = pj.logpy(P, y_row<Mdl>(a, f, t));
         // the next step's look-ahead likelihood of these new inner particles
         const float g0 = fuse ? la_logpy_wave<Mdl>(a, key, t + 1, k, jj, xn, zn,
-                                                   y_row<Mdl>(a, f, min(fv.t, a.run_T - 1) + 1), ca)
+                                                   y_row<Mdl>(a, f, min(t, a.run_T - 1) + 1), ca)
                               : 0.f;
         if (on) {
           lv = l0;
@@ -2166,7 +2385,12 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
 // through one L2.
 template <class Mdl, int SEG, int JPT, bool PLAIN>
 static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<Mdl>()))) void k_newcloud(StepArgs a) {
-  const int ti = Mdl::kStreamZ ? xcd_contiguous_tile((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+  if (!PLAIN && (int)blockIdx.x < a.n_head) {
+    est_head<Mdl::DX, Mdl::DZ, has_yhat<Mdl>()>(a, blockIdx.x);
+    return;
+  }
+  const int b = PLAIN ? (int)blockIdx.x : (int)blockIdx.x - a.n_head;
+  const int ti = Mdl::kStreamZ ? xcd_contiguous_tile(b, (int)gridDim.x - (PLAIN ? 0 : a.n_head)) : b;
   newcloud_tile<Mdl, SEG, JPT, PLAIN>(a, ti);
 }
 

@@ -74,6 +74,8 @@ struct Layout {
   size_t xrb;
   // predicted observation: per-outer partial sums (two, like ell) and [F]
   size_t yp0, yp1, est_y;
+  // a run's second view of the filters' progress, and second kpart
+  size_t tcur1, cur1, act1, kpart1;
   int NT = 0;
   long long NMT = 0;
   int n_tiles = 0, n_rgroups = 0;
@@ -181,6 +183,10 @@ static dpf_status plan(const dpf_config* c, const Engine*& eng, Layout& L) {
   L.yp0 = carve(cur, NT * 4);
   L.yp1 = carve(cur, NT * 4);
   L.est_y = carve(cur, F * 4);
+  L.tcur1 = carve(cur, F * 4);
+  L.cur1 = carve(cur, F);
+  L.act1 = carve(cur, F);
+  L.kpart1 = carve(cur, NT * dz * 4);
   L.total = cur;
   return DPF_OK;
 }
@@ -205,6 +211,7 @@ struct dpf_handle {
   std::vector<float> prm_h;
   std::vector<TileClass> classes;
   std::vector<int> fcls;  // tile class of each filter
+  bool one_group = false;  // every filter has one resampling group
   // multi-step graph cache
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -326,9 +333,10 @@ static dpf_status launch_classes(dpf_handle* h, int op, StepArgs a, int grid_cap
     a.n_tiles = tc.n_tiles;
     TileClass g = tc;
     if (grid_cap > 0 && g.n_tiles > grid_cap) g.n_tiles = grid_cap;
-    g.n_tiles += a.n_commit;  // extra head workgroups (first class only)
+    g.n_tiles += a.n_commit + a.n_head;  // extra head workgroups (first class only)
     dpf_status s = h->eng->launch(op, a, g, h->stream);
     a.n_commit = 0;
+    a.n_head = 0;
     if (s != DPF_OK) return s;
   }
   return DPF_OK;
@@ -340,16 +348,35 @@ static dpf_status launch_finalize(dpf_handle* h, const StepArgs& a) {
   return h->eng->finalize(a, h->F, h->stream);
 }
 
-// End of a look-ahead step: estimates; next = 1 in a look-ahead run (the
-// next step's group statistics, activity and time advance, which spare that
-// step its statistics kernel).  Up to kPostFenceGroups groups in the handle:
-// one launch whose last workgroup per filter finishes it; more: the group
-// pass and a per-filter pass as two launches (same arithmetic).
+// Up to kPostFenceGroups resampling groups in the handle the last workgroup of
+// a filter finishes its estimates (a device-scope fence per workgroup); more:
+// a launch of its own does.
 constexpr int kPostFenceGroups = 64;
 
-static dpf_status launch_post(dpf_handle* h, const StepArgs& a, int next) {
-  const int split = h->L.n_rgroups > kPostFenceGroups ? 1 : 0;
-  return h->eng->post(a, at<int2>(h, h->L.rgroups), h->L.n_rgroups, h->F, next, split, h->stream);
+static bool many_groups(const dpf_handle* h) { return h->L.n_rgroups > kPostFenceGroups; }
+
+static dpf_status launch_end(dpf_handle* h, int op, const StepArgs& a, int took, int next, int split) {
+  return h->eng->post(op, a, at<int2>(h, h->L.rgroups), h->L.n_rgroups, h->F, StepEnd{took, next, split}, h->stream);
+}
+
+// The estimates of the step whose view a holds (its progress after the step),
+// copied to the handle's own view when tcur_n is set.
+static dpf_status launch_post(dpf_handle* h, const StepArgs& a, int took) {
+  const int split = many_groups(h) ? 1 : 0;
+  const dpf_status s = launch_end(h, END_POST, a, took, 0, split);
+  return s == DPF_OK && split ? launch_end(h, END_FINISH, a, took, 0, 0) : s;
+}
+
+// View 0 is the handle's own progress, view 1 the other one of a step.
+static void set_view(dpf_handle* h, StepArgs& a, int v) {
+  a.tcur = at<int>(h, v ? h->L.tcur1 : h->L.tcur);
+  a.cur = at<unsigned char>(h, v ? h->L.cur1 : h->L.cur);
+  a.act = at<unsigned char>(h, v ? h->L.act1 : h->L.act);
+}
+static void set_view_after(dpf_handle* h, StepArgs& a, int v) {
+  a.tcur_n = at<int>(h, v ? h->L.tcur1 : h->L.tcur);
+  a.cur_n = at<unsigned char>(h, v ? h->L.cur1 : h->L.cur);
+  a.act_n = at<unsigned char>(h, v ? h->L.act1 : h->L.act);
 }
 
 static dpf_status queue_init(dpf_handle* h) {
@@ -430,6 +457,7 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
     h->finfo_h[f] = FilterInfo{rg, G, 0, 0};
     rg += G;
   }
+  h->one_group = rg == F;
   h->fcls.resize(F);
   for (int f = 0; f < F; ++f) h->fcls[f] = class_of(h->M[f]);
   hipError_t e = hipSuccess;
@@ -530,15 +558,43 @@ extern "C" dpf_status dpf_destroy(dpf_handle* h) {
   return DPF_OK;
 }
 
-// fuse (look-ahead runs only): 0 a plain step; 1 the first step of a run,
-// whose new-cloud kernel also computes the next step's weights and whose
-// step-end kernel also prepares the next step's resampling (group
-// statistics, time advance); 2 a later step of the run (no weights or
-// statistics kernel: the previous step did their work).  par: the weight
-// buffers this step reads (the next step's go to the other pair).
+// The plain DPF's step.
+static dpf_status queue_plain_step(dpf_handle* h, StepArgs a) {
+  dpf_status s = phase_mark(h, 0);
+  if (s == DPF_OK) s = launch_classes(h, OP_DPF_WEIGHTS, a);
+  if (s == DPF_OK) s = phase_mark(h, 1);
+  if (s == DPF_OK) {
+    hipLaunchKernelGGL(k_res_stats, dim3(h->L.n_rgroups), dim3(kBlock), 0, h->stream, a,
+                       at<int2>(h, h->L.rgroups), 1);
+    LAUNCH_CHECK("k_res_stats");
+  }
+  if (s == DPF_OK) s = phase_mark(h, 2);
+  if (s == DPF_OK) s = launch_classes(h, OP_NEWCLOUD_PLAIN, a);
+  if (s == DPF_OK) s = phase_mark(h, 3);
+  if (s == DPF_OK) s = launch_finalize(h, a);
+  if (s == DPF_OK) s = phase_mark(h, 4);
+  h->mom_valid = a.mom != nullptr;
+  return s;
+}
+
+// One step.  fuse (look-ahead runs only): 0 a step on its own; 1 the first
+// step of a run; 2 a later one (its weights were computed by the previous
+// step's new-cloud kernel).  In a run, par alternates: the view, weight and
+// kpart buffers this step reads (it writes the other view and the next
+// step's weights to the other pair); last: the run's last step.
+//
+// Launches of a look-ahead step between its weights and the next's: the
+// new-cloud kernel, and
+//   every filter of one group (N <= 256): nothing -- the new-cloud kernel
+//     resolves the ancestors from the weights, and the next one's head
+//     workgroups form this step's estimates;
+//   up to kPostFenceGroups groups: k_run_stats (the next step's group
+//     statistics);
+//   more: k_post (group statistics and partial estimates) and k_resolve (the
+//     next step's ancestors, the estimates).
 static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride, const unsigned char* active,
                              const int* run_Tf, int run_T, float* trace_x, float* trace_z, int fuse = 0,
-                             int par = 0) {
+                             int par = 0, bool last = true) {
   StepArgs a = make_args(h);
   a.Y = Y;
   a.y_tstride = y_tstride;
@@ -548,35 +604,60 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
   a.trace_x = trace_x;
   a.trace_z = trace_z;
   a.advance = 1;
-  const bool plain = h->algo == DPF_ALGO_PLAIN;
+  h->ell_sel = fuse ? par : 0;
+  if (h->algo == DPF_ALGO_PLAIN) return queue_plain_step(h, a);
+  const bool many = many_groups(h) && !h->one_group;
+  a.rgroups = at<int2>(h, h->L.rgroups);
   if (fuse) {
     float* e[2] = {at<float>(h, h->L.ell), at<float>(h, h->L.ell1)};
     float* w[2] = {at<float>(h, h->L.logw), at<float>(h, h->L.logw1)};
+    float* k[2] = {at<float>(h, h->L.kpart), at<float>(h, h->L.kpart1)};
     a.ell = e[par];
     a.logw = w[par];
     a.ell_next = e[par ^ 1];
     a.logw_next = w[par ^ 1];
+    a.kpart = k[par];
+    a.kpart_prev = k[par ^ 1];
   }
-  h->ell_sel = fuse ? par : 0;
-  if (h->predict && !plain) {
+  if (h->predict) {
     float* yb[2] = {at<float>(h, h->L.yp0), at<float>(h, h->L.yp1)};
     a.yp = yb[fuse ? par : 0];
     a.yp_next = fuse ? yb[par ^ 1] : nullptr;
     a.trace_y = h->ytrace;
   }
+  const int view = fuse ? par : 0;
+  set_view(h, a, view);
   dpf_status s = phase_mark(h, 0);
-  const int wop = plain ? OP_DPF_WEIGHTS : (h->n_comp > 0 ? OP_LA_WEIGHTS_NESTED : OP_LA_WEIGHTS);
-  if (s == DPF_OK && fuse != 2) s = launch_classes(h, wop, a);
+  if (s == DPF_OK && fuse != 2) s = launch_classes(h, h->n_comp > 0 ? OP_LA_WEIGHTS_NESTED : OP_LA_WEIGHTS, a);
   if (s == DPF_OK) s = phase_mark(h, 1);
-  if (s == DPF_OK && fuse != 2) {
+  if (s == DPF_OK && fuse != 2 && !h->one_group) {
     hipLaunchKernelGGL(k_res_stats, dim3(h->L.n_rgroups), dim3(kBlock), 0, h->stream, a,
-                       at<int2>(h, h->L.rgroups), 1);
+                       at<int2>(h, h->L.rgroups), 0);
     LAUNCH_CHECK("k_res_stats");
+    if (many) s = launch_end(h, END_RESOLVE, a, 0, 0, 0);
   }
   if (s == DPF_OK) s = phase_mark(h, 2);
-  if (s == DPF_OK) s = launch_classes(h, plain ? OP_NEWCLOUD_PLAIN : OP_NEWCLOUD_LA, a);
+  set_view_after(h, a, view ^ 1);
+  a.anc_ready = many ? 1 : 0;
+  a.n_head = fuse && !many ? h->L.n_rgroups : 0;
+  if (s == DPF_OK) s = launch_classes(h, OP_NEWCLOUD_LA, a);
   if (s == DPF_OK) s = phase_mark(h, 3);
-  if (s == DPF_OK) s = plain ? launch_finalize(h, a) : launch_post(h, a, fuse ? 1 : 0);
+  // the kernels after the step, on the view after it
+  StepArgs b = a;
+  set_view(h, b, view ^ 1);
+  b.tcur_n = nullptr;
+  b.cur_n = b.act_n = nullptr;
+  if (s == DPF_OK && fuse && many && !last) {
+    s = launch_end(h, END_POST, b, 2, 1, 1);
+    b.logw = b.logw_next;
+    if (s == DPF_OK) s = launch_end(h, END_RESOLVE, b, 2, 1, 0);
+  } else if (s == DPF_OK) {
+    if (fuse && !many && !h->one_group) s = launch_end(h, END_RUN_STATS, a, 0, 0, 0);
+    if (s == DPF_OK && last) {
+      if (view == 0) set_view_after(h, b, 0);
+      s = launch_post(h, b, 2);
+    }
+  }
   if (s == DPF_OK) s = phase_mark(h, 4);
   h->mom_valid = a.mom != nullptr;
   return s;
@@ -639,7 +720,7 @@ static dpf_status queue_learned_step(dpf_handle* h, const float* Y, long long y_
   a.n_commit = h->L.n_rgroups;
   if (s == DPF_OK) s = launch_classes(h, OP_NEWCLOUD_FALLBACK, a, kGatedGrid);
   if (s == DPF_OK) s = phase_mark(h, 3);
-  if (s == DPF_OK) s = launch_post(h, a, 0);
+  if (s == DPF_OK) s = launch_post(h, a, 1);
   if (s == DPF_OK) s = phase_mark(h, 4);
   h->mom_valid = true;
   return s;
@@ -778,7 +859,7 @@ static dpf_status queue_run_step(dpf_handle* h, int mode, const float* d_Y, int 
   // (the fused next-step weights are the paired form: a nested run takes
   // every step whole)
   if (h->algo == DPF_ALGO_LOOKAHEAD && T > 1 && h->n_comp == 0)
-    return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt, q == 0 ? 1 : 2, q & 1);
+    return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt, q == 0 ? 1 : 2, q & 1, q == T - 1);
   return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt);
 }
 
@@ -816,7 +897,9 @@ static dpf_status run_steps(dpf_handle* h, int mode, const float* d_Y, int32_t T
     if (st != DPF_OK || T == 1) return st;
   }
   const int S = T - 1 < kGraphChunk ? T - 1 : kGraphChunk;
-  const int R = (T - 1) % S;  // tail steps T - R .. T - 1
+  // tail steps T - R .. T - 1 (a run's last step differs from the others, so
+  // of several chunks the last one is a tail too)
+  const int R = T - 1 > S && (T - 1) % S == 0 ? S : (T - 1) % S;
   // every value make_args copies into the captured kernel arguments that can
   // change between runs is part of the key: the buffers, the stream, the
   // mode, whether cloud moments are maintained, and the fallback threshold
@@ -864,7 +947,7 @@ static dpf_status run_steps(dpf_handle* h, int mode, const float* d_Y, int32_t T
     memcpy(h->g_key, key, sizeof(key));
     h->g_T = T;
   }
-  for (int q = 1; q + S <= T; q += S) HIP_TRY(hipGraphLaunch(h->gexec, h->stream));
+  for (int q = 1; q + S <= T - R; q += S) HIP_TRY(hipGraphLaunch(h->gexec, h->stream));
   if (R > 0) HIP_TRY(hipGraphLaunch(h->gexec_tail, h->stream));
   // (the captured steps do not update the host's record of the buffers)
   if (mode == 0 && h->algo == DPF_ALGO_LOOKAHEAD && h->n_comp == 0) h->ell_sel = (T - 1) & 1;
