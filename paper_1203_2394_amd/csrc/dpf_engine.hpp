@@ -41,9 +41,25 @@ static constexpr ClassShape kClasses[] = {{32, 1}, {64, 1}, {128, 1}, {64, 4},  
                                           {16, 2}, {16, 4}, {16, 8}};
 constexpr int kNumClasses = 14;
 constexpr int kNumDefaultClasses = 6;
+// Narrow classes, which stand in for the default ones of up to 128 lanes and
+// one inner particle per lane (M <= ord): several outer particles per wave, so
+// what a segment costs whatever its size (searches, scans, reductions, the
+// offsets' Philox block) is shared by more inner particles, and fewer idle
+// lanes where M does not fill the default class.  Their log-sum-exps add in
+// the default class's order, so a filter's particles and weights are the same
+// bits in either.  Built for the models of one or two inner components
+// (narrow_model); indices from kNumClasses on, not public.  256 filters of
+// 200 x 20: 51.8 us per step in 32 lanes, 34.3 in 8 x 3; 32 of 1000 x 100: 105 us
+// in 128 lanes, 62 in 16 x 7.
+struct NarrowShape {
+  int seg, jpt, ord;
+};
+static constexpr NarrowShape kNarrow[] = {{8, 1, 32},  {8, 2, 32},  {8, 3, 32},  {8, 4, 32},  {16, 3, 64}, {16, 4, 64},
+                                          {16, 5, 128}, {16, 6, 128}, {16, 7, 128}, {16, 8, 128}};
+constexpr int kNumNarrow = 10;
 
 struct TileClass {
-  int cls;
+  int cls;  // kClasses, then kNarrow
   int n_tiles;
   int4* d_tiles;
 };
@@ -94,6 +110,7 @@ struct Engine {
   dpf_status (*post)(int op, const StepArgs& a, const int2* rgroups, int n_rgroups, int F, const StepEnd& e,
                      hipStream_t s);
   bool yhat;  // the look-ahead pass can form the predicted observation
+  bool narrow;  // the narrow classes are built
 };
 
 extern const Engine kEngLinGauss, kEngNonLin, kEngHighDim, kEngTwoDim, kEngFourDim, kEngTwoDimZ;

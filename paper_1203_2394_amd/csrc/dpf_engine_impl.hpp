@@ -62,6 +62,40 @@ static void launch_op(int op, const StepArgs& a, int n, hipStream_t s) {
   }
 }
 
+// Narrow classes: the small models (a segment's fixed work outweighs its inner
+// particles' there; NONLIN's eight-component clouds and the wide z gain
+// nothing).
+template <class Mdl>
+constexpr bool narrow_model() { return Mdl::DZ <= 2; }
+
+template <class Mdl, int K>
+static void launch_narrow(int op, const StepArgs& a, int n, hipStream_t s) {
+  constexpr int SEG = kNarrow[K].seg, JPT = kNarrow[K].jpt, ORD = kNarrow[K].ord;
+  switch (op) {
+    case OP_INIT_LA:
+      hipLaunchKernelGGL((k_init<Mdl, SEG, JPT, false>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+    case OP_INIT_PLAIN:
+      hipLaunchKernelGGL((k_init<Mdl, SEG, JPT, true>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+    case OP_LA_WEIGHTS:
+      hipLaunchKernelGGL((k_la_weights<Mdl, SEG, JPT, ORD>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+    case OP_LA_WEIGHTS_NESTED:
+      hipLaunchKernelGGL((k_la_weights_nested<Mdl, SEG, JPT, ORD>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+    case OP_DPF_WEIGHTS:
+      hipLaunchKernelGGL((k_dpf_weights<Mdl, SEG, JPT, ORD>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+    case OP_NEWCLOUD_LA:
+      hipLaunchKernelGGL((k_newcloud<Mdl, SEG, JPT, false, ORD>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+    case OP_NEWCLOUD_PLAIN:
+      hipLaunchKernelGGL((k_newcloud<Mdl, SEG, JPT, true, ORD>), dim3(n), dim3(kBlock), 0, s, a);
+      break;
+  }
+}
+
 template <class Mdl>
 static dpf_status engine_mlp_state(const StepArgs& a, hipStream_t s) {
   if constexpr (learned_model<Mdl>()) {
@@ -87,6 +121,28 @@ static dpf_status engine_mdn_draw(const StepArgs& a, hipStream_t s) {
 template <class Mdl>
 static dpf_status engine_launch(int op, const StepArgs& a, const TileClass& tc, hipStream_t s) {
   const int n = tc.n_tiles;
+  if constexpr (narrow_model<Mdl>()) {
+    if (tc.cls >= kNumClasses) {
+      // (the learned passes and the moments run in the public classes)
+      if (op == OP_LEARNED_INNER || op == OP_MOMENTS || op == OP_LA_WEIGHTS_FALLBACK || op == OP_NEWCLOUD_FALLBACK)
+        return fail(DPF_EUNSUPPORTED, "operation %d has no narrow class", op);
+      switch (tc.cls - kNumClasses) {
+        case 0: launch_narrow<Mdl, 0>(op, a, n, s); break;
+        case 1: launch_narrow<Mdl, 1>(op, a, n, s); break;
+        case 2: launch_narrow<Mdl, 2>(op, a, n, s); break;
+        case 3: launch_narrow<Mdl, 3>(op, a, n, s); break;
+        case 4: launch_narrow<Mdl, 4>(op, a, n, s); break;
+        case 5: launch_narrow<Mdl, 5>(op, a, n, s); break;
+        case 6: launch_narrow<Mdl, 6>(op, a, n, s); break;
+        case 7: launch_narrow<Mdl, 7>(op, a, n, s); break;
+        case 8: launch_narrow<Mdl, 8>(op, a, n, s); break;
+        case 9: launch_narrow<Mdl, 9>(op, a, n, s); break;
+        default: return fail(DPF_EUNSUPPORTED, "no kernel class %d", tc.cls);
+      }
+      LAUNCH_CHECK("step kernel");
+      return DPF_OK;
+    }
+  }
   switch (tc.cls) {
     case 0: launch_op<Mdl, 32, 1>(op, a, n, s); break;
     case 1: launch_op<Mdl, 64, 1>(op, a, n, s); break;
@@ -177,7 +233,8 @@ static Engine make_engine(void (*derive)(const double*, std::vector<float>&)) {
                 engine_rb<Mdl>,
                 engine_finalize<Mdl>,
                 engine_post<Mdl>,
-                has_yhat<Mdl>()};
+                has_yhat<Mdl>(),
+                narrow_model<Mdl>()};
 }
 
 }  // namespace dpf

@@ -266,6 +266,59 @@ __device__ __forceinline__ float seg_lse(Lse l, SegScratch& sh) {
   return (m == -INFINITY) ? -INFINITY : m + fast_log(s);
 }
 
+// Log-sum-exp over a narrow segment's items (v[r]: item ls + r SEG, -inf where
+// there is none): the bits that a segment of ORD lanes with one item each
+// gets, which the narrow class stands in for (these weights decide the
+// resampling).
+template <int SEG, int JPT, int ORD>
+__device__ __forceinline__ float seg_lse_ord(const float* v, SegScratch& sh) {
+  float ml = -INFINITY, x[JPT];
+#pragma unroll
+  for (int r = 0; r < JPT; ++r)
+    if (finitef(v[r])) ml = fmaxf(ml, v[r]);
+  const float m = seg_max<SEG>(ml, sh);
+#pragma unroll
+  for (int r = 0; r < JPT; ++r) x[r] = finitef(v[r]) ? fast_exp(v[r] - m) : 0.f;
+  const float s = seg_sum_ord<SEG, JPT, ORD>(x);
+  return (m == -INFINITY) ? -INFINITY : m + fast_log(s);
+}
+
+// A segment's accumulated log-sum-exp and sum: ORD = 0 each lane's items as
+// they come (online), then the lanes; else in the order of an ORD-lane segment.
+template <int SEG, int JPT, int ORD>
+struct SegLse {
+  Lse l;
+  float v[ORD ? JPT : 1];
+  __device__ SegLse() {
+#pragma unroll
+    for (int r = 0; r < (ORD ? JPT : 1); ++r) v[r] = -INFINITY;
+  }
+  __device__ __forceinline__ void add(int r, float e) {
+    if constexpr (ORD == 0) l.add(e);
+    else v[r] = e;
+  }
+  __device__ __forceinline__ float get(SegScratch& sh) const {
+    if constexpr (ORD == 0) return seg_lse<SEG>(l, sh);
+    else return seg_lse_ord<SEG, JPT, ORD>(v, sh);
+  }
+};
+template <int SEG, int JPT, int ORD>
+struct SegSum {
+  float v[ORD ? JPT : 1];
+  __device__ SegSum() {
+#pragma unroll
+    for (int r = 0; r < (ORD ? JPT : 1); ++r) v[r] = 0.f;
+  }
+  __device__ __forceinline__ void add(int r, float q, float h) {
+    if constexpr (ORD == 0) v[0] += q * h;
+    else v[r] = q * h;
+  }
+  __device__ __forceinline__ float get(SegScratch& sh) const {
+    if constexpr (ORD == 0) return seg_sum<SEG>(v[0], sh);
+    else return seg_sum_ord<SEG, JPT, ORD>(v);
+  }
+};
+
 // Block-wide (256 threads) FP64 reductions and scans in a fixed order:
 // DPP within each wave, then the four wave results in order.
 __device__ __forceinline__ double block_sum_256(double v, double* red4) {
@@ -454,7 +507,7 @@ __device__ __forceinline__ float la_ell(float lam, float g) {
   asm volatile("" : "+v"(g));
   return lam + g;
 }
-template <class Mdl, int SEG, int JPT>
+template <class Mdl, int SEG, int JPT, int ORD = 0>
 __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool fallback) {
   __shared__ SegScratch sh;
   const int4 tile = a.tiles[ti];
@@ -486,10 +539,10 @@ __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool 
   const float* zrow = a.z[src] + (io + (long long)ci * M) * Mdl::DZ;
   const float* lrow = a.lam[src] + io + (long long)ci * M;
   float* erow = a.ell + io + (long long)(vi ? i : 0) * M;
-  Lse acc;
+  SegLse<SEG, JPT, ORD> acc;
   constexpr bool kH = has_yhat<Mdl>();
   const bool want_h = kH && a.yp != nullptr && !fallback;
-  float hv = 0.f;  // sum over the lane's draws of qbar h(xla, zla)
+  SegSum<SEG, JPT, ORD> hv;  // of the draws' qbar h(xla, zla)
   if constexpr (Mdl::kStreamZ) {
     // wide z: every lane of the wave takes part in the matrix-core residual
     float ca[WaveProj<Mdl>::NA];
@@ -506,7 +559,7 @@ __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool 
       if (on) {
         const float e = la_ell(lj, g);
         erow[j] = e;
-        acc.add(e);
+        acc.add(r, e);
       }
     }
   } else {
@@ -522,20 +575,20 @@ __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool 
       if (want_h) {
         float h[1];
         g = la_logpy<Mdl, kH>(a, key, t, i, j, x, z, y, h);
-        hv += fast_exp(lj) * h[0];
+        hv.add(r, fast_exp(lj), h[0]);
       } else {
         g = la_logpy<Mdl>(a, key, t, i, j, x, z, y);
       }
       const float e = la_ell(lj, g);
       erow[j] = e;
-      acc.add(e);
+      acc.add(r, e);
     }
   }
   }
-  const float lw = seg_lse<SEG>(acc, sh);
+  const float lw = acc.get(sh);
   if (vi && ls == 0) a.logw[oo + i] = lw;
   if (want_h) {
-    const float hs = seg_sum<SEG>(hv, sh);
+    const float hs = hv.get(sh);
     if (vi && ls == 0) a.yp[oo + i] = hs;
   }
 }
@@ -553,7 +606,7 @@ __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool 
 // candidates.  Otherwise the segment walks the candidates in order, forming
 // each one's conditioned cumulative sum together and spreading its
 // companions over the lanes.
-template <class Mdl, int SEG, int JPT>
+template <class Mdl, int SEG, int JPT, int ORD = 0>
 __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti) {
   constexpr int DX = Mdl::DX, DZ = Mdl::DZ, DY = Mdl::DY;
   constexpr int NSEG = kBlock / SEG, CAP = SEG * JPT;
@@ -628,7 +681,7 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
   // mean of h over their companions
   const bool want_h = kH && a.yp != nullptr;
   const float invK = 1.0f / (float)K;
-  float hv = 0.f;
+  SegSum<SEG, JPT, ORD> hv;
   float ev[JPT];
 #pragma unroll
   for (int r = 0; r < JPT; ++r) ev[r] = -INFINITY;
@@ -688,7 +741,7 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
         }
         const float g = (acck.m == -INFINITY) ? -INFINITY : acck.m + fast_log(acck.s) - logK;
         ev[r] = la_ell(lamv[r], g);
-        if (want_h) hv += fast_exp(lamv[r]) * (hk * invK);
+        if (want_h) hv.add(r, fast_exp(lamv[r]), hk * invK);
       }
     }
   } else {
@@ -790,30 +843,30 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
         }
         const float g = (acck.m == -INFINITY) ? -INFINITY : acck.m + fast_log(acck.s) - logK;
         ev[r] = la_ell(lamv[r], g);
-        if (want_h) hv += fast_exp(lamv[r]) * (hk * invK);
+        if (want_h) hv.add(r, fast_exp(lamv[r]), hk * invK);
       }
     }
   }
-  Lse acc;
+  SegLse<SEG, JPT, ORD> acc;
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
     const int j = ls + r * SEG;
     if (vi && j < M) {
       erow[j] = ev[r];
-      acc.add(ev[r]);
+      acc.add(r, ev[r]);
     }
   }
-  const float lw = seg_lse<SEG>(acc, sh);
+  const float lw = acc.get(sh);
   if (vi && ls == 0) a.logw[oo + i] = lw;
   if (want_h) {
-    const float hs = seg_sum<SEG>(hv, sh);
+    const float hs = hv.get(sh);
     if (vi && ls == 0) a.yp[oo + i] = hs;
   }
 }
 
-template <class Mdl, int SEG, int JPT>
+template <class Mdl, int SEG, int JPT, int ORD = 0>
 __global__ __launch_bounds__(kBlock) void k_la_weights_nested(StepArgs a) {
-  la_weights_nested_tile<Mdl, SEG, JPT>(a, blockIdx.x);
+  la_weights_nested_tile<Mdl, SEG, JPT, ORD>(a, blockIdx.x);
 }
 
 static __device__ bool learned_rejected(const StepArgs& a, int f, int N, float* fred4, double* red4);
@@ -821,9 +874,9 @@ static __device__ bool learned_rejected(const StepArgs& a, int f, int N, float* 
 // One workgroup per tile.  (A kernel that loops over tiles compiles to
 // markedly slower code for the single-tile case, so the learned step's
 // fallback has kernels of its own.)
-template <class Mdl, int SEG, int JPT>
+template <class Mdl, int SEG, int JPT, int ORD = 0>
 static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<Mdl>()))) void k_la_weights(StepArgs a) {
-  la_weights_tile<Mdl, SEG, JPT>(a, blockIdx.x, false);
+  la_weights_tile<Mdl, SEG, JPT, ORD>(a, blockIdx.x, false);
 }
 
 // Learned step's fallback, a smaller grid looping over the tiles: each
@@ -874,7 +927,7 @@ static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(m
 // Fig. 2 step 1 (eq:approx2 with unit inner weights): ell = log p(y_t | xt, zt),
 // log w_i = logsumexp_j ell - log M, and the per-particle partial
 // sum_j qbar_ij zt_ij (qbar = softmax_j ell, step 3) for the estimate.
-template <class Mdl, int SEG, int JPT>
+template <class Mdl, int SEG, int JPT, int ORD = 0>
 static __global__ __launch_bounds__(kBlock) void k_dpf_weights(StepArgs a) {
   __shared__ SegScratch sh;
   __shared__ float vred[kBlock / kWave][Mdl::DZ];
@@ -900,7 +953,7 @@ static __global__ __launch_bounds__(kBlock) void k_dpf_weights(StepArgs a) {
   const float* zrow = a.z[src] + (io + (long long)(vi ? i : 0) * M) * Mdl::DZ;
   float* erow = a.ell + io + (long long)(vi ? i : 0) * M;
   float ev[JPT];
-  Lse acc;
+  SegLse<SEG, JPT, ORD> acc;
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
     const int j = ls + r * SEG;
@@ -911,10 +964,10 @@ static __global__ __launch_bounds__(kBlock) void k_dpf_weights(StepArgs a) {
       for (int d = 0; d < Mdl::DZ; ++d) z[d] = zrow[d * M + j];
       ev[r] = Mdl::logpy_post(as_prm(a.prm), r0, z);
       erow[j] = ev[r];
-      acc.add(ev[r]);
+      acc.add(r, ev[r]);
     }
   }
-  const float lse = seg_lse<SEG>(acc, sh);
+  const float lse = acc.get(sh);
   // qbar-weighted cloud mean of the proposals (uniform if degenerate)
   const bool deg = !(lse > -INFINITY);
   float part[Mdl::DZ];
@@ -1840,7 +1893,7 @@ static __global__ __launch_bounds__(kBlock) void k_resolve(StepArgs a, const int
 // x_{t+1} from the a_k-th component (DPF_X at (t, k, 0)), kappa = ell_pj +
 // log p(x_{t+1} | x_p, z_pj), systematic inner resampling, DPF_Z normals;
 // no measurement update (that happens at the next step).
-template <class Mdl, int SEG, int JPT, bool PLAIN>
+template <class Mdl, int SEG, int JPT, bool PLAIN, int ORD = 0>
 __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   constexpr int DX = Mdl::DX, DZ = Mdl::DZ, DY = Mdl::DY;
   constexpr int NSEG = kBlock / SEG;
@@ -2205,7 +2258,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   constexpr bool kH = !PLAIN && has_yhat<Mdl>();
   const bool want_h = kH && fuse && a.yp_next != nullptr;
   float hn[kH ? JPT : 1];
-  Lse acc;
+  SegLse<SEG, JPT, ORD> acc;
   // wide z: the new z of every lane of the wave goes through the matrix-core
   // residual together (lanes without a particle carry zeros)
   float ca[kStream ? Mdl::DZ / 2 : 1];
@@ -2246,7 +2299,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         if (on) {
           lv = l0;
           gv = g0;
-          acc.add(lv);
+          acc.add(r, lv);
         }
       }
     } else if (vk && jj < M) {
@@ -2269,7 +2322,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         for (int d = 0; d < DZ; ++d) zkeep[kKeepZ ? r : 0][d] = zn[d];
       }
       if (!PLAIN) {
-        acc.add(lv);
+        acc.add(r, lv);
         // the next step's look-ahead likelihood of this new inner particle
         // (ALU work that overlaps the gathers of the others)
         if (want_h) {
@@ -2299,7 +2352,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   }
   uint32_t fl = (deg1 || deg2) ? (uint32_t)F_DEGENERATE_INNER : 0u;
   if (!PLAIN) {
-    const float lse = seg_lse<SEG>(acc, sh);
+    const float lse = acc.get(sh);
     const bool deg3 = !(lse > -INFINITY);
     if (deg3) fl |= F_DEGENERATE_INNER;
     float* ldst = a.lam[dst] + io + (long long)k * M;
@@ -2357,22 +2410,22 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     // weights kernel's lane layout and summation order
     if (fuse) {
       float* en = a.ell_next + io + (long long)(vk ? k : 0) * M;
-      Lse acc2;
-      float hv = 0.f;
+      SegLse<SEG, JPT, ORD> acc2;
+      SegSum<SEG, JPT, ORD> hv;
 #pragma unroll
       for (int r = 0; r < JPT; ++r) {
         const int jj = ls + r * SEG;
         if (vk && jj < M) {
           const float e = la_ell(lamv[r], gn[r]);
           en[jj] = e;
-          acc2.add(e);
-          if (want_h) hv += fast_exp(lamv[r]) * hn[kH ? r : 0];
+          acc2.add(r, e);
+          if (want_h) hv.add(r, fast_exp(lamv[r]), hn[kH ? r : 0]);
         }
       }
-      const float lw = seg_lse<SEG>(acc2, sh);
+      const float lw = acc2.get(sh);
       if (vk && ls == 0) a.logw_next[oo + k] = lw;
       if (want_h) {
-        const float hs = seg_sum<SEG>(hv, sh);
+        const float hs = hv.get(sh);
         if (vk && ls == 0) a.yp_next[oo + k] = hs;
       }
     }
@@ -2383,7 +2436,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
 // With the wide inner state the children of one parent (neighbouring tiles
 // after the ordered resampling) run on one XCD and read the parent's cloud
 // through one L2.
-template <class Mdl, int SEG, int JPT, bool PLAIN>
+template <class Mdl, int SEG, int JPT, bool PLAIN, int ORD = 0>
 static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<Mdl>()))) void k_newcloud(StepArgs a) {
   if (!PLAIN && (int)blockIdx.x < a.n_head) {
     est_head<Mdl::DX, Mdl::DZ, has_yhat<Mdl>()>(a, blockIdx.x);
@@ -2391,7 +2444,7 @@ static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(m
   }
   const int b = PLAIN ? (int)blockIdx.x : (int)blockIdx.x - a.n_head;
   const int ti = Mdl::kStreamZ ? xcd_contiguous_tile(b, (int)gridDim.x - (PLAIN ? 0 : a.n_head)) : b;
-  newcloud_tile<Mdl, SEG, JPT, PLAIN>(a, ti);
+  newcloud_tile<Mdl, SEG, JPT, PLAIN, ORD>(a, ti);
 }
 
 // Learned step: the new clouds of the filters that fell back only (smaller

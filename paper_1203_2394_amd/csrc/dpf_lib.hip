@@ -212,6 +212,8 @@ struct dpf_handle {
   std::vector<TileClass> classes;
   std::vector<int> fcls;  // tile class of each filter
   bool one_group = false;  // every filter has one resampling group
+  std::vector<char> fdef;  // whether the filter's class is the default (a narrow class may stand in)
+  bool wide = false;       // no narrow classes from here on (learned passes, moments)
   // multi-step graph cache
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -460,6 +462,7 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
   h->one_group = rg == F;
   h->fcls.resize(F);
   for (int f = 0; f < F; ++f) h->fcls[f] = class_of(h->M[f]);
+  h->fdef.assign(F, 1);
   hipError_t e = hipSuccess;
 #define UP(off, vec)                                                                                   \
   if (e == hipSuccess && !(vec).empty())                                                               \
@@ -493,20 +496,51 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
   return DPF_OK;
 }
 
-// Tiles of every filter in the class h->fcls[f], grouped by class, uploaded
-// to the workspace (room for one tile per outer particle was reserved).
+// The narrow class (index from kNumClasses on) for a default class and inner
+// size; -1: none.
+static int narrow_class(int cls, int M) {
+  if (kClasses[cls].jpt != 1) return -1;
+  for (int k = 0; k < kNumNarrow; ++k)
+    if (kNarrow[k].ord == kClasses[cls].seg && M <= kNarrow[k].seg * kNarrow[k].jpt) return kNumClasses + k;
+  return -1;
+}
+
+// Whether narrow classes stand in for the handle's default ones.  A narrow
+// wave does the work of several wide ones one after the other, so it pays once
+// the narrow waves alone fill the SIMDs (1024) with some to spare: measured
+// over runs of the small models (N = 200 to 2000, M = 10 to 100, look-ahead
+// and plain) narrow / wide speed 0.82 to 1.09 at 1000 waves, 0.92 to 1.09 at
+// 1500, 1.04 to 1.36 at 1600 to 1700, 1.05 to 1.4 at 2000, 1.16 to 1.62 at
+// 3000 and 1.5 to 2.0 beyond 6000.
+constexpr long long kNarrowWaves = 1600;
+
+static bool use_narrow(const dpf_handle* h) {
+  if (h->wide || !h->eng->narrow) return false;
+  long long waves = 0;
+  for (int f = 0; f < h->F; ++f) {
+    const int c = h->fdef[f] ? narrow_class(h->fcls[f], h->M[f]) : -1;
+    if (c >= 0) waves += (h->N[f] + kWave / kNarrow[c - kNumClasses].seg - 1) / (kWave / kNarrow[c - kNumClasses].seg);
+  }
+  return waves >= kNarrowWaves;
+}
+
+// Tiles of every filter in its launch class, grouped by class, uploaded to the
+// workspace (room for one tile per outer particle was reserved).
 static dpf_status build_tiles(dpf_handle* h) {
   const int F = h->F;
-  std::vector<std::vector<int4>> by(kNumClasses);
+  const bool narrow = use_narrow(h);
+  std::vector<std::vector<int4>> by(kNumClasses + kNumNarrow);
   for (int f = 0; f < F; ++f) {
-    const int segs = kBlock / kClasses[h->fcls[f]].seg;
+    const int nc = narrow && h->fdef[f] ? narrow_class(h->fcls[f], h->M[f]) : -1;
+    const int c = nc >= 0 ? nc : h->fcls[f];
+    const int segs = kBlock / (c < kNumClasses ? kClasses[c].seg : kNarrow[c - kNumClasses].seg);
     int nt = 0;
     for (int i0 = 0; i0 < h->N[f]; i0 += segs)
-      by[h->fcls[f]].push_back(make_int4(f, i0, nt++, h->finfo_h[f].rg_base));
+      by[c].push_back(make_int4(f, i0, nt++, h->finfo_h[f].rg_base));
   }
   h->tiles_h.clear();
   h->classes.clear();
-  for (int k = 0; k < kNumClasses; ++k) {
+  for (int k = 0; k < kNumClasses + kNumNarrow; ++k) {
     if (by[k].empty()) continue;
     TileClass tc;
     tc.cls = k;
@@ -522,6 +556,15 @@ static dpf_status build_tiles(dpf_handle* h) {
   return DPF_OK;
 }
 
+// Before a learned pass or the cloud moments, which have no narrow class.
+static dpf_status use_wide(dpf_handle* h) {
+  if (h->wide) return DPF_OK;
+  h->wide = true;
+  for (const TileClass& tc : h->classes)
+    if (tc.cls >= kNumClasses) return build_tiles(h);
+  return DPF_OK;
+}
+
 extern "C" int32_t dpf_tile_classes(int32_t* seg, int32_t* jpt, int32_t n) {
   for (int k = 0; k < kNumClasses && k < n; ++k) {
     if (seg) seg[k] = kClasses[k].seg;
@@ -533,7 +576,9 @@ extern "C" int32_t dpf_tile_classes(int32_t* seg, int32_t* jpt, int32_t n) {
 extern "C" dpf_status dpf_set_tiling(dpf_handle* h, const int32_t* h_cls) {
   if (!h || !h_cls) return fail(DPF_EINVAL, "handle and class array are required");
   std::vector<int> c(h->F);
+  std::vector<char> def(h->F);
   for (int f = 0; f < h->F; ++f) {
+    def[f] = h_cls[f] < 0;
     const int k = h_cls[f] < 0 ? class_of(h->M[f]) : h_cls[f];
     if (k >= kNumClasses) return fail(DPF_EINVAL, "class %d of filter %d is not built", k, f);
     if (kClasses[k].seg * kClasses[k].jpt < h->M[f])
@@ -542,6 +587,7 @@ extern "C" dpf_status dpf_set_tiling(dpf_handle* h, const int32_t* h_cls) {
     c[f] = k;
   }
   h->fcls = c;
+  h->fdef = def;
   return build_tiles(h);
 }
 
@@ -667,6 +713,8 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
 // step's features; with feat, also the raw feature rows for y.
 static dpf_status queue_moments(dpf_handle* h, const float* y, float* feat) {
   if (!h->eng->moments) return fail(DPF_EUNSUPPORTED, "cloud moments are not built for this model");
+  const dpf_status w = use_wide(h);
+  if (w != DPF_OK) return w;
   StepArgs a = make_args(h);
   a.mom = at<float>(h, h->L.mom);
   g_mom_args = MomArgs{y, feat};
@@ -682,7 +730,8 @@ static dpf_status queue_learned_step(dpf_handle* h, const float* Y, long long y_
                                      const unsigned char* active, const int* run_Tf, int run_T, float* trace_x,
                                      float* trace_z, const float* mdn_given) {
   h->rb_ready = false;
-  dpf_status s = DPF_OK;
+  dpf_status s = use_wide(h);
+  if (s != DPF_OK) return s;
   if (!h->mom_valid && !mdn_given) s = queue_moments(h, nullptr, nullptr);
   if (s != DPF_OK) return s;
   h->ell_sel = 0;

@@ -1,7 +1,7 @@
 // Segment primitives for 256-thread workgroups on wave64 hardware.
 //
 // A workgroup is split into 256/SEG segments of SEG lanes (SEG in
-// {16, 32, 64, 128, 256}); one segment serves one outer particle's inner cloud
+// {8, 16, 32, 64, 128, 256}); one segment serves one outer particle's inner cloud
 // of M <= SEG*JPT inner particles, lane l handling inner indices
 // l, l+SEG, ... (coalesced in the [N][dz][M] layout).  Segments of up to 64
 // lanes live inside one wavefront and reduce / scan with cross-lane
@@ -136,6 +136,19 @@ __device__ __forceinline__ void tr_step(float* v, int lane) {
 template <int SEG, int NV>
 __device__ __forceinline__ float seg_sum_vec_t(const float* vin, float (*red)[NV], int& slot) {
   static_assert(NV == 1 || NV == 2 || NV == 4 || NV == 8 || NV == 16, "NV must be a power of two <= 16");
+  if constexpr (SEG == 8) {
+    // half rows: value q's total in lane q of the segment
+    static_assert(NV <= 8, "one value per lane");
+    const int ls = threadIdx.x % SEG;
+    float r = 0.f;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const float t = half_row_reduce<OpAdd>(vin[q]);
+      if (ls == q) r = t;
+    }
+    slot = ls < NV ? ls : -1;
+    return r;
+  }
   constexpr int P = log2_nv<NV>();
   constexpr int SH = 4 - P;  // owner lanes are multiples of 2^SH within the row
   float v[NV];
@@ -175,7 +188,7 @@ __device__ __forceinline__ float seg_sum_vec_t(const float* vin, float (*red)[NV
 // `want` (0 <= want < NV; other lanes pass want < 0 and get their own value).
 template <int SEG, int NV>
 __device__ __forceinline__ float seg_vec_fetch(float tot, int want) {
-  constexpr int SH = 4 - log2_nv<NV>();
+  constexpr int SH = SEG == 8 ? 0 : 4 - log2_nv<NV>();
   const int lane = threadIdx.x & (kWave - 1);
   int src = lane;
   if (want >= 0) {
@@ -189,16 +202,44 @@ __device__ __forceinline__ float seg_vec_fetch(float tot, int want) {
   return __shfl(tot, src);
 }
 
+// Sum over a narrow segment (SEG = 8 or 16 lanes, lane l holding items
+// l, l + SEG, ... in x[0 .. JPT)) in the order in which a segment of ORD lanes
+// with one item each sums them (seg_reduce): rows of 16 items as a DPP row
+// reduction, then the rows, and beyond 64 items the waves, in pairs.  Items
+// beyond the last are 0 and may be left out (x + 0 = x).
+template <int SEG, int JPT, int ORD>
+__device__ __forceinline__ float seg_sum_ord(const float* x) {
+  static_assert((SEG == 8 || SEG == 16) && SEG * JPT <= ORD, "narrow segments");
+  constexpr int NR = ORD / 16;
+  float R[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    if constexpr (SEG == 16) {
+      R[q] = q < JPT ? row_reduce<OpAdd>(x[q < JPT ? q : 0]) : 0.f;
+    } else {
+      R[q] = 2 * q < JPT ? half_row_reduce<OpAdd>(x[2 * q < JPT ? 2 * q : 0]) : 0.f;
+      if (2 * q + 1 < JPT) R[q] += half_row_reduce<OpAdd>(x[2 * q + 1 < JPT ? 2 * q + 1 : 0]);
+    }
+  }
+#pragma unroll
+  for (int h = 1; h < NR; h *= 2) {
+#pragma unroll
+    for (int q = 0; q + h < NR; q += 2 * h) R[q] += R[q + h];
+  }
+  return R[0];
+}
+
 // Inclusive FP64 scan within the segment; `total` receives the segment sum.
 template <int SEG>
 __device__ __forceinline__ double seg_scan_incl(double v, SegScratch& sh, double& total) {
   constexpr int W = wave_width<SEG>();
   v = seg_scan_wave<W>(v);
   if constexpr (SEG <= kWave) {
-    if constexpr (W == 16) {
-      const int row = (threadIdx.x & 63) >> 4;
-      const double t0 = readlane_d(v, 15), t1 = readlane_d(v, 31), t2 = readlane_d(v, 47), t3 = readlane_d(v, 63);
-      total = row == 0 ? t0 : (row == 1 ? t1 : (row == 2 ? t2 : t3));
+    if constexpr (W == 8) {
+      const double t0 = dpp_d<kDppRowBcast + 7>(v, v), t1 = dpp_d<kDppRowBcast + 15>(v, v);
+      total = (threadIdx.x & 8) ? t1 : t0;
+    } else if constexpr (W == 16) {
+      total = dpp_d<kDppRowBcast + 15>(v, v);
     } else if constexpr (W == 32) {
       total = (threadIdx.x & 63) < 32 ? readlane_d(v, 31) : readlane_d(v, 63);
     } else {

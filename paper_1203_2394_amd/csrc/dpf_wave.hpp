@@ -9,8 +9,8 @@
 //               and max are commutative, so all lanes hold identical bits);
 //   row scan:   row_shr 1, 2, 4, 8 with zero fill (Hillis-Steele);
 //   rows:       row totals read with readlane and combined in a fixed order.
-// FP64 values move as two 32-bit halves.  Segments of 16 lanes are rows, of
-// 32 lanes two rows; 64 lanes are the whole wave.  Every lane of the wave
+// FP64 values move as two 32-bit halves.  Segments of 8 lanes are half rows,
+// of 16 lanes rows, of 32 lanes two rows; 64 lanes are the whole wave.  Every lane of the wave
 // must be active.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -27,6 +27,7 @@ constexpr int kDppRowShr1 = 0x111;
 constexpr int kDppRowShr2 = 0x112;
 constexpr int kDppRowShr4 = 0x114;
 constexpr int kDppRowShr8 = 0x118;
+constexpr int kDppRowBcast = 0x150;  // + n: lane n of each row to the whole row
 
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v, int fill) {
@@ -80,11 +81,26 @@ __device__ __forceinline__ double row_reduce(double v) {
   return v;
 }
 
-// Reduction over segments of W lanes (W = 16, 32 or 64); every lane of a
+// The first three steps: every lane of a half row gets its total.
+template <class Op>
+__device__ __forceinline__ float half_row_reduce(float v) {
+  v = Op::apply(v, dpp_f<kDppQuadXor1>(v, v));
+  v = Op::apply(v, dpp_f<kDppQuadXor2>(v, v));
+  return Op::apply(v, dpp_f<kDppRowHalfMirror>(v, v));
+}
+template <class Op>
+__device__ __forceinline__ double half_row_reduce(double v) {
+  v = Op::apply(v, dpp_d<kDppQuadXor1>(v, v));
+  v = Op::apply(v, dpp_d<kDppQuadXor2>(v, v));
+  return Op::apply(v, dpp_d<kDppRowHalfMirror>(v, v));
+}
+
+// Reduction over segments of W lanes (W = 8, 16, 32 or 64); every lane of a
 // segment gets the segment result.
 template <class Op, int W, class T>
 __device__ __forceinline__ T seg_reduce_wave(T v) {
-  static_assert(W == 16 || W == 32 || W == 64, "segment width");
+  static_assert(W == 8 || W == 16 || W == 32 || W == 64, "segment width");
+  if constexpr (W == 8) return half_row_reduce<Op>(v);
   v = row_reduce<Op>(v);
   if constexpr (W == 16) {
     return v;
@@ -99,13 +115,25 @@ __device__ __forceinline__ T seg_reduce_wave(T v) {
   }
 }
 
-// Inclusive sum scan over segments of W lanes (W = 16, 32 or 64).  Lanes of
+// Inclusive sum scan over segments of W lanes (W = 8 (FP64), 16, 32 or 64).  Lanes of
 // a row combine in Hillis-Steele order, so neighbouring prefixes may differ
 // in association (at the rounding level) from a serial sum.
 template <int W, class T>
 __device__ __forceinline__ T seg_scan_wave(T v) {
-  static_assert(W == 16 || W == 32 || W == 64, "segment width");
+  static_assert(W == 8 || W == 16 || W == 32 || W == 64, "segment width");
   const T z = T(0);
+  if constexpr (W == 8) {
+    // (a row's shift carries the lower half's last lanes into the upper half:
+    // masked)
+    const int l8 = threadIdx.x & 7;
+    const double d1 = dpp_d<kDppRowShr1>(v, z);
+    v += l8 >= 1 ? d1 : z;
+    const double d2 = dpp_d<kDppRowShr2>(v, z);
+    v += l8 >= 2 ? d2 : z;
+    const double d4 = dpp_d<kDppRowShr4>(v, z);
+    v += l8 >= 4 ? d4 : z;
+    return v;
+  }
   if constexpr (sizeof(T) == 8) {
     v += dpp_d<kDppRowShr1>(v, z);
     v += dpp_d<kDppRowShr2>(v, z);
