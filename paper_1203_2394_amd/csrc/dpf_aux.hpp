@@ -205,7 +205,7 @@ static __global__ __launch_bounds__(kBlock) void k_prim_res_select(const double*
 
 // One segment per (S index); the cdf build and search are those of k_newcloud.
 template <int SEG, int JPT>
-static __global__ __launch_bounds__(kBlock) void k_seg_systematic_prim(const double* w, int S, int n,
+static __global__ __launch_bounds__(kBlock) void k_seg_systematic_prim(const double* wt, int S, int n,
                                                                  int n_out, const double* u,
                                                                  int* out) {
   constexpr int NSEG = kBlock / SEG;
@@ -215,23 +215,28 @@ static __global__ __launch_bounds__(kBlock) void k_seg_systematic_prim(const dou
   const int ls = threadIdx.x % SEG;
   const int g = blockIdx.x * NSEG + s;
   const bool vg = g < S;
-  double carry = 0.0;
+  double w[JPT], P[JPT];
+  int res[JPT];
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
-    const double wj = (vg && j < n) ? w[(long long)g * n + j] : 0.0;
-    double tot;
-    const double c = seg_scan_incl<SEG>(wj, sh, tot);
-    cdf[s][r * SEG + ls] = carry + c;
-    carry += tot;
+    const int j = ls * JPT + r;
+    w[r] = (vg && j < n) ? wt[(long long)g * n + j] : 0.0;
   }
+  seg_cdf<SEG, JPT>(w, cdf[s], sh);
   __syncthreads();
   if (!vg) return;
   const double uu = u[g];
   const double total = cdf[s][n - 1];
+#pragma unroll
   for (int r = 0; r < JPT; ++r) {
     const int k = ls + r * SEG;
-    if (k < n_out) out[(long long)g * n_out + k] = cdf_search(cdf[s], n, sys_point(k, uu, total, n_out));
+    P[r] = k < n_out ? sys_point(k, uu, total, n_out) : 0.0;
+  }
+  cdf_find<SEG * JPT, JPT>(cdf[s], n, total, P, res);
+#pragma unroll
+  for (int r = 0; r < JPT; ++r) {
+    const int k = ls + r * SEG;
+    if (k < n_out) out[(long long)g * n_out + k] = res[r];
   }
 }
 

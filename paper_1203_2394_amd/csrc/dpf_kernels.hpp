@@ -244,19 +244,40 @@ __device__ __forceinline__ const float* y_row(const StepArgs& a, int f, int t) {
   return a.Y + (long long)(t - 1) * a.y_tstride + (long long)f * Mdl::DY;
 }
 
-// Online log-sum-exp accumulator (non-finite values are skipped).
+// Online log-sum-exp accumulator (non-finite values are skipped): a new
+// maximum rescales the sum, s e^(m - v) + 1, another value adds e^(v - m) --
+// the same exponential either way, so no branch.
 struct Lse {
   float m = -INFINITY, s = 0.f;
-  __device__ void add(float v) {
-    if (!finitef(v)) return;
-    if (v > m) {
-      s = s * fast_exp(m - v) + 1.0f;
-      m = v;
-    } else {
-      s += fast_exp(v - m);
-    }
+  __device__ __forceinline__ void add(float v) {
+    const bool ok = finitef(v), up = v > m;
+    const float e = fast_exp(-fabsf(v - m));
+    const float t = up ? s * e + 1.0f : s + e;
+    s = ok ? t : s;
+    m = ok && up ? v : m;
   }
 };
+
+// p[i] with a 32-bit byte offset (a wave-uniform p stays in scalar registers).
+__device__ __forceinline__ float at32(const float* p, int i) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + (uint32_t)i * 4u);
+}
+// A lane's JPT consecutive items from row[j0] on, in loads of up to 16 bytes
+// (item by item, each load of a wave would touch every line of the segment's
+// row again).  j0 is clamped into the row of n items, so up to JPT - 1 floats
+// after the row are read too -- the next row, or the array that follows in the
+// workspace; the caller masks items by ls JPT + r < n.
+template <int JPT>
+struct Items {
+  float v[JPT];
+};
+template <int JPT>
+__device__ __forceinline__ Items<JPT> load_items(const float* row, int j0, int n) {
+  return *reinterpret_cast<const Items<JPT>*>(row + min(j0, n - 1));
+}
+__device__ __forceinline__ void put32(float* p, int i, float v) {
+  *reinterpret_cast<float*>(reinterpret_cast<char*>(p) + (uint32_t)i * 4u) = v;
+}
 
 template <int SEG>
 __device__ __forceinline__ float seg_lse(Lse l, SegScratch& sh) {
@@ -1385,7 +1406,7 @@ __device__ __forceinline__ OuterDraws outer_draws(Key key, int t, int k, uint32_
 
 // One systematic draw (offset u) over weights exp(e_j - max), j < M (non-
 // finite: 0; none finite: uniform), by one wave: each lane sums a chunk of
-// ceil(M / 64) <= CMAX consecutive weights, the chunk totals are scanned
+// CMAX (chunks of more than 16: ceil(M / 64)) consecutive weights, the chunk totals are scanned
 // across lanes, and the lane holding the point walks its chunk.  Chunks of
 // up to 16 stay in registers; longer ones are read again.
 template <int CMAX>
@@ -1393,15 +1414,16 @@ __device__ int select_w0(const float* e, int M, double u, bool& deg_out) {
   constexpr bool kReg = CMAX <= 16;
   constexpr int R = kReg ? CMAX : 1;
   const int l = threadIdx.x & (kWave - 1);
-  const int C = (M + kWave - 1) / kWave;
+  const int C = kReg ? CMAX : (M + kWave - 1) / kWave;
   const int j0 = l * C;
   const int nv = max(0, min(C, M - j0));  // entries of this lane's chunk
   float ev[R];
   float mloc = -INFINITY;
   if constexpr (kReg) {
+    const Items<R> it = load_items<R>(e, j0, M);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      ev[q] = q < nv ? e[j0 + q] : -INFINITY;
+      ev[q] = q < nv ? it.v[q] : -INFINITY;
       if (finitef(ev[q])) mloc = fmaxf(mloc, ev[q]);
     }
   } else {
@@ -1906,8 +1928,6 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   __shared__ SegScratch sh;
   __shared__ double cdf[NSEG][SEG * JPT];
   __shared__ float roll_sh[kRoll ? 2 * JPT : 1][kRoll ? kBlock : 1];
-  __shared__ float xs_sh[NSEG][DX];
-  __shared__ int csel[NSEG];
   __shared__ float vred[kBlock / kWave][2 * DZ];
   __shared__ int anc_sh[NSEG];
   __shared__ ResScratch rsh;
@@ -1948,7 +1968,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   float yn[DY];
   if (!PLAIN && a.ell_next != nullptr) load_y<Mdl>(a, f, min(t, a.run_T - 1) + 1, yn);
   const int N = fv.N, M = fv.M;
-  const int s = threadIdx.x / SEG;
+  const int s = SEG >= kWave ? __builtin_amdgcn_readfirstlane(threadIdx.x / SEG) : threadIdx.x / SEG;
   const int ls = threadIdx.x % SEG;
   const int k = tile.y + s;
   const bool vk = k < N;
@@ -2026,15 +2046,15 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       const float* zpw = a.z[src] + (io + (long long)pcw * M) * DZ;
       if constexpr (kPre) {
         const float* kr = PLAIN ? a.ell + io + (long long)pw * M : a.lam[src] + io + (long long)pcw * M;
+        const Items<JPT> ki = load_items<JPT>(kr, ls * JPT, M);
 #pragma unroll
-        for (int r = 0; r < JPT; ++r) {
-          const int j = ls + r * SEG;
-          if (j < M) {
-            kpre[r] = kr[j];
-            if constexpr (kPreZ) {
+        for (int r = 0; r < JPT; ++r) kpre[r] = ki.v[r];
+        if constexpr (kPreZ) {
 #pragma unroll
-              for (int d = 0; d < DZ; ++d) zpre[kPreZ ? r : 0][kPreZ ? d : 0] = zpw[d * M + j];
-            }
+          for (int d = 0; d < DZ; ++d) {
+            const Items<JPT> zi = load_items<JPT>(zpw + d * M, ls * JPT, M);
+#pragma unroll
+            for (int r = 0; r < JPT; ++r) zpre[kPreZ ? r : 0][kPreZ ? d : 0] = zi.v[r];
           }
         }
       }
@@ -2043,15 +2063,15 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       // every lane of the wave computes the new x (same counters)
       float zc[DZ], nu[DX];
       if constexpr (kPreZ) {
-        // z of the candidate: held by lane cw % 64 in its slot cw / 64
-        const int rr = cw / SEG;
+        // z of the candidate: held by lane cw / JPT in its slot cw % JPT
+        const int rr = cw % JPT;
 #pragma unroll
         for (int d = 0; d < DZ; ++d) {
           float v = zpre[0][kPreZ ? d : 0];
 #pragma unroll
           for (int r = 1; r < JPT; ++r)
             if (rr == r) v = zpre[kPreZ ? r : 0][kPreZ ? d : 0];
-          zc[d] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), cw % SEG));
+          zc[d] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), cw / JPT));
         }
       } else {
 #pragma unroll
@@ -2070,9 +2090,9 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       }
     }
     if constexpr (SEG == kWave) {
-      p = pw;
+      p = __builtin_amdgcn_readfirstlane(pw);
       c = cw;
-      pc = pcw;
+      pc = __builtin_amdgcn_readfirstlane(pcw);
       deg1 = d1;
 #pragma unroll
       for (int d = 0; d < DX; ++d) {
@@ -2095,7 +2115,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         }
       }
       __syncthreads();
-      p = pc_sh[s][0];
+      p = __builtin_amdgcn_readfirstlane(pc_sh[s][0]);
       c = pc_sh[s][1];
       deg1 = d1_sh[s] != 0;
 #pragma unroll
@@ -2142,56 +2162,75 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   const float* ep = a.ell + io + (long long)p * M;
 
   // ---- 1. selection over the parent's ell (candidate / ancestor) --------
+  // (lane ls: JPT consecutive items; one scan over the lanes, then each lane
+  // counts its cumulative weights up to the point)
   float ev[JPT];
   float mloc = -INFINITY;
+  const Items<JPT> ei = load_items<JPT>(ep, ls * JPT, M);
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
-    ev[r] = (vk && j < M) ? ep[j] : -INFINITY;
+    const int j = ls * JPT + r;
+    ev[r] = (vk && j < M) ? ei.v[r] : -INFINITY;
     if (finitef(ev[r])) mloc = fmaxf(mloc, ev[r]);
   }
   const float m1 = seg_max<SEG>(mloc, sh);
   deg1 = !(m1 > -INFINITY);
-  double carry = 0.0;
+  double acc1 = 0.0;
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
-    double w = 0.0;
-    if (j < M) w = deg1 ? 1.0 : (finitef(ev[r]) ? (double)fast_exp(ev[r] - m1) : 0.0);
-    double tot;
-    const double c = seg_scan_incl<SEG>(w, sh, tot);
-    cdf[s][r * SEG + ls] = carry + c;
-    carry += tot;
+    const int j = ls * JPT + r;
+    ev[r] = j < M ? (deg1 ? 1.0f : (finitef(ev[r]) ? fast_exp(ev[r] - m1) : 0.0f)) : 0.0f;
+    acc1 += (double)ev[r];
   }
-  seg_lds_sync<SEG>();
-  if (ls == 0) {
-    csel[s] = vk ? cdf_search(cdf[s], M, sys_point(0, ud.cand, cdf[s][M - 1], 1)) : 0;
-    if (vk) a.sel[oo + k] = csel[s];
+  double ex1, in1;
+  seg_scan_wave_both<SEG>(acc1, ex1, in1);
+  const double tot1 = seg_last<SEG>(in1);
+  const double P1 = ud.cand * tot1;
+  // first index whose cumulative weight exceeds the point (a point at the
+  // total: the first that reaches it)
+  float below = 0.f, short1 = 0.f;
+  {
+    double cum = ex1;
+#pragma unroll
+    for (int r = 0; r < JPT; ++r) {
+      cum += (double)ev[r];
+      const double C = r == JPT - 1 ? in1 : fmin(cum, in1);
+      const bool in = ls * JPT + r < M;
+      below += in && C <= P1 ? 1.f : 0.f;
+      short1 += in && C < tot1 ? 1.f : 0.f;
+    }
   }
-  seg_lds_sync<SEG>();
-  c = csel[s];
+  c = (int)seg_reduce_wave<OpAdd, SEG>(below);
+  if (__ballot(c >= M)) {
+    const int c2 = (int)seg_reduce_wave<OpAdd, SEG>(short1);
+    c = c >= M ? min(c2, M - 1) : c;
+  }
+  if (vk && ls == 0) a.sel[oo + k] = c;
 
-  // ---- 2. the new outer particle ----------------------------------------
-  if (ls == 0) {
-    float zc[DZ], nu[DX];
+  // ---- 2. the new outer particle (every lane of the segment the same) ----
+  {
+    float zc[DZ], nu[DX], xo[DX];
 #pragma unroll
     for (int d = 0; d < DZ; ++d) zc[d] = zp0[d * M + c];
     if (PLAIN)
       normals<DX>(key, (uint32_t)t, (uint32_t)k, 0u, P_DPF_X, nu);
     else
       normals<DX>(key, (uint32_t)t, (uint32_t)p, (uint32_t)c, P_LA_X, nu);
-    float xw[DX];
-    Mdl::fx(as_prm(a.prm), xp, zc, nu, PLAIN ? t : t - 1, xw);
+    // (opaque on both sides: products shared with the conditioning below
+    // would change what is fused, hence the rounding)
 #pragma unroll
-    for (int d = 0; d < DX; ++d) xs_sh[s][d] = xw[d];
-    if (vk) {
+    for (int d = 0; d < DX; ++d) {
+      xo[d] = xp[d];
+      asm volatile("" : "+v"(xo[d]));
+    }
+    Mdl::fx(as_prm(a.prm), xo, zc, nu, PLAIN ? t : t - 1, xn);
 #pragma unroll
-      for (int d = 0; d < DX; ++d) a.x[dst][(long long)d * a.NT + oo + k] = xw[d];
+    for (int d = 0; d < DX; ++d) asm volatile("" : "+v"(xn[d]));
+    if (vk && ls == 0) {
+#pragma unroll
+      for (int d = 0; d < DX; ++d) a.x[dst][(long long)d * a.NT + oo + k] = xn[d];
     }
   }
-  seg_lds_sync<SEG>();
-#pragma unroll
-  for (int d = 0; d < DX; ++d) xn[d] = xs_sh[s][d];
 
   }
   // the new clouds are written in slot order: the slots of copy dst become
@@ -2203,20 +2242,31 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   (void)c;
 
   // ---- 3. x-conditioned inner weights and local systematic resampling ---
+  // (lane ls: JPT consecutive inner particles)
   const float* lp = a.lam[src] + io + (long long)pc * M;
   float ev[JPT];
   float mk = -INFINITY;
   float cpx[kXZ ? NPX : 1];
   if constexpr (kXZ) Mdl::px_pre(as_prm(a.prm), xn, xp, PLAIN ? t : t - 1, cpx);
+  Items<kPre ? 1 : JPT> ki;
+  Items<kXZ && !kPre ? JPT : 1> zi[kXZ && !kPre ? DZ : 1];
+  if constexpr (!kPre) {
+    ki = load_items<JPT>(PLAIN ? ep : lp, ls * JPT, M);
+    if constexpr (kXZ) {
+#pragma unroll
+      for (int d = 0; d < DZ; ++d) zi[d] = load_items<JPT>(zp + d * M, ls * JPT, M);
+    }
+  }
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
+    const int j = ls * JPT + r;
     if (vk && j < M) {
-      float kap = kPre ? kpre[kPre ? r : 0] : (PLAIN ? ep[j] : lp[j]);
+      float kap = kPre ? kpre[kPre ? r : 0] : ki.v[kPre ? 0 : r];
       if constexpr (kXZ) {
         float zj[DZ];
 #pragma unroll
-        for (int d = 0; d < DZ; ++d) zj[d] = kPreZ ? zpre[kPreZ ? r : 0][kPreZ ? d : 0] : zp[d * M + j];
+        for (int d = 0; d < DZ; ++d)
+          zj[d] = kPreZ ? zpre[kPreZ ? r : 0][kPreZ ? d : 0] : zi[kPre ? 0 : d].v[kPre ? 0 : r];
         kap += Mdl::logpx_post(as_prm(a.prm), cpx, zj);
       }
       ev[r] = kap;
@@ -2227,20 +2277,24 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   }
   const float m2 = seg_max<SEG>(mk, sh);
   const bool deg2 = !(m2 > -INFINITY);
-  double carry = 0.0;
 #pragma unroll
-  for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
-    double w = 0.0;
-    if (j < M) w = deg2 ? 1.0 : (finitef(ev[r]) ? (double)fast_exp(ev[r] - m2) : 0.0);
-    double tot;
-    const double cc = seg_scan_incl<SEG>(w, sh, tot);
-    cdf[s][r * SEG + ls] = carry + cc;
-    carry += tot;
-  }
+  for (int r = 0; r < JPT; ++r)
+    ev[r] = ls * JPT + r < M ? (deg2 ? 1.0f : (finitef(ev[r]) ? fast_exp(ev[r] - m2) : 0.0f)) : 0.0f;
+  seg_cdf<SEG, JPT>(ev, cdf[s], sh);
   seg_lds_sync<SEG>();
-  const double u_in = ud.inner;
   const double tot2 = cdf[s][M - 1];
+  const SysPoints pts(ud.inner, tot2, M);
+  // inner ancestors of this lane's new particles ls, ls + SEG, ...
+  int anc2[kRoll ? 1 : JPT];
+  if constexpr (!kRoll) {
+    double P[JPT];
+#pragma unroll
+    for (int r = 0; r < JPT; ++r) {
+      const int jj = ls + r * SEG;
+      P[r] = jj < M ? pts(jj) : 0.0;
+    }
+    cdf_find<SEG * JPT, JPT>(cdf[s], M, tot2, P, anc2);
+  }
 
   // ---- 4. gather + propagate (+ measurement update in look-ahead mode) ---
   float pre[Mdl::NPRE];
@@ -2269,7 +2323,15 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     float lv = -INFINITY, gv = 0.f;
     if constexpr (kStream) {
       const bool on = vk && jj < M;
-      const int b = on ? cdf_search(cdf[s], M, sys_point(jj, u_in, tot2, M)) : 0;
+      int b;
+      if constexpr (kRoll) {
+        const double P[1] = {jj < M ? pts(jj) : 0.0};
+        int bb[1];
+        cdf_find<SEG * JPT, 1>(cdf[s], M, tot2, P, bb);
+        b = bb[0];
+      } else {
+        b = anc2[kRoll ? 0 : r];
+      }
       float zg[DZ], zn[DZ];
 #pragma unroll
       for (int d = 0; d < DZ; ++d) zg[d] = on ? zp[d * M + b] : 0.f;
@@ -2303,10 +2365,10 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         }
       }
     } else if (vk && jj < M) {
-      const int b = cdf_search(cdf[s], M, sys_point(jj, u_in, tot2, M));
+      const int b = anc2[kRoll ? 0 : r];
       float zg[DZ], zn[DZ], nu[DZ];
 #pragma unroll
-      for (int d = 0; d < DZ; ++d) zg[d] = zp[d * M + b];
+      for (int d = 0; d < DZ; ++d) zg[d] = at32(zp + d * M, b);
       if constexpr (kEarly) {
 #pragma unroll
         for (int d = 0; d < DZ; ++d) nu[d] = nue[kEarly ? r : 0][d];
@@ -2315,7 +2377,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       }
       Mdl::fz_post(as_prm(a.prm), pre, zg, nu, zn);
 #pragma unroll
-      for (int d = 0; d < DZ; ++d) zdst[d * M + jj] = zn[d];
+      for (int d = 0; d < DZ; ++d) put32(zdst + d * M, jj, zn[d]);
       if (!PLAIN) lv = Mdl::logpy_post(as_prm(a.prm), r0, zn);
       if constexpr (kKeepZ) {
 #pragma unroll

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kBlock) void k_learned_inner(StepArgs a) {
   if (tile.z == 0 && threadIdx.x == 0) a.act[f] = act ? 1 : 0;
   if (!act) return;
   const int N = a.fN[f], M = a.fM[f];
-  const int s = threadIdx.x / SEG;
+  const int s = SEG >= kWave ? __builtin_amdgcn_readfirstlane(threadIdx.x / SEG) : threadIdx.x / SEG;
   const int ls = threadIdx.x % SEG;
   const int i = tile.y + s;
   const bool vi = i < N;
@@ -241,16 +241,22 @@ __global__ __launch_bounds__(kBlock) void k_learned_inner(StepArgs a) {
   if constexpr (Mdl::kXdepZ) Mdl::px_pre(as_prm(a.prm), xn, xp, t - 1, cpx);
   float ev[JPT];
   float mk = -INFINITY;
+  const Items<JPT> ki = load_items<JPT>(lp, ls * JPT, M);
+  Items<JPT> zi[Mdl::kXdepZ ? DZ : 1];
+  if constexpr (Mdl::kXdepZ) {
+#pragma unroll
+    for (int d = 0; d < DZ; ++d) zi[d] = load_items<JPT>(zp + d * M, ls * JPT, M);
+  }
 #pragma unroll
   for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
+    const int j = ls * JPT + r;  // JPT consecutive inner particles per lane
     ev[r] = -INFINITY;
     if (vi && j < M) {
-      float kap = lp[j];
+      float kap = ki.v[r];
       if constexpr (Mdl::kXdepZ) {
         float zj[DZ];
 #pragma unroll
-        for (int d = 0; d < DZ; ++d) zj[d] = zp[d * M + j];
+        for (int d = 0; d < DZ; ++d) zj[d] = zi[Mdl::kXdepZ ? d : 0].v[r];
         kap += Mdl::logpx_post(as_prm(a.prm), cpx, zj);
       } else {
         kap += lpx0;
@@ -261,21 +267,24 @@ __global__ __launch_bounds__(kBlock) void k_learned_inner(StepArgs a) {
   }
   const float m2 = seg_max<SEG>(mk, sh);
   const bool deg2 = !(m2 > -INFINITY);
-  double carry = 0.0;
 #pragma unroll
-  for (int r = 0; r < JPT; ++r) {
-    const int j = ls + r * SEG;
-    double w = 0.0;
-    if (j < M) w = deg2 ? 1.0 : (finitef(ev[r]) ? (double)fast_exp(ev[r] - m2) : 0.0);
-    double tot;
-    const double cc = seg_scan_incl<SEG>(w, sh, tot);
-    cdf[s][r * SEG + ls] = carry + cc;
-    carry += tot;
-  }
-  __syncthreads();
+  for (int r = 0; r < JPT; ++r)
+    ev[r] = ls * JPT + r < M ? (deg2 ? 1.0f : (finitef(ev[r]) ? fast_exp(ev[r] - m2) : 0.0f)) : 0.0f;
+  seg_cdf<SEG, JPT>(ev, cdf[s], sh);
+  seg_lds_sync<SEG>();
   const double tot2 = cdf[s][M - 1];
   const float log_px = deg2 ? -INFINITY : m2 + fast_log((float)tot2);  // eq:approx1 at x_t
-  const double u_in = uniform53(key, (uint32_t)t, (uint32_t)i, P_INNER_U);
+  const SysPoints pts(uniform53(key, (uint32_t)t, (uint32_t)i, P_INNER_U), tot2, M);
+  int anc2[JPT];
+  {
+    double P[JPT];
+#pragma unroll
+    for (int r = 0; r < JPT; ++r) {
+      const int jj = ls + r * SEG;
+      P[r] = jj < M ? pts(jj) : 0.0;
+    }
+    cdf_find<SEG * JPT, JPT>(cdf[s], M, tot2, P, anc2);
+  }
 
   // ---- 3. local resampling, propagation, measurement update --------------
   float pre[Mdl::NPRE];
@@ -292,14 +301,14 @@ __global__ __launch_bounds__(kBlock) void k_learned_inner(StepArgs a) {
     const int jj = ls + r * SEG;
     llv[r] = -INFINITY;
     if (vi && jj < M) {
-      const int b = cdf_search(cdf[s], M, sys_point(jj, u_in, tot2, M));
+      const int b = anc2[r];
       float zg[DZ], nu[DZ], zn[DZ];
 #pragma unroll
-      for (int d = 0; d < DZ; ++d) zg[d] = zp[d * M + b];
+      for (int d = 0; d < DZ; ++d) zg[d] = at32(zp + d * M, b);
       normals<DZ>(key, (uint32_t)t, (uint32_t)i, (uint32_t)jj, P_NEW_Z, nu);
       Mdl::fz_post(as_prm(a.prm), pre, zg, nu, zn);
 #pragma unroll
-      for (int d = 0; d < DZ; ++d) zdst[d * M + jj] = zn[d];
+      for (int d = 0; d < DZ; ++d) put32(zdst + d * M, jj, zn[d]);
       if constexpr (kKeepZ) {
 #pragma unroll
         for (int d = 0; d < DZ; ++d) zkeep[kKeepZ ? r : 0][d] = zn[d];

@@ -229,22 +229,28 @@ __device__ __forceinline__ float seg_sum_ord(const float* x) {
   return R[0];
 }
 
+// The last lane's value in every lane of a segment of up to 64 lanes.
+template <int SEG>
+__device__ __forceinline__ double seg_last(double v) {
+  if constexpr (SEG == 8) {
+    const double t0 = dpp_d<kDppRowBcast + 7>(v, v), t1 = dpp_d<kDppRowBcast + 15>(v, v);
+    return (threadIdx.x & 8) ? t1 : t0;
+  } else if constexpr (SEG == 16) {
+    return dpp_d<kDppRowBcast + 15>(v, v);
+  } else if constexpr (SEG == 32) {
+    return (threadIdx.x & 63) < 32 ? readlane_d(v, 31) : readlane_d(v, 63);
+  } else {
+    return readlane_d(v, 63);
+  }
+}
+
 // Inclusive FP64 scan within the segment; `total` receives the segment sum.
 template <int SEG>
 __device__ __forceinline__ double seg_scan_incl(double v, SegScratch& sh, double& total) {
   constexpr int W = wave_width<SEG>();
   v = seg_scan_wave<W>(v);
   if constexpr (SEG <= kWave) {
-    if constexpr (W == 8) {
-      const double t0 = dpp_d<kDppRowBcast + 7>(v, v), t1 = dpp_d<kDppRowBcast + 15>(v, v);
-      total = (threadIdx.x & 8) ? t1 : t0;
-    } else if constexpr (W == 16) {
-      total = dpp_d<kDppRowBcast + 15>(v, v);
-    } else if constexpr (W == 32) {
-      total = (threadIdx.x & 63) < 32 ? readlane_d(v, 31) : readlane_d(v, 63);
-    } else {
-      total = readlane_d(v, 63);
-    }
+    total = seg_last<W>(v);
   } else {
     const int w = threadIdx.x / kWave;
     if ((threadIdx.x & (kWave - 1)) == kWave - 1) sh.d[0][w] = v;
@@ -311,6 +317,91 @@ __device__ __forceinline__ int xcd_contiguous_tile(int b, int n) {
   constexpr int kXcd = 8;
   const int q = n / kXcd, r = n % kXcd, x = b % kXcd;
   return x * q + min(x, r) + b / kXcd;
+}
+
+// The points of one resampling with a fixed count n: sys_point with the
+// division replaced by the correctly rounded reciprocal y of n and Markstein's
+// correction (q = RN(b y); r = b - q n, exact by one FMA; RN(q + r y) is the
+// correctly rounded b / n: P. Markstein, "Computation of elementary functions
+// on the IBM RISC System/6000 processor", IBM J. R&D 34, 1990), so the same
+// bits for totals away from under- and overflow: these are sums of weights
+// whose largest is 1.
+struct SysPoints {
+  double u, total, n, y;
+  __device__ __forceinline__ SysPoints(double u_, double total_, int n_out)
+      : u(u_), total(total_), n((double)n_out), y(1.0 / (double)n_out) {}
+  __device__ __forceinline__ double operator()(int k) const {
+    const double b = ((double)k + u) * total;
+    const double q = b * y;
+    return __builtin_fma(__builtin_fma(-q, n, b), y, q);
+  }
+};
+
+// A segment's cumulative weights of items j = ls JPT + r (lane ls holds JPT
+// consecutive ones, w[r], 0 beyond the last) into cdf[SEG JPT]: lane sums, one
+// scan over the lanes, then each lane walks its items (capped by its scanned
+// total).  Entries beyond the last item repeat the total.
+template <int SEG, int JPT, class T>
+__device__ __forceinline__ void seg_cdf(const T* w, double* cdf, SegScratch& sh) {
+  const int ls = threadIdx.x % SEG;
+  double acc = 0.0, ex, incl;
+#pragma unroll
+  for (int r = 0; r < JPT; ++r) acc += (double)w[r];
+  if constexpr (SEG <= kWave) {
+    seg_scan_wave_both<SEG>(acc, ex, incl);
+  } else {
+    seg_scan_wave_both<kWave>(acc, ex, incl);
+    const int v = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) sh.d[0][v] = incl;
+    __syncthreads();
+    const int w0 = (threadIdx.x / SEG) * (SEG / kWave);
+    double pre = 0.0;
+#pragma unroll
+    for (int q = 0; q < SEG / kWave; ++q)
+      if (w0 + q < v) pre += sh.d[0][w0 + q];
+    ex += pre;
+    incl += pre;
+  }
+  double cum = ex;
+#pragma unroll
+  for (int r = 0; r < JPT; ++r) {
+    cum += (double)w[r];
+    cdf[ls * JPT + r] = r == JPT - 1 ? incl : fmin(cum, incl);
+  }
+}
+
+// The systematic search rule (cdf_search) for R points at once over a
+// segment's n cumulative weights C (NMAX entries, the last total repeated):
+// a branch-free search with steps of falling powers of two, R independent
+// chains whose LDS reads overlap, three instructions per probe.  (One point
+// after the other, by halving an interval: eight instructions and an exposed
+// LDS latency per probe, a seventh of the new-cloud kernel's life.)  A point
+// at or past the total takes the rule's second form.
+template <int NMAX, int R>
+__device__ __forceinline__ void cdf_find(const double* C, int n, double total, const double (&P)[R], int (&b)[R]) {
+  if constexpr (NMAX == 1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) b[r] = 0;
+  } else {
+    constexpr int S0 = [] {
+      int s = 1;
+      while (2 * s < NMAX) s *= 2;
+      return s;
+    }();
+    const double* c[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) c[r] = C[S0 - 1] <= P[r] ? C + (NMAX - S0) : C;
+#pragma unroll
+    for (int st = S0 / 2; st >= 1; st /= 2) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) c[r] = c[r][st - 1] <= P[r] ? c[r] + st : c[r];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      b[r] = min((int)(c[r] - C), n - 1);
+      if (!(P[r] < total)) b[r] = cdf_search(C, n, P[r]);
+    }
+  }
 }
 
 __device__ __forceinline__ bool finitef(float v) { return fabsf(v) <= 3.402823466e38f; }

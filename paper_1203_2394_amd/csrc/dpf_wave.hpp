@@ -159,4 +159,33 @@ __device__ __forceinline__ T seg_scan_wave(T v) {
   return v;
 }
 
+// Inclusive and exclusive FP64 scan over segments of W lanes (the association
+// of seg_scan_wave).
+template <int W>
+__device__ __forceinline__ void seg_scan_wave_both(double v, double& ex, double& incl) {
+  static_assert(W == 8 || W == 16 || W == 32 || W == 64, "segment width");
+  if constexpr (W == 8) {
+    incl = seg_scan_wave<8>(v);
+    const double up = dpp_d<kDppRowShr1>(incl, 0.0);
+    ex = (threadIdx.x & 7) ? up : 0.0;
+  } else {
+    v = seg_scan_wave<16>(v);
+    ex = dpp_d<kDppRowShr1>(v, 0.0);
+    if constexpr (W == 16) {
+      incl = v;
+    } else {
+      const double t0 = readlane_d(v, 15), t1 = readlane_d(v, 31), t2 = readlane_d(v, 47);
+      const int row = (threadIdx.x & 63) >> 4;
+      double off = 0.0;
+      if constexpr (W == 32) {
+        off = row == 1 ? t0 : (row == 3 ? t2 : 0.0);
+      } else {
+        off = row == 1 ? t0 : (row == 2 ? t0 + t1 : (row == 3 ? (t0 + t1) + t2 : 0.0));
+      }
+      incl = v + off;
+      ex += off;
+    }
+  }
+}
+
 }  // namespace dpf
