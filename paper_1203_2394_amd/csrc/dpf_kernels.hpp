@@ -633,15 +633,20 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
   constexpr int NSEG = kBlock / SEG, CAP = SEG * JPT;
   constexpr bool kCond = Mdl::kXdepZ;
   constexpr bool kHoldZ = kCond && JPT * DZ <= 64;  // the lane's cloud stays in registers
+  constexpr bool kAux = kCond && Mdl::kAux;
   __shared__ SegScratch sh;
   __shared__ double cdf[NSEG][kCond ? 1 : CAP];
   __shared__ float cz[NSEG][kCond ? CAP : 1][DZ];
+  __shared__ float caux[NSEG][kAux ? CAP : 1];
   __shared__ float lms[NSEG][kCond ? CAP : 1];
-  // each lane's conditioned weights of its current candidate, kept between
-  // the total and the cumulative pass when the cloud is small (row padded
-  // by one word: lanes at the same index fall in different banks)
-  constexpr bool kWCache = kCond && CAP <= 32;
-  __shared__ float wc[kWCache ? kBlock : 1][kWCache ? CAP + 1 : 1];
+  // small clouds: each lane's conditioned log-weights of its current
+  // candidate, then, per pair of items, the first one's weight and the
+  // cumulative weight after the second (the sum between them is one addition:
+  // a quarter less LDS than all sums, three workgroups per CU instead of two),
+  // [pair][lane]: a lane's entries lie in its own banks whatever the pair
+  constexpr bool kCum = kCond && CAP <= 32;
+  __shared__ double cum2[kCum ? CAP / 2 : 1][kCum ? kBlock : 1];
+  __shared__ float wev[kCum ? CAP / 2 : 1][kCum ? kBlock : 1];
   constexpr bool kH = has_yhat<Mdl>();
   const int4 tile = a.tiles[ti];
   const int f = tile.x;
@@ -735,17 +740,22 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
         float pre[Mdl::NPRE], r0[DY];
         Mdl::fz_pre(as_prm(a.prm), x, xl[r], t - 1, pre);
         Mdl::obs_pre(as_prm(a.prm), y, xl[r], r0);
-        const double u = uniform53_ab(key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_B);
+        const SysPoints pts(uniform53_ab(key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_B), total, K);
         Lse acck;
         float hk = 0.f;
         for (int k0 = 0; k0 < K; k0 += CPB) {
           float nb[CPB * DZ];
+          double P[CPB];
+          int bk[CPB];
           normals_kb<DZ>(key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_Z, k0, nb);
+#pragma unroll
+          for (int q = 0; q < CPB; ++q) P[q] = k0 + q < K ? pts(k0 + q) : 0.0;
+          cdf_find<CAP, CPB>(cdf[s], M, total, P, bk);
 #pragma unroll
           for (int q = 0; q < CPB; ++q) {
             const int k = k0 + q;
             if (k >= K) break;
-            const int b = cdf_search(cdf[s], M, sys_point(k, u, total, K));
+            const int b = bk[q];
             float zg[DZ], zc[DZ];
 #pragma unroll
             for (int d = 0; d < DZ; ++d) zg[d] = zrow[d * M + b];
@@ -766,12 +776,16 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
       }
     }
   } else {
-    // ---- each lane scores its own candidates.  Per candidate, three passes
-    // over the segment's cloud (staged in LDS, read by every lane at the same
-    // index): the largest conditioned log-weight, the FP64 total, then the
-    // cumulative sum in inner order up to each systematic point (companion k
-    // takes the first index whose cumulative weight exceeds point k; points
-    // at or past the total take the last index with positive weight).
+    // ---- each lane scores its own candidates.  Per candidate, passes over
+    // the segment's cloud (staged in LDS, read by every lane at the same
+    // index, with what the model needs of each z alone): the largest
+    // conditioned log-weight, then the FP64 cumulative sum in inner order.
+    // Companion k takes the first index whose cumulative weight exceeds point
+    // k; points at or past the total take the last index with positive
+    // weight.  Clouds of up to 32 keep the log-weights and the cumulative
+    // sums in the lane's LDS column and search it (256 filters of 200 x 20,
+    // K = 8: 99 us with the log-weights and their divisions formed again in each
+    // pass and a cursor per lane, 58 us now); larger ones form them again.
 #pragma unroll
     for (int r = 0; r < JPT; ++r) {
       const int j = ls + r * SEG;
@@ -779,7 +793,22 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
 #pragma unroll
         for (int d = 0; d < DZ; ++d)
           cz[s][kCond ? j : 0][d] = vi ? (kHoldZ ? zh[kHoldZ ? r : 0][kHoldZ ? d : 0] : zrow[d * M + j]) : 0.f;
+        if constexpr (kAux) caux[s][kAux ? j : 0] = Mdl::aux(cz[s][kCond ? j : 0]);
       }
+    }
+    // items beyond M: no weight (up to a multiple of four), +inf for the searches
+#pragma unroll
+    for (int r = 0; r < JPT; ++r) {
+      const int j = ls + r * SEG;
+      if (j >= M) {
+#pragma unroll
+        for (int d = 0; d < DZ; ++d) cz[s][kCond ? j : 0][d] = 0.f;
+        if constexpr (kAux) caux[s][kAux ? j : 0] = 0.f;
+        lms[s][kCond ? j : 0] = -INFINITY;
+      }
+    }
+    if constexpr (kCum) {
+      for (int q = (M + 3) / 4 * 2; q < CAP / 2; ++q) cum2[kCum ? q : 0][kCum ? threadIdx.x : 0] = INFINITY;
     }
     seg_lds_sync<SEG>();
     if (vi) {
@@ -791,38 +820,64 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
         float cpx[Mdl::NPX];
         Mdl::px_pre(as_prm(a.prm), xl[r], x, t - 1, cpx);
         auto kappa = [&](int jj) {
-          float zj[DZ];
+          float zj[DZ], lx;
 #pragma unroll
           for (int d = 0; d < DZ; ++d) zj[d] = cz[s][kCond ? jj : 0][d];
-          float kp = lms[s][kCond ? jj : 0] + Mdl::logpx_post(as_prm(a.prm), cpx, zj);
+          if constexpr (kAux) lx = Mdl::logpx_post_aux(as_prm(a.prm), cpx, zj, caux[s][kAux ? jj : 0]);
+          else lx = Mdl::logpx_post(as_prm(a.prm), cpx, zj);
+          float kp = lms[s][kCond ? jj : 0] + lx;
           asm volatile("" : "+v"(kp));
           return kp;
         };
+        // this lane's columns; they hold the log-weights first (odd items' in
+        // the low words of cum2)
+        double* const cum = &cum2[0][kCum ? threadIdx.x : 0];
+        float* const we = &wev[0][kCum ? threadIdx.x : 0];
+        constexpr int CST = kCum ? kBlock : 1;  // entries from one pair to the next
+        auto keep = [&](int jj, float kp) {
+          if (jj & 1) cum[(jj >> 1) * CST] = __hiloint2double(0, __float_as_int(kp));
+          else we[(jj >> 1) * CST] = kp;
+        };
+        auto kept = [&](int jj) -> float {
+          return (jj & 1) ? __int_as_float(__double2loint(cum[(jj >> 1) * CST])) : we[(jj >> 1) * CST];
+        };
+        // (items by fours, so that their LDS reads and exponentials overlap;
+        // those beyond M weigh nothing)
+        constexpr int U = CAP % 4 == 0 ? 4 : 1;
         float mx = -INFINITY;
-        for (int jj = 0; jj < M; ++jj) {
-          const float kp = kappa(jj);
-          if (finitef(kp)) mx = fmaxf(mx, kp);
+        for (int j4 = 0; j4 < M; j4 += U) {
+          float kp[U];
+#pragma unroll
+          for (int v = 0; v < U; ++v) kp[v] = kappa(j4 + v);
+#pragma unroll
+          for (int v = 0; v < U; ++v) {
+            if constexpr (kCum) keep(j4 + v, kp[v]);
+            mx = fmaxf(mx, finitef(kp[v]) ? kp[v] : -INFINITY);
+          }
         }
         const bool deg = !(mx > -INFINITY);
         auto weight = [&](int jj) -> float {
-          const float kp = kappa(jj);
-          return deg ? 1.0f : (finitef(kp) ? fast_exp(kp - mx) : 0.0f);
+          const float kp = kCum ? kept(jj) : kappa(jj);
+          const float w = finitef(kp) ? fast_exp(kp - mx) : 0.0f;
+          return deg ? (jj < M ? 1.0f : 0.0f) : w;
         };
         double total = 0.0;
         int lastpos = 0;
-        for (int jj = 0; jj < M; ++jj) {
-          const float w = weight(jj);
-          if constexpr (kWCache) wc[kWCache ? threadIdx.x : 0][kWCache ? jj : 0] = w;
-          total += (double)w;
-          if (w > 0.0f) lastpos = jj;
+        for (int j4 = 0; j4 < M; j4 += U) {
+          float w[U];
+#pragma unroll
+          for (int v = 0; v < U; ++v) w[v] = weight(j4 + v);
+#pragma unroll
+          for (int v = 0; v < U; ++v) {
+            total += (double)w[v];
+            if constexpr (kCum) {
+              if (v & 1) cum[(j4 / 2 + v / 2) * CST] = total;
+              else we[(j4 / 2 + v / 2) * CST] = w[v];
+            }
+            lastpos = w[v] > 0.0f ? j4 + v : lastpos;
+          }
         }
-        // the third pass takes these weights back (small clouds) or forms
-        // them again, the same values either way
-        auto weight3 = [&](int jj) -> double {
-          if constexpr (kWCache) return (double)wc[kWCache ? threadIdx.x : 0][kWCache ? jj : 0];
-          else return (double)weight(jj);
-        };
-        const double u = uniform53_ab(key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_B);
+        const SysPoints pts(uniform53_ab(key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_B), total, K);
         float pre[Mdl::NPRE], r0[DY];
         Mdl::fz_pre(as_prm(a.prm), x, xl[r], t - 1, pre);
         Mdl::obs_pre(as_prm(a.prm), y, xl[r], r0);
@@ -832,7 +887,8 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
           float zg[DZ], zc[DZ];
 #pragma unroll
           for (int d = 0; d < DZ; ++d) zg[d] = cz[s][kCond ? b : 0][d];
-          Mdl::fz_post(as_prm(a.prm), pre, zg, nu, zc);
+          if constexpr (kAux) Mdl::fz_post_aux(as_prm(a.prm), pre, zg, caux[s][kAux ? b : 0], nu, zc);
+          else Mdl::fz_post(as_prm(a.prm), pre, zg, nu, zc);
           acck.add(Mdl::logpy_post(as_prm(a.prm), r0, zc));
           if constexpr (kH) {
             if (want_h) {
@@ -842,24 +898,55 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
             }
           }
         };
-        // companion k: a cursor over the cumulative sum advances to the
-        // first index whose sum exceeds point k (the points increase), then
-        // every lane propagates its companion k together
+        // (larger clouds) a cursor over the cumulative sum: the points increase
         int jc = -1;
         double c = 0.0;
         for (int k0 = 0; k0 < K; k0 += CPB) {
           float nb[CPB * DZ];
           normals_kb<DZ>(key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_Z, k0, nb);
+          int bk[CPB];
+          if constexpr (kCum) {
+            // CPB searches of the pairs at once (+inf beyond M), then the pair's
+            // first item
+            constexpr int NQ = CAP / 2;
+            constexpr int S0 = [] {
+              int st = 1;
+              while (2 * st < NQ) st *= 2;
+              return st;
+            }();
+            double P[CPB];
+            const double* at[CPB];
+#pragma unroll
+            for (int q = 0; q < CPB; ++q) {
+              P[q] = k0 + q < K ? pts(k0 + q) : 0.0;
+              at[q] = cum[(S0 - 1) * CST] <= P[q] ? cum + (NQ - S0) * CST : cum;
+            }
+#pragma unroll
+            for (int st = S0 / 2; st >= 1; st /= 2) {
+#pragma unroll
+              for (int q = 0; q < CPB; ++q) at[q] = at[q][(st - 1) * CST] <= P[q] ? at[q] + st * CST : at[q];
+            }
+#pragma unroll
+            for (int q = 0; q < CPB; ++q) {
+              const int pr = (int)(at[q] - cum) / CST;
+              const double before = pr > 0 ? cum[(pr - 1) * CST] : 0.0;
+              const int b = 2 * pr + (before + (double)we[pr * CST] <= P[q] ? 1 : 0);
+              bk[q] = P[q] < total ? min(b, M - 1) : lastpos;
+            }
+          }
 #pragma unroll
           for (int q = 0; q < CPB; ++q) {
             const int k = k0 + q;
             if (k >= K) break;
-            const double P = sys_point(k, u, total, K);
-            while (!(c > P) && jc + 1 < M) {
-              ++jc;
-              c += weight3(jc);
+            if constexpr (!kCum) {
+              const double P = pts(k);
+              while (!(c > P) && jc + 1 < M) {
+                ++jc;
+                c += (double)weight(jc);
+              }
+              bk[q] = c > P ? jc : lastpos;
             }
-            emit(c > P ? jc : lastpos, nb + q * DZ);
+            emit(bk[q], nb + q * DZ);
           }
         }
         const float g = (acck.m == -INFINITY) ? -INFINITY : acck.m + fast_log(acck.s) - logK;

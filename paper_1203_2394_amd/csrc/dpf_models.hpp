@@ -16,6 +16,8 @@
 //                                 part that does not, NPX values, so that
 //   logpx_post(P, c, z)           gives logpx for many z at the cost of the
 //                                 z-dependent terms alone
+//   aux(z), fz_post_aux, logpx_post_aux   (kAux models) a value of z alone that
+//                                 fz_post and logpx_post need, and those with it given
 //   obs_mean(P, x, z, h)          the noise-free observation h(x, z) (models with
 //                                 a one-dimensional y: the predicted observation)
 //
@@ -91,6 +93,7 @@ struct LinGauss {
   static constexpr int DX = DX_, DZ = DZ_, DY = DY_, NPRE = DZ_;
   static constexpr bool kXdepZ = true;
   static constexpr bool kStreamZ = false;
+  static constexpr bool kAux = false;
   struct Layout {
     static constexpr int Ax = 0, Cxz = Ax + DX * DX, qx = Cxz + DX * DZ, Az = qx + 1,
                          Bzx = Az + DZ * DZ, qz = Bzx + DZ * DX, Hx = qz + 1, Hz = Hx + DY * DX,
@@ -208,6 +211,7 @@ struct NonLin {
   static constexpr int DX = DX_, DZ = DZ_, DY = DZ_, NPRE = DZ;
   static constexpr bool kXdepZ = false;
   static constexpr bool kStreamZ = false;
+  static constexpr bool kAux = false;
   struct Layout {
     static constexpr int a = 0, b = 1, qx = 2, W = 3, rho = W + DZ * DX, qz = rho + 1, c = qz + 1,
                          r = c + 1, bmode = r + 1, n_raw = bmode + 1;
@@ -280,6 +284,7 @@ struct HighDim {
   static constexpr int DX = DX_, DZ = DZ_, DY = DY_, NPRE = DZ;
   static constexpr bool kXdepZ = false;
   static constexpr bool kStreamZ = true;
+  static constexpr bool kAux = false;
   static constexpr int NPL = DX;
   struct Layout {
     static constexpr int a = 0, b = 1, qx = 2, Alo = 3, Adg = Alo + DZ - 1, Aup = Adg + DZ,
@@ -472,6 +477,18 @@ struct Table1M1 {
     px_pre(P, xn, x, t, c);
     return logpx_post(P, c, z);
   }
+  // The same with sat(i) given (kAux: a value of z alone, shared by everything
+  // that visits the particle -- an FP32 division otherwise repeated there).
+  static constexpr bool kAux = true;
+  __device__ static float aux(const float* z) { return sat(z[0]); }
+  __device__ static void fz_post_aux(Prm P, const float* pre, const float* z, float s, const float* nu, float* zn) {
+    zn[0] = pre[1] * z[0] + pre[2] * s + pre[0] + P[L::sic] * nu[0];
+  }
+  __device__ static float logpx_post_aux(Prm P, const float* c, const float* z, float s) {
+    const float si = c[2] != 0.0f ? c[2] * s : 0.0f;
+    const float e = c[0] - c[1] * z[0] - si;
+    return P[L::co] - 0.5f * P[L::inv_qo] * e * e;
+  }
   // noise-free observation h(x, z) = atan(x) + z^2 / 20
   __device__ static void obs_mean(Prm, const float* x, const float* z, float* h) {
     h[0] = ZF ? atanf(z[0]) + 0.05f * x[0] * x[0] : atanf(x[0]) + 0.05f * z[0] * z[0];
@@ -494,6 +511,7 @@ struct FourDim {
   static constexpr int DX = 2, DZ = 2, DY = 1, NPRE = 2;
   static constexpr bool kXdepZ = false;
   static constexpr bool kStreamZ = false;
+  static constexpr bool kAux = false;
   struct Layout {
     static constexpr int a1 = 0, bs = 1, c21 = 2, a2 = 3, qx1 = 4, qx2 = 5, qz1 = 6, qz2 = 7, cz = 8, rho = 9,
                          b = 10, amp = 11, freq = 12, r = 13, n_raw = 14;
