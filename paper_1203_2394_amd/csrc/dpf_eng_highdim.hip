@@ -23,6 +23,21 @@ static void derive_highdim(int dx, int dz, int dy, const double* p, std::vector<
                       0.5 * log(nu * M_PI * r)));                // lt0
   o.push_back((float)(0.5 * (nu + 1.0)));                        // tnu
   o.push_back((float)(1.0 / (nu * r)));                          // inv_nur
+  // the transition's rows by pairs of components (copies of the raw values)
+  const double* lo = p + 3;
+  const double* dg = lo + dz - 1;
+  const double* up = dg + dz;
+  const double* B = up + dz - 1;
+  for (int s = 0; s < dz / 2; ++s) {
+    const int k = 2 * s;
+    const double alo[2] = {k > 0 ? lo[k - 1] : 0.0, lo[k]}, aup[2] = {up[k], k + 2 < dz ? up[k + 1] : 0.0};
+    for (int h = 0; h < 2; ++h) o.push_back((float)dg[k + h]);
+    for (int h = 0; h < 2; ++h) o.push_back((float)alo[h]);
+    for (int h = 0; h < 2; ++h) o.push_back((float)aup[h]);
+    for (int h = 0; h < 2; ++h)
+      for (int d = 0; d < dx; ++d) o.push_back((float)B[(k + h) * dx + d]);
+    for (int q = 6 + 2 * dx; q < 16; ++q) o.push_back(0.0f);
+  }
 }
 
 const Engine kEngHighDim = make_engine<HighDim<4, 64, 32>>([](const double* p, std::vector<float>& o) { derive_highdim(4, 64, 32, p, o); });

@@ -511,11 +511,15 @@ __device__ __forceinline__ float la_logpy_wave(const StepArgs& a, const Key& key
   Mdl::fz_lite(P, x, xl, t - 1, c);
   WaveProj<Mdl> pj;
   pj.start();
+  const float sz = P[Mdl::Layout::sz];
+  auto nxt = Mdl::load_pair(P, 0);  // the rows of the next pair, fetched one ahead
   normal_pairs<Mdl::DX, Mdl::DX + Mdl::DZ, true>(
       key, (uint32_t)t, (uint32_t)i, (uint32_t)j, P_LA_X, r24f(w0), [&](int d, float n0, float n1) {
         const int kk = d - Mdl::DX;
-        const float z0 = Mdl::fz_post_k(P, Mdl::fz_pre_lite(P, c, kk), z, n0, kk);
-        const float z1 = Mdl::fz_post_k(P, Mdl::fz_pre_lite(P, c, kk + 1), z, n1, kk + 1);
+        const auto row = nxt;
+        if (kk + 2 < Mdl::DZ) nxt = Mdl::load_pair(P, kk / 2 + 1);
+        const float z0 = Mdl::fz_post_row(row, 0, sz, Mdl::fz_pre_row(row, 0, c), z, n0, kk);
+        const float z1 = Mdl::fz_post_row(row, 1, sz, Mdl::fz_pre_row(row, 1, c), z, n1, kk + 1);
         pj.add(ca[kk / 2], z0, z1);
       });
   return pj.logpy(P, yrow);
@@ -568,7 +572,9 @@ __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool 
     // wide z: every lane of the wave takes part in the matrix-core residual
     float ca[WaveProj<Mdl>::NA];
     WaveProj<Mdl>::load_a(as_prm(a.prm), ca);
-    const float* yrow = y_row<Mdl>(a, f, t);
+    __shared__ __align__(16) float yrow[Mdl::DY];
+    if (threadIdx.x < Mdl::DY) yrow[threadIdx.x] = y_row<Mdl>(a, f, t)[threadIdx.x];
+    __syncthreads();
     for (int r = 0; r < JPT; ++r) {
       const int j = ls + r * SEG;
       const bool on = vi && j < M;
@@ -2384,9 +2390,22 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   }
 
   // ---- 4. gather + propagate (+ measurement update in look-ahead mode) ---
-  float pre[Mdl::NPRE];
   // (plain: t is the step just taken and the proposal is for t + 1)
-  fz_pre_seg<Mdl, SEG>(as_prm(a.prm), xp, xn, PLAIN ? t : t - 1, pre);
+  // Wide z, a wave or more per particle: component q of the shared part stays
+  // in lane q and is read from there when its turn comes (64 scalars held at
+  // once spilled).
+  constexpr bool kPreLane = kStream && SEG >= kWave && DZ <= kWave;
+  float pre[kPreLane ? 1 : Mdl::NPRE];
+  if constexpr (kPreLane) {
+    const int q = threadIdx.x & (kWave - 1);
+    pre[0] = Mdl::fz_pre_k(as_prm(a.prm), xp, xn, PLAIN ? t : t - 1, q < DZ ? q : 0);
+  } else {
+    fz_pre_seg<Mdl, SEG>(as_prm(a.prm), xp, xn, PLAIN ? t : t - 1, pre);
+  }
+  auto pre_at = [&](int d) -> float {
+    if constexpr (kPreLane) return readlane_f(pre[0], d);
+    else return pre[kPreLane ? 0 : d];
+  };
   float y[DY], r0[DY];
   if (!PLAIN) {
     load_y<Mdl>(a, f, t, y);
@@ -2403,7 +2422,15 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   // wide z: the new z of every lane of the wave goes through the matrix-core
   // residual together (lanes without a particle carry zeros)
   float ca[kStream ? Mdl::DZ / 2 : 1];
-  if constexpr (kStream) WaveProj<Mdl>::load_a(as_prm(a.prm), ca);
+  __shared__ __align__(16) float y_sh[kStream ? 2 : 1][kStream ? DY : 4];  // y_t, y_{t+1}
+  if constexpr (kStream) {
+    WaveProj<Mdl>::load_a(as_prm(a.prm), ca);
+    if (!PLAIN && threadIdx.x < 2 * DY) {
+      const int h = threadIdx.x / DY, q = threadIdx.x % DY;
+      y_sh[h][kStream ? q : 0] = y_row<Mdl>(a, f, h ? min(t, a.run_T - 1) + 1 : t)[q];
+    }
+    __syncthreads();
+  }
 #pragma unroll kRoll ? 1 : JPT
   for (int r = 0; r < JPT; ++r) {
     const int jj = ls + r * SEG;
@@ -2425,10 +2452,14 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       const Prm P = as_prm(a.prm);
       WaveProj<Mdl> pj;
       pj.start();
+      const float sz = P[Mdl::Layout::sz];
+      auto nxt = Mdl::load_pair(P, 0);  // the rows of the next pair, fetched one ahead
       normal_pairs<0, DZ, false>(key, (uint32_t)t, (uint32_t)k, (uint32_t)jj, PLAIN ? P_DPF_Z : P_NEW_Z, 0.f,
                                  [&](int d, float n0, float n1) {
-                                   zn[d] = Mdl::fz_post_k(P, pre[d], zg, n0, d);
-                                   zn[d + 1] = Mdl::fz_post_k(P, pre[d + 1], zg, n1, d + 1);
+                                   const auto row = nxt;
+                                   if (d + 2 < DZ) nxt = Mdl::load_pair(P, d / 2 + 1);
+                                   zn[d] = Mdl::fz_post_row(row, 0, sz, pre_at(d), zg, n0, d);
+                                   zn[d + 1] = Mdl::fz_post_row(row, 1, sz, pre_at(d + 1), zg, n1, d + 1);
                                    if (on) {
                                      zdst[d * M + jj] = zn[d];
                                      zdst[(d + 1) * M + jj] = zn[d + 1];
@@ -2440,11 +2471,9 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         for (int d = 0; d < DZ; ++d) zkeep[kKeepZ ? r : 0][d] = zn[d];
       }
       if (!PLAIN) {
-        const float l0 = pj.logpy(P, y_row<Mdl>(a, f, t));
+        const float l0 = pj.logpy(P, y_sh[0]);
         // the next step's look-ahead likelihood of these new inner particles
-        const float g0 = fuse ? la_logpy_wave<Mdl>(a, key, t + 1, k, jj, xn, zn,
-                                                   y_row<Mdl>(a, f, min(t, a.run_T - 1) + 1), ca)
-                              : 0.f;
+        const float g0 = fuse ? la_logpy_wave<Mdl>(a, key, t + 1, k, jj, xn, zn, y_sh[kStream ? 1 : 0], ca) : 0.f;
         if (on) {
           lv = l0;
           gv = g0;

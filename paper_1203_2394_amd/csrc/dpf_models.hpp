@@ -296,9 +296,45 @@ struct HighDim {
     //          tnu = (nu+1)/2, inv_nur = 1/(nu r)
     static constexpr int sx = n_raw, sz = sx + 1, inv_qx = sz + 1, cx = inv_qx + 1,
                          inv_r = cx + 1, cy = inv_r + 1, lg0 = cy + 1, lt0 = lg0 + 1,
-                         tnu = lt0 + 1, inv_nur = tnu + 1, n_total = inv_nur + 1;
+                         tnu = lt0 + 1, inv_nur = tnu + 1,
+                         // the transition's rows by pairs of components, 16 floats each (one
+                         // 64-byte scalar load): Adg, Alo, Aup, B of both (Alo of the first
+                         // component and Aup of the last: 0, not used)
+                         pr = inv_nur + 1, n_total = pr + 16 * (DZ / 2);
   };
   using L = Layout;
+  static_assert(DX == 4 && DZ % 2 == 0, "pair rows: 3 x 2 + 2 x 4 of 16 floats");
+  // Rows of components 2 s and 2 s + 1.
+  struct Pair {
+    float adg[2], alo[2], aup[2], b[2][DX];
+  };
+  __device__ static __forceinline__ Pair load_pair(Prm P, int s) {
+    Prm q = P + L::pr + 16 * s;
+    Pair r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      r.adg[h] = q[h];
+      r.alo[h] = q[2 + h];
+      r.aup[h] = q[4 + h];
+#pragma unroll
+      for (int d = 0; d < DX; ++d) r.b[h][d] = q[6 + DX * h + d];
+    }
+    return r;
+  }
+  // fz_pre_lite and fz_post_k of component k (= h mod 2) with its row given.
+  __device__ static __forceinline__ float fz_pre_row(const Pair& r, int h, const float* c) {
+    float s = 0.f;
+#pragma unroll
+    for (int d = 0; d < DX; ++d) s += r.b[h][d] * c[d];
+    return s;
+  }
+  __device__ static __forceinline__ float fz_post_row(const Pair& r, int h, float sz, float prek, const float* z,
+                                                      float nuk, int k) {
+    float v = prek + r.adg[h] * z[k] + sz * nuk;
+    if (k > 0) v += r.alo[h] * z[k - 1];
+    if (k + 1 < DZ) v += r.aup[h] * z[k + 1];
+    return v;
+  }
 
   __device__ static void fx(Prm P, const float* x, const float*, const float* nu, int,
                             float* xn) {
@@ -348,8 +384,9 @@ struct HighDim {
   // components of log((1 - eps) N(e_k; 0, r) + eps t_nu(e_k; 0, r)), each as
   // max + log(1 + exp(-|difference|))
   __device__ static float row_term(Prm P, float e) {
-    const float e2 = e * e;
-    if (P[L::gonly] != 0.0f) return e2;
+    return P[L::gonly] != 0.0f ? e * e : row_mix(P, e * e);
+  }
+  __device__ static __forceinline__ float row_mix(Prm P, float e2) {
     const float lg = P[L::lg0] - 0.5f * P[L::inv_r] * e2;
     const float lt = P[L::lt0] - P[L::tnu] * fast_log(1.0f + e2 * P[L::inv_nur]);
     const float mx = fmaxf(lg, lt);

@@ -64,16 +64,34 @@ struct WaveProj {
     d1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, __uint_as_float(b[1]), d1, 0, 0, 0);
   }
 
-  // log p(y | z) of this lane's particle; y the observation (DY values in
-  // memory), added to -C z row by row.
+  // log p(y | z) of this lane's particle; y the observation (DY values in LDS,
+  // 16-byte aligned), added to -C z row by row.  All of the lane's rows are
+  // fetched before the first is used, and the likelihood's form is chosen
+  // once: a load and a branch per row cost 32 exposed memory latencies per
+  // particle and pass, a quarter of the kernel.
   __device__ __forceinline__ float logpy(Prm P, const float* y) const {
     const int half = (threadIdx.x >> 5) & 1;
-    float s0 = 0.f, s1 = 0.f;
+    float4 y4[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float yi = y[8 * (r >> 2) + 4 * half + (r & 3)];
-      s0 += Mdl::row_term(P, yi + d0[r]);
-      s1 += Mdl::row_term(P, yi + d1[r]);
+    for (int q = 0; q < 4; ++q) y4[q] = reinterpret_cast<const float4*>(y)[2 * q + half];
+    float s0 = 0.f, s1 = 0.f;
+    auto rows = [&](auto&& term) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float4 v = y4[r >> 2];
+        const float yi = (r & 3) == 0 ? v.x : (r & 3) == 1 ? v.y : (r & 3) == 2 ? v.z : v.w;
+        s0 += term(yi + d0[r]);
+        s1 += term(yi + d1[r]);
+      }
+    };
+    if (P[Mdl::Layout::gonly] != 0.0f) {
+      rows([](float e) {
+        float e2 = e * e;
+        asm volatile("" : "+v"(e2));  // (a rounding of its own, not fused into the sum)
+        return e2;
+      });
+    } else {
+      rows([&](float e) { return Mdl::row_mix(P, e * e); });
     }
     const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
     return Mdl::logpy_sum(P, __uint_as_float(t[0]) + __uint_as_float(t[1]));
