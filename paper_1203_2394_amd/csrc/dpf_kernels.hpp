@@ -579,8 +579,10 @@ __device__ __forceinline__ void la_weights_tile(const StepArgs& a, int ti, bool 
       const int j = ls + r * SEG;
       const bool on = vi && j < M;
       float z[Mdl::DZ];
+      int Mr = __builtin_amdgcn_readfirstlane(M);  // opaque: DZ row bases kept over the items would spill
+      asm volatile("" : "+s"(Mr));
 #pragma unroll
-      for (int d = 0; d < Mdl::DZ; ++d) z[d] = on ? zrow[d * M + j] : 0.f;
+      for (int d = 0; d < Mdl::DZ; ++d) z[d] = on ? at32(zrow + d * Mr, j) : 0.f;
       const float lj = on ? lrow[j] : 0.f;
       const float g = la_logpy_wave<Mdl>(a, key, t, i, on ? j : 0, x, z, yrow, ca);
       if (on) {
@@ -2436,6 +2438,13 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     const int jj = ls + r * SEG;
     float lv = -INFINITY, gv = 0.f;
     if constexpr (kStream) {
+      // Bound by the vector units: at N = 16384, M = 1024, DZ = 64 vector
+      // instructions fill some 3 of a step's 3.5 ms (two generators, 132 normals
+      // and two mixtures of 32 terms a particle), FP32 matrix products 1 ms,
+      // mostly under them.  A run of 4 steps with its export takes 18.5 ms; 22.0
+      // when the rows came as single scalars, y and the likelihood's form were
+      // looked up term by term and each pair of components was stored under a
+      // mask of its own and by 64-bit addresses.
       const bool on = vk && jj < M;
       int b;
       if constexpr (kRoll) {
@@ -2447,8 +2456,10 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
         b = anc2[kRoll ? 0 : r];
       }
       float zg[DZ], zn[DZ];
+      int Mr = __builtin_amdgcn_readfirstlane(M);  // opaque: 2 DZ row bases kept over the items would spill
+      asm volatile("" : "+s"(Mr));
 #pragma unroll
-      for (int d = 0; d < DZ; ++d) zg[d] = on ? zp[d * M + b] : 0.f;
+      for (int d = 0; d < DZ; ++d) zg[d] = on ? at32(zp + d * Mr, b) : 0.f;
       const Prm P = as_prm(a.prm);
       WaveProj<Mdl> pj;
       pj.start();
@@ -2460,12 +2471,12 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
                                    if (d + 2 < DZ) nxt = Mdl::load_pair(P, d / 2 + 1);
                                    zn[d] = Mdl::fz_post_row(row, 0, sz, pre_at(d), zg, n0, d);
                                    zn[d + 1] = Mdl::fz_post_row(row, 1, sz, pre_at(d + 1), zg, n1, d + 1);
-                                   if (on) {
-                                     zdst[d * M + jj] = zn[d];
-                                     zdst[(d + 1) * M + jj] = zn[d + 1];
-                                   }
                                    if (!PLAIN) pj.add(ca[d / 2], zn[d], zn[d + 1]);
                                  });
+      if (on) {
+#pragma unroll
+        for (int d = 0; d < DZ; ++d) put32(zdst + d * Mr, jj, zn[d]);
+      }
       if constexpr (kKeepZ) {
 #pragma unroll
         for (int d = 0; d < DZ; ++d) zkeep[kKeepZ ? r : 0][d] = zn[d];
