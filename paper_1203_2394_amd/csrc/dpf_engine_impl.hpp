@@ -96,10 +96,21 @@ static void launch_narrow(int op, const StepArgs& a, int n, hipStream_t s) {
   }
 }
 
+// Row tiles per workgroup of k_mlp_fwd_state.  Two workgroups fit a CU, and
+// each fetches the whole network (156 KB): past 512 of them the next round
+// starts over, so larger batches take more rows per workgroup.  One, two and
+// four tiles: 11.0, 11.2, 16.0 us at 8192 rows; 15.5, 14.8, 16.4 at 12288;
+// 19.2, 15.7, 16.6 at 16384; 34.1, 26.0, 23.5 at 32768.
+constexpr int mlp_row_tiles(int rows) { return rows <= 8192 ? 1 : rows <= 16384 ? 2 : 4; }
+
 template <class Mdl>
 static dpf_status engine_mlp_state(const StepArgs& a, hipStream_t s) {
   if constexpr (learned_model<Mdl>()) {
-    hipLaunchKernelGGL(k_mlp_fwd_state<Mdl>, dim3((a.NT + kMlpRows - 1) / kMlpRows), dim3(kBlock), 0, s, a);
+    const int rt = mlp_row_tiles(a.NT), rows = kMlpRows * rt;
+    const dim3 n((a.NT + rows - 1) / rows);
+    if (rt == 4) hipLaunchKernelGGL((k_mlp_fwd_state<Mdl, 4>), n, dim3(kBlock), 0, s, a);
+    else if (rt == 2) hipLaunchKernelGGL((k_mlp_fwd_state<Mdl, 2>), n, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_mlp_fwd_state<Mdl, 1>), n, dim3(kBlock), 0, s, a);
     LAUNCH_CHECK("k_mlp_fwd_state");
     return DPF_OK;
   } else {

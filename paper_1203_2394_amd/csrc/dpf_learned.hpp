@@ -110,68 +110,72 @@ __device__ __forceinline__ void mdn_propose(const StepArgs& a, int f, int g, con
   a.sel[g] = comp;
 }
 
-// Network on the current state of every stepping filter: one 16-row tile of
+// Network on the current state of every stepping filter: RT 16-row tiles of
 // outer particles per workgroup; rows of filters that sit the step out get
 // zero features (their outputs are not used).  The epilogue draws each
-// row's proposal from its mixture.
-template <class Mdl>
-__global__ __launch_bounds__(kBlock) void k_mlp_fwd_state(StepArgs a) {
-  constexpr int NF = Mdl::DX + Mdl::DY + 2 * Mdl::DZ;
-  static_assert(NF <= kMlpIn, "features do not fit the input layer");
-  __shared__ MlpShared sh;
-  MlpFrags<4> fr;
-  mlp_load_blob<4, true>(a.mlp, fr);
-  const int row0 = blockIdx.x * kMlpRows;
-  const int nrows = min(kMlpRows, a.NT - row0);
-  const float* fmean = reinterpret_cast<const float*>(a.mlp + MlpBlobLayout::fmean);
-  const float* fstd = reinterpret_cast<const float*>(a.mlp + MlpBlobLayout::fstd);
-  // The tile's features, two per thread: column c of row g is
-  // [x_{t-1} (DX), y_t (DY), cloud mean (DZ), cloud variance (DZ)][c],
-  // standardised.  Every load is issued at a clamped (in-range) index before
-  // any value is used and the results are masked afterwards: a load guarded
-  // by a branch would wait inside it, one memory round per guard.
-  static_assert(kMlpRows * kMlpIn == 2 * kBlock, "two features per thread");
+// row's proposal from its mixture.  Bound by the GELUs' vector instructions
+// (11 us at 32768 rows) and a fixed 8 us of launch, features, weights and
+// draws: 23.5 us there, 42 with 16 rows per workgroup (four rounds, each
+// fetching the network again), a filter search per feature, the rounding to
+// BF16 by integer arithmetic and one LDS write per element.
+template <class Mdl, int RT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_fwd_state(StepArgs a) {
   constexpr int DX = Mdl::DX, DY = Mdl::DY, DZ = Mdl::DZ;
-  float fv[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int e = threadIdx.x + q * kBlock;
-    const int r = e / kMlpIn, c = e % kMlpIn;
-    const int g = row0 + min(r, nrows - 1);
-    const int f = filter_of_outer(a.ooff, a.n_filters, g);
-    const int cc = min(c, NF - 1);
+  constexpr int NF = DX + DY + 2 * DZ;
+  constexpr int R = kMlpRows * RT;  // rows of the workgroup
+  static_assert(NF <= kMlpIn && R <= kBlock, "features fit the input layer, a thread per row");
+  __shared__ MlpTiles<RT> sh;
+  __shared__ int4 row_sh[R];  // filter, state copy, observation row, stepping
+  const int row0 = blockIdx.x * R;
+  const int nrows = min(R, a.NT - row0);
+  if (threadIdx.x < R) {
+    const int f = filter_of_outer(a.ooff, a.n_filters, row0 + min((int)threadIdx.x, nrows - 1));
     const int am = a.active != nullptr ? a.active[f] : 1;
     const int tf = a.run_Tf != nullptr ? a.run_Tf[f] : 0x7fffffff;
     const int tc = a.tcur[f];
     const unsigned char cu = a.cur[f];
-    const float mu = fmean[cc], sd = fstd[cc];
-    const float* px = a.x[copy_of(cu)] + (long long)min(cc, DX - 1) * a.NT + g;
     // (a run's observation row, clamped: a filter past its horizon reads row
     // run_T - 1 and masks it)
-    const int ty = a.y_tstride != 0 ? min(tc, a.run_T - 1) : 0;
-    const float* py = a.Y + (long long)ty * a.y_tstride + (long long)f * DY + min(max(cc - DX, 0), DY - 1);
+    row_sh[threadIdx.x] = make_int4(f, copy_of(cu), a.y_tstride != 0 ? min(tc, a.run_T - 1) : 0,
+                                    am != 0 && tc < min(tf, a.run_T));
+  }
+  __syncthreads();
+  // The tile's features, two per thread and row tile: column c of row g is
+  // [x_{t-1} (DX), y_t (DY), cloud mean (DZ), cloud variance (DZ)][c],
+  // standardised.  Every load is issued at a clamped (in-range) index before
+  // any value is used and the results are masked afterwards: a load guarded
+  // by a branch would wait inside it, one memory round per guard.
+  static_assert(kMlpRows * kMlpIn == 2 * kBlock, "two features per thread and row tile");
+  const float* fmean = reinterpret_cast<const float*>(a.mlp + MlpBlobLayout::fmean);
+  const float* fstd = reinterpret_cast<const float*>(a.mlp + MlpBlobLayout::fstd);
+  const int c = threadIdx.x % kMlpIn, cc = min(c, NF - 1);
+  const float mu = fmean[cc], sd = fstd[cc];
+  float fv[2 * RT];
+#pragma unroll
+  for (int q = 0; q < 2 * RT; ++q) {
+    const int r = (threadIdx.x + q * kBlock) / kMlpIn;
+    const int g = row0 + min(r, nrows - 1);
+    const int4 ri = row_sh[r];
+    const float* px = a.x[ri.y] + (long long)min(cc, DX - 1) * a.NT + g;
+    const float* py = a.Y + (long long)ri.z * a.y_tstride + (long long)ri.x * DY + min(max(cc - DX, 0), DY - 1);
     const float* pm = a.mom + (long long)g * 2 * DZ + min(max(cc - DX - DY, 0), 2 * DZ - 1);
-    const float raw = *(cc < DX ? px : (cc < DX + DY ? py : pm));
-    const bool act = am != 0 && tc < min(tf, a.run_T);
-    fv[q] = (r < nrows && c < NF && act) ? (raw - mu) / sd : 0.f;
+    fv[q] = *(cc < DX ? px : (cc < DX + DY ? py : pm));
   }
+  MlpFrags<4> fr;
+  mlp_load_blob<4, true>(a.mlp, fr);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int e = threadIdx.x + q * kBlock;
-    sh.x0[e / kMlpIn][e % kMlpIn] = f2bf(fv[q]);
+  for (int q = 0; q < 2 * RT; ++q) {
+    const int r = (threadIdx.x + q * kBlock) / kMlpIn;
+    sh.x0[r][c] = f2bf((r < nrows && c < NF && row_sh[r].w) ? (fv[q] - mu) / sd : 0.f);
   }
   __syncthreads();
-  mlp_rows(fr, sh, row0, nrows, a.mdn);
+  mlp_tiles<RT>(fr, a.mlp, sh, row0, nrows, a.mdn);
   __syncthreads();
-  if (threadIdx.x < nrows) {
-    const int g = row0 + threadIdx.x;
-    const int f = filter_of_outer(a.ooff, a.n_filters, g);
-    if (step_active(a, f)) {
-      float o[Mdn<Mdl::DX>::kUsed];
+  if (threadIdx.x < nrows && row_sh[threadIdx.x].w) {
+    float o[Mdn<Mdl::DX>::kUsed];
 #pragma unroll
-      for (int c = 0; c < Mdn<Mdl::DX>::kUsed; ++c) o[c] = sh.o[threadIdx.x][c];
-      mdn_propose<Mdl::DX>(a, f, g, o);
-    }
+    for (int q = 0; q < Mdn<Mdl::DX>::kUsed; ++q) o[q] = sh.o[threadIdx.x][q];
+    mdn_propose<Mdl::DX>(a, row_sh[threadIdx.x].x, row0 + threadIdx.x, o);
   }
 }
 

@@ -63,13 +63,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short bf16_t;
 
-// Round to nearest even; NaN stays NaN.
-__device__ __forceinline__ bf16_t f2bf(float v) {
-  uint32_t u = __float_as_uint(v);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
+// Round to nearest even; NaN stays NaN (the card's own conversion; by integer
+// arithmetic it was a third of a hidden layer's vector instructions).
+__device__ __forceinline__ bf16_t f2bf(float v) { return __builtin_bit_cast(bf16_t, (__bf16)v); }
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 __device__ __forceinline__ bf16x8 ld8(const bf16_t* p) {
@@ -260,6 +256,93 @@ __device__ __forceinline__ void mlp_rows(const MlpFrags<NT>& fr, MlpShared& sh, 
   mlp_hidden<NT, kMlpHid, kHidStride, false>(sh.h1, fr.w2, fr.b2, sh.h2);
   __syncthreads();
   mlp_out_layer(fr, sh, row0, nrows, out);
+}
+
+// The same for RT row tiles at once (4 waves): one buffer for both hidden
+// layers, each read whole before its successor is written.
+template <int RT>
+struct alignas(16) MlpTiles {
+  bf16_t x0[16 * RT][kInStride];
+  bf16_t h[16 * RT][kHidStride];
+  float part[2][16 * RT][16];
+  float o[16 * RT][kMlpOut + 1];
+};
+template <int RT, int KIN, int SIN>
+__device__ __forceinline__ void mlp_hidden_tiles(const bf16_t (*in)[SIN], const bf16x8 (*wf)[4], const f32x4* bias,
+                                                 bf16_t (*out)[kHidStride]) {
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lr = l & 15, lk = 8 * (l >> 4);
+  // (weights as the A operand: a lane's four D elements are consecutive
+  // columns of one row, an 8-byte store)
+  f32x4 acc[RT][4];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) acc[rt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int ks = 0; ks < KIN / 32; ++ks) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const bf16x8 a = ld8(&in[16 * rt + lr][32 * ks + lk]);
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) acc[rt][nt] = mfma16(wf[ks][nt], a, acc[rt][nt]);
+    }
+  }
+  __syncthreads();  // in may be out
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      bf16_t h[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h[r] = f2bf(gelu_f(acc[rt][nt][r] + bias[nt][r]));
+      store_rows4(&out[16 * rt + lr][16 * (4 * w + nt) + 4 * (l >> 4)], h);
+    }
+  }
+  __syncthreads();
+}
+template <int RT>
+__device__ __forceinline__ void mlp_tiles(const MlpFrags<4>& fr, const unsigned char* blob, MlpTiles<RT>& sh, int row0,
+                                          int nrows, float* out) {
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  f32x4 b1[4], b2[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const int n = 16 * (4 * w + nt) + 4 * (l >> 4);
+    b1[nt] = *reinterpret_cast<const f32x4*>(blob + MlpBlobLayout::b1 + 4 * n);
+    b2[nt] = *reinterpret_cast<const f32x4*>(blob + MlpBlobLayout::b2 + 4 * n);
+  }
+  mlp_hidden_tiles<RT, kMlpIn, kInStride>(sh.x0, fr.w1, b1, sh.h);
+  mlp_hidden_tiles<RT, kMlpHid, kHidStride>(sh.h, fr.w2, b2, sh.h);
+  const int lr = l & 15, lk = 8 * (l >> 4);
+  const int nt = w & 1, kh = w >> 1;
+  f32x4 acc[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      acc[rt] = mfma16(ld8(&sh.h[16 * rt + lr][32 * (4 * kh + q) + lk]), fr.w3[q], acc[rt]);
+    if (kh == 1) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sh.part[nt][16 * rt + 4 * (l >> 4) + r][lr] = acc[rt][r];
+    }
+  }
+  __syncthreads();
+  if (kh == 0) {
+    const int n = 16 * nt + lr;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * rt + 4 * (l >> 4) + r;
+        const float v = (acc[rt][r] + sh.part[nt][row][lr]) + fr.b3;
+        sh.o[row][n] = v;
+        if (out && row < nrows) out[(size_t)(row0 + row) * kMlpOut + n] = v;
+      }
+    }
+  }
 }
 
 // Standardised FP32 features X [B][32] -> outputs [B][32].
@@ -473,7 +556,8 @@ __device__ __forceinline__ void mlp_back_layer(const bf16_t (*in)[SIN], const bf
     bf16_t h[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float v = acc[nt][r] * gelu_grad_f(a[nt][r]);
+      float v = acc[nt][r] * gelu_grad_f(a[nt][r]);
+      asm volatile("" : "+v"(v));  // the rounded product, not a fused sum
       cs += v;
       h[r] = f2bf(v);
       if (out) out[4 * (l >> 4) + r][n] = h[r];
