@@ -52,6 +52,26 @@ static __global__ void k_state_copy_x(float* ext, float* buf0, float* buf1, cons
     buf0[e] = ext[e];
 }
 
+// The estimates of a handle to up to five arrays of the caller, in one launch:
+// a step served by itself is bound by its launches, and five copies took
+// longer than the step's kernels.  Words of 4 bytes (nothing is asked of the
+// arrays beyond what their types ask).
+constexpr int kEstArrays = 5;
+struct EstCopy {
+  uint32_t* dst[kEstArrays];
+  const uint32_t* src[kEstArrays];
+  long long end[kEstArrays];  // words of this array and those before it
+};
+static __global__ __launch_bounds__(kBlock) void k_estimate_copy(EstCopy e) {
+  const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
+  long long first = 0;
+#pragma unroll
+  for (int q = 0; q < kEstArrays; ++q) {
+    if (i >= first && i < e.end[q]) e.dst[q][i - first] = e.src[q][i - first];
+    first = e.end[q];
+  }
+}
+
 // ---- state export and import: one launch
 // The external state is [t (F words, padded to tb bytes)][x][z][lam] in the
 // layouts of the workspace.  Workgroup (b, y) moves the y-th of gridDim.y

@@ -883,19 +883,44 @@ extern "C" dpf_status dpf_features(dpf_handle* h, const float* d_y, float* d_fea
   return queue_moments(h, d_y, d_feat);
 }
 
+// Whether p is memory that a kernel on this device can write (device, managed
+// or pinned); anything else is left to the runtime's copy.
+static bool kernel_may_write(const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  return at.devicePointer == p && (at.type != hipMemoryTypeDevice || at.device == dev);
+}
+
 extern "C" dpf_status dpf_estimate(dpf_handle* h, float* d_xmean, float* d_zmean, float* d_ess,
                                    double* d_loglik, uint32_t* d_flags) {
   if (!h) return fail(DPF_EINVAL, "handle is NULL");
-  const int F = h->F;
-  if (d_xmean)
-    HIP_TRY(hipMemcpyAsync(d_xmean, h->ws + h->L.est_x, (size_t)F * h->dx * 4, hipMemcpyDeviceToDevice, h->stream));
-  if (d_zmean)
-    HIP_TRY(hipMemcpyAsync(d_zmean, h->ws + h->L.est_z, (size_t)F * h->dz * 4, hipMemcpyDeviceToDevice, h->stream));
-  if (d_ess) HIP_TRY(hipMemcpyAsync(d_ess, h->ws + h->L.ess, (size_t)F * 4, hipMemcpyDeviceToDevice, h->stream));
-  if (d_loglik)
-    HIP_TRY(hipMemcpyAsync(d_loglik, h->ws + h->L.loglik, (size_t)F * 8, hipMemcpyDeviceToDevice, h->stream));
-  if (d_flags)
-    HIP_TRY(hipMemcpyAsync(d_flags, h->ws + h->L.flags, (size_t)F * 4, hipMemcpyDeviceToDevice, h->stream));
+  const size_t F = h->F;
+  void* const dst[kEstArrays] = {d_xmean, d_zmean, d_ess, d_loglik, d_flags};
+  const char* const src[kEstArrays] = {h->ws + h->L.est_x, h->ws + h->L.est_z, h->ws + h->L.ess, h->ws + h->L.loglik,
+                                       h->ws + h->L.flags};
+  const size_t words[kEstArrays] = {F * h->dx, F * h->dz, F, 2 * F, F};
+  EstCopy e;
+  long long n = 0;
+  bool kernel = true;
+  for (int q = 0; q < kEstArrays; ++q) {
+    e.dst[q] = (uint32_t*)dst[q];
+    e.src[q] = (const uint32_t*)src[q];
+    e.end[q] = n += dst[q] ? (long long)words[q] : 0;
+    kernel = kernel && (!dst[q] || kernel_may_write(dst[q]));
+  }
+  if (kernel) {
+    if (n == 0) return DPF_OK;
+    hipLaunchKernelGGL(k_estimate_copy, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, h->stream, e);
+    LAUNCH_CHECK("k_estimate_copy");
+    return DPF_OK;
+  }
+  for (int q = 0; q < kEstArrays; ++q)
+    if (dst[q]) HIP_TRY(hipMemcpyAsync(dst[q], src[q], words[q] * 4, hipMemcpyDeviceToDevice, h->stream));
   return DPF_OK;
 }
 
