@@ -128,6 +128,7 @@ struct StepArgs {
   const int2* rgroups;  // (filter, group) of each resampling workgroup
   const int4* ginfo;    // per resampling group: its filter's (first outer index, N, first group, groups)
   int n_commit;         // learned-step commit workgroups at the head of the launch
+  int later_step;       // nested run: a step after its first
   int n_comp;           // companions per look-ahead candidate (nested estimator; 0: paired)
   // predicted observation (models with a one-dimensional y), or null: per
   // outer particle sum_j qbar h(xla, zla) of this step's look-ahead draws
@@ -663,7 +664,9 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
   asm volatile("" ::"v"(am), "v"(tf));
   const FilterView fv = load_filter(a, f);
   const bool act = am != 0 && fv.t < min(tf, a.run_T);  // step_active
-  if (tile.z == 0 && threadIdx.x == 0) a.act[f] = act ? 1 : 0;
+  // (in a run, bit 1 is the previous step's new-cloud kernel's)
+  if (tile.z == 0 && threadIdx.x == 0)
+    a.act[f] = (unsigned char)((act ? 1 : 0) | (a.later_step ? a.act[f] & 2 : 0));
   if (!act) return;
   const int N = fv.N, M = fv.M, K = a.n_comp;
   constexpr int CPB = comp_per_block<DZ>();  // companions per block of normals

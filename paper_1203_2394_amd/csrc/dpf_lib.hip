@@ -625,7 +625,7 @@ static dpf_status queue_plain_step(dpf_handle* h, StepArgs a) {
 
 // One step.  fuse (look-ahead runs only): 0 a step on its own; 1 the first
 // step of a run; 2 a later one (its weights were computed by the previous
-// step's new-cloud kernel).  In a run, par alternates: the view, weight and
+// step's new-cloud kernel; nested weights are launched each step).  In a run, par alternates: the view, weight and
 // kpart buffers this step reads (it writes the other view and the next
 // step's weights to the other pair); last: the run's last step.
 //
@@ -650,7 +650,8 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
   a.trace_x = trace_x;
   a.trace_z = trace_z;
   a.advance = 1;
-  h->ell_sel = fuse ? par : 0;
+  const bool nested = h->n_comp > 0;  // (every step launches its weights)
+  h->ell_sel = fuse && !nested ? par : 0;
   if (h->algo == DPF_ALGO_PLAIN) return queue_plain_step(h, a);
   const bool many = many_groups(h) && !h->one_group;
   a.rgroups = at<int2>(h, h->L.rgroups);
@@ -658,23 +659,26 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
     float* e[2] = {at<float>(h, h->L.ell), at<float>(h, h->L.ell1)};
     float* w[2] = {at<float>(h, h->L.logw), at<float>(h, h->L.logw1)};
     float* k[2] = {at<float>(h, h->L.kpart), at<float>(h, h->L.kpart1)};
-    a.ell = e[par];
-    a.logw = w[par];
-    a.ell_next = e[par ^ 1];
-    a.logw_next = w[par ^ 1];
+    if (!nested) {
+      a.ell = e[par];
+      a.logw = w[par];
+      a.ell_next = e[par ^ 1];
+      a.logw_next = w[par ^ 1];
+    }
     a.kpart = k[par];
     a.kpart_prev = k[par ^ 1];
   }
   if (h->predict) {
     float* yb[2] = {at<float>(h, h->L.yp0), at<float>(h, h->L.yp1)};
-    a.yp = yb[fuse ? par : 0];
-    a.yp_next = fuse ? yb[par ^ 1] : nullptr;
+    a.yp = yb[fuse && !nested ? par : 0];
+    a.yp_next = fuse && !nested ? yb[par ^ 1] : nullptr;
     a.trace_y = h->ytrace;
   }
   const int view = fuse ? par : 0;
   set_view(h, a, view);
   dpf_status s = phase_mark(h, 0);
-  if (s == DPF_OK && fuse != 2) s = launch_classes(h, h->n_comp > 0 ? OP_LA_WEIGHTS_NESTED : OP_LA_WEIGHTS, a);
+  a.later_step = nested && fuse == 2 ? 1 : 0;
+  if (s == DPF_OK && (fuse != 2 || nested)) s = launch_classes(h, nested ? OP_LA_WEIGHTS_NESTED : OP_LA_WEIGHTS, a);
   if (s == DPF_OK) s = phase_mark(h, 1);
   if (s == DPF_OK && fuse != 2 && !h->one_group) {
     hipLaunchKernelGGL(k_res_stats, dim3(h->L.n_rgroups), dim3(kBlock), 0, h->stream, a,
@@ -930,9 +934,11 @@ static dpf_status queue_run_step(dpf_handle* h, int mode, const float* d_Y, int 
                                  float* xt, float* zt, int q) {
   const long long stride = (long long)h->F * h->dy;
   if (mode == 1) return queue_learned_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt, nullptr);
-  // (the fused next-step weights are the paired form: a nested run takes
-  // every step whole)
-  if (h->algo == DPF_ALGO_LOOKAHEAD && T > 1 && h->n_comp == 0)
+  // (the fused next-step weights are the paired form: a nested run launches
+  // its weights each step, and takes the rest of the run's form where that
+  // needs no weights of the next step: every filter of one group; 86 us per
+  // step of 256 filters of 200 x 20 with k_post and k_post_end, 79 so)
+  if (h->algo == DPF_ALGO_LOOKAHEAD && T > 1 && (h->n_comp == 0 || h->one_group))
     return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt, q == 0 ? 1 : 2, q & 1, q == T - 1);
   return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt);
 }
