@@ -111,6 +111,7 @@ struct Engine {
                      hipStream_t s);
   bool yhat;  // the look-ahead pass can form the predicted observation
   bool narrow;  // the narrow classes are built
+  bool plain_fused;  // a plain run's new-cloud kernel computes the next step's weights
 };
 
 extern const Engine kEngLinGauss, kEngNonLin, kEngHighDim, kEngTwoDim, kEngFourDim, kEngTwoDimZ;

@@ -188,7 +188,7 @@ static dpf_status engine_rb(const StepArgs& a, double* tmp, float* out, hipStrea
 template <class Mdl>
 static dpf_status engine_finalize(const StepArgs& a, int F, hipStream_t s) {
   constexpr int DX = Mdl::DX, DZ = Mdl::DZ;
-  hipLaunchKernelGGL((k_finalize<DX, DZ, true>), dim3(F), dim3(fin_block<DX, DZ>()), 0, s, a);
+  hipLaunchKernelGGL((k_finalize<DX, DZ>), dim3(F), dim3(fin_block<DX, DZ>()), 0, s, a);
   LAUNCH_CHECK("k_finalize");
   return DPF_OK;
 }
@@ -245,7 +245,8 @@ static Engine make_engine(void (*derive)(const double*, std::vector<float>&)) {
                 engine_finalize<Mdl>,
                 engine_post<Mdl>,
                 has_yhat<Mdl>(),
-                narrow_model<Mdl>()};
+                narrow_model<Mdl>(),
+                !Mdl::kStreamZ};
 }
 
 }  // namespace dpf

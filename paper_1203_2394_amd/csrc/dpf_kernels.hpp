@@ -53,6 +53,15 @@ constexpr bool has_moments() { return Mdl::DX + Mdl::DY + 2 * Mdl::DZ <= kFeatMa
 template <class Mdl>
 constexpr bool has_yhat() { return Mdl::DY == 1; }
 
+// obs_pre as the plain weights form it, in their kernel and in a run's
+// new-cloud kernel (a model of several observed components writes its
+// roundings out; one component leaves the compiler no choice).
+template <class Mdl>
+__device__ __forceinline__ void obs_pre_weights(Prm P, const float* y, const float* x, float* r0) {
+  if constexpr (Mdl::DY > 1 && !Mdl::kStreamZ) Mdl::obs_pre_plain(P, y, x, r0);
+  else Mdl::obs_pre(P, y, x, r0);
+}
+
 // Number of z-free terms of log p(x' | x, z) (px_pre); 1 for models whose
 // transition of x ignores z (unused there).
 template <class Mdl>
@@ -1068,7 +1077,7 @@ static __global__ __launch_bounds__(kBlock) void k_dpf_weights(StepArgs a) {
   load_y<Mdl>(a, f, t, y);
 #pragma unroll
   for (int d = 0; d < Mdl::DX; ++d) x[d] = vi ? a.x[src][(long long)d * a.NT + oo + i] : 0.f;
-  Mdl::obs_pre(as_prm(a.prm), y, x, r0);
+  obs_pre_weights<Mdl>(as_prm(a.prm), y, x, r0);
   const float* zrow = a.z[src] + (io + (long long)(vi ? i : 0) * M) * Mdl::DZ;
   float* erow = a.ell + io + (long long)(vi ? i : 0) * M;
   float ev[JPT];
@@ -1701,66 +1710,124 @@ __device__ void commit_group(const StepArgs& a, int b) {
   }
 }
 
+// Estimate q of filter f (x's components, z's, then yhat) of the step that
+// ended at time t.
+template <int DX, int DZ>
+__device__ __forceinline__ void est_store(const StepArgs& a, int f, int t, int q, double e) {
+  if (q < DX) {
+    a.est_x[f * DX + q] = (float)e;
+    if (a.trace_x) a.trace_x[((long long)(t - 1) * a.n_filters + f) * DX + q] = (float)e;
+  } else if (q < DX + DZ) {
+    a.est_z[f * DZ + q - DX] = (float)e;
+    if (a.trace_z) a.trace_z[((long long)(t - 1) * a.n_filters + f) * DZ + q - DX] = (float)e;
+  } else {
+    a.est_y[f] = (float)e;
+    if (a.trace_y) a.trace_y[(long long)(t - 1) * a.n_filters + f] = (float)e;
+  }
+}
+
 // ---------------------------------------------------------------- estimates
-// One workgroup per filter, FP64 sums in a fixed order (strided per thread,
-// then DPP and the wave results in order), so results are reproducible.
-// Used by the plain DPF (the look-ahead steps end with k_post):
-//   plain:      xhat = sum_i Wbar_i xt_i, zhat = sum_i Wbar_i sum_j qbar z
-//               over the proposals weighted at this step (previous copy)
+// Estimates of a plain step, xhat = sum_i Wbar_i xt_i and zhat = sum_i Wbar_i
+// sum_j qbar z over the proposals weighted at this step (copy xs; their sums
+// kp), one workgroup of RB threads per filter: FP64 sums in a fixed order (BS
+// threads' strided sums, then DPP and the wave results in order; a smaller
+// workgroup takes several of the threads each), so results are reproducible
+// and do not depend on the launch.  m, total, deg: of the outer weights.
 template <int DX, int DZ>
 constexpr int fin_block() { return DX + DZ > 16 ? 256 : 1024; }
 
-template <int DX, int DZ, bool PLAIN>
-static __global__ __launch_bounds__((fin_block<DX, DZ>())) void k_finalize(StepArgs a) {
+template <int DX, int DZ, int RB>
+__device__ __forceinline__ void finalize_filter(const StepArgs& a, int f, int N, int oo, int t, const float* xs,
+                                                const float* kp, double m, double total, bool deg) {
   constexpr int NV = DX + DZ;
   constexpr int BS = fin_block<DX, DZ>();
   __shared__ double red[NV][BS / kWave];
-  const int f = blockIdx.x;
-  if (!a.act[f]) return;
-  const int N = a.fN[f];
-  const int oo = a.ooff[f];
-  const int t = a.tcur[f];
-  const float* xs = a.x[PLAIN ? copy_of(a.cur[f]) ^ 1 : copy_of(a.cur[f])];
-  double mx = 0.0, tot = 1.0;
-  bool deg = false;
-  if (PLAIN) {
-    mx = a.fstat[4 * f + 0];
-    tot = a.fstat[4 * f + 1];
-    deg = a.fstat[4 * f + 3] != 0.0;
-  }
-  double acc[NV];
+  for (int v0 = 0; v0 < BS; v0 += RB) {
+    double acc[NV];
 #pragma unroll
-  for (int q = 0; q < NV; ++q) acc[q] = 0.0;
-  // unrolled so that the loads of several particles are in flight together
-  // (same summation order as the plain loop)
-#pragma unroll 4
-  for (int i = threadIdx.x; i < N; i += BS) {
-    double w;
-    if (PLAIN) {
+    for (int q = 0; q < NV; ++q) acc[q] = 0.0;
+    // unrolled so that the loads of several particles are in flight together
+    // (same summation order as the plain loop; head workgroups less: their
+    // registers are those of the new-cloud kernel)
+#pragma unroll RB < BS ? 2 : 4
+    for (int i = v0 + threadIdx.x; i < N; i += BS) {
       const float lw = a.logw[oo + i];
-      w = deg ? 1.0 / N : (finitef(lw) ? (double)fast_exp(lw - (float)mx) / tot : 0.0);
-    } else {
-      w = 1.0 / N;
+      const double w = deg ? 1.0 / N : (finitef(lw) ? (double)fast_exp(lw - (float)m) / total : 0.0);
+      for (int d = 0; d < DX; ++d) acc[d] += w * (double)xs[(long long)d * a.NT + oo + i];
+      for (int d = 0; d < DZ; ++d) acc[DX + d] += w * (double)kp[(long long)(oo + i) * DZ + d];
     }
-    for (int d = 0; d < DX; ++d) acc[d] += w * (double)xs[(long long)d * a.NT + oo + i];
-    for (int d = 0; d < DZ; ++d) acc[DX + d] += w * (double)a.kpart[(long long)(oo + i) * DZ + d];
-  }
-  for (int q = 0; q < NV; ++q) {
-    const double v = seg_reduce_wave<OpAdd, kWave>(acc[q]);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[q][threadIdx.x / kWave] = v;
+    for (int q = 0; q < NV; ++q) {
+      const double v = v0 < N ? seg_reduce_wave<OpAdd, kWave>(acc[q]) : 0.0;
+      if ((threadIdx.x & (kWave - 1)) == 0) red[q][(v0 + threadIdx.x) / kWave] = v;
+    }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < NV; q += BS) {
+  for (int q = threadIdx.x; q < NV; q += RB) {
     double v = 0.0;
     for (int w = 0; w < BS / kWave; ++w) v += red[q][w];
-    if (q < DX) {
-      a.est_x[f * DX + q] = (float)v;
-      if (a.trace_x) a.trace_x[((long long)(t - 1) * a.n_filters + f) * DX + q] = (float)v;
-    } else {
-      a.est_z[f * DZ + q - DX] = (float)v;
-      if (a.trace_z) a.trace_z[((long long)(t - 1) * a.n_filters + f) * DZ + q - DX] = (float)v;
-    }
+    est_store<DX, DZ>(a, f, t, q, v);
   }
+}
+
+// Of a step on its own, after its new-cloud kernel.
+template <int DX, int DZ>
+static __global__ __launch_bounds__((fin_block<DX, DZ>())) void k_finalize(StepArgs a) {
+  const int f = blockIdx.x;
+  if (!a.act[f]) return;
+  finalize_filter<DX, DZ, fin_block<DX, DZ>()>(a, f, a.fN[f], a.ooff[f], a.tcur[f], a.x[copy_of(a.cur[f]) ^ 1],
+                                               a.kpart, a.fstat[4 * f + 0], a.fstat[4 * f + 1],
+                                               a.fstat[4 * f + 3] != 0.0);
+}
+
+// Shift and total of resolve_points, in its arithmetic and order.
+static __device__ ResResult res_total(int n, const double* gstat, int G) {
+  __shared__ double red4[kBlock / kWave], tot;
+  __shared__ float fred4[kBlock / kWave];
+  const int th = threadIdx.x, thc = min(th, G - 1);
+  const double g0 = gstat[4 * thc], g1 = gstat[4 * thc + 1];
+  const float gm = th < G ? (float)g0 : -INFINITY;
+  ResResult r;
+  const float m = block_max_256(gm, fred4);
+  r.deg = !(m > -INFINITY);
+  r.m = r.deg ? 0.f : m;
+  const double T = th >= G ? 0.0 : r.deg ? (double)min(kResGroup, n - th * kResGroup) : group_scale<LogSrc>(gm, m) * g1;
+  const double B = block_scan_incl_256(T, red4);
+  if (th == G - 1) tot = B;
+  __syncthreads();
+  r.total = tot;
+  r.sumsq = 0.0;
+  r.nonf = false;
+  return r;
+}
+
+// Head workgroup of a plain run's new-cloud launch: filter f's estimates of
+// the step being taken (its weights, sums and state copy are the previous
+// launch's; this one writes the other buffers).  The weights' total is formed
+// as the new-cloud workgroups form it.
+template <int DX, int DZ>
+__device__ __forceinline__ void est_head_plain(const StepArgs& a, int f) {
+  const int act = a.act[f], t = a.tcur[f], N = a.fN[f], oo = a.ooff[f], cu = a.cur[f];
+  const FilterInfo fi = a.finfo[f];
+  asm volatile("" ::"v"(act), "v"(t), "v"(N), "v"(oo), "v"(cu));
+  if (!(act & 1)) return;
+  ResResult rr;
+  if (fi.ngroup == 1) {
+    double C[4];
+    rr = self_cdf(a.logw + oo, N, false, C);
+  } else {
+    rr = res_total(N, a.gstat + 4LL * fi.rg_base, fi.ngroup);
+  }
+  finalize_filter<DX, DZ, kBlock>(a, f, N, oo, t + 1, a.x[copy_of((unsigned char)cu)], a.kpart_prev,
+                                  rr.deg ? 0.0 : (double)rr.m, rr.total, rr.deg);
+}
+
+// A plain run of an odd number of steps ends in the other view.
+static __global__ __launch_bounds__(kBlock) void k_view_copy(StepArgs a) {
+  const int f = blockIdx.x * kBlock + threadIdx.x;
+  if (f >= a.n_filters) return;
+  a.tcur_n[f] = a.tcur[f];
+  a.cur_n[f] = a.cur[f];
+  a.act_n[f] = a.act[f];
 }
 
 // ------------------------------------------------------- look-ahead step end
@@ -1783,22 +1850,6 @@ __device__ __forceinline__ double est_partial(const double* v, double (*part)[NV
   __syncthreads();
   const int q = threadIdx.x;
   return q < NV ? ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q] : 0.0;
-}
-
-// Estimate q of filter f (x's components, z's, then yhat) of the step that
-// ended at time t.
-template <int DX, int DZ>
-__device__ __forceinline__ void est_store(const StepArgs& a, int f, int t, int q, double e) {
-  if (q < DX) {
-    a.est_x[f * DX + q] = (float)e;
-    if (a.trace_x) a.trace_x[((long long)(t - 1) * a.n_filters + f) * DX + q] = (float)e;
-  } else if (q < DX + DZ) {
-    a.est_z[f * DZ + q - DX] = (float)e;
-    if (a.trace_z) a.trace_z[((long long)(t - 1) * a.n_filters + f) * DZ + q - DX] = (float)e;
-  } else {
-    a.est_y[f] = (float)e;
-    if (a.trace_y) a.trace_y[(long long)(t - 1) * a.n_filters + f] = (float)e;
-  }
 }
 
 // Sum over the filter's groups of partial q (rows of gpart have NV values).
@@ -2042,7 +2093,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     gst[2] = gp[2];
   }
   // the next step's horizon (look-ahead run)
-  const int tf_next = (!PLAIN && a.ell_next != nullptr && a.run_Tf != nullptr) ? a.run_Tf[f] : 0x7fffffff;
+  const int tf_next = (a.ell_next != nullptr && a.run_Tf != nullptr) ? a.run_Tf[f] : 0x7fffffff;
   const FilterView fv = load_filter(a, f);
   // the view holds the filter's progress before the step (act_n given) or after
   const int before = a.act_n != nullptr ? 1 : 0;
@@ -2050,9 +2101,11 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   const bool act = fv.act & 1;
   const unsigned char cb = (unsigned char)(fv.cur ^ (act ? before : 0));
   const int dst = copy_of(cb), src = dst ^ 1;
-  // look-ahead run: this kernel also computes the next step's weights (Fig. 4
-  // steps 1-2 at t + 1) for the filters that take it; y_{t+1} fetched early
-  const bool next = !PLAIN && t < min(tf_next, a.run_T);
+  // run: this kernel also computes the next step's weights (Fig. 4 steps 1-2,
+  // or Fig. 2 step 1, at t + 1) for the filters that take it; y_{t+1} fetched
+  // early.  (The wide-z plain pass keeps its weights kernel.)
+  constexpr bool kPlainFuse = PLAIN && !kStream;
+  const bool next = (!PLAIN || kPlainFuse) && t < min(tf_next, a.run_T);
   const bool fuse = next && a.ell_next != nullptr;
   if (before && tile.z == 0 && threadIdx.x == 0) {
     // the view after the step (the new clouds are in slot order)
@@ -2064,7 +2117,12 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   // learned step with accepted proposals: committed by commit_group
   if (!PLAIN && fv.fb == 0) return;
   float yn[DY];
-  if (!PLAIN && a.ell_next != nullptr) load_y<Mdl>(a, f, min(t, a.run_T - 1) + 1, yn);
+  if ((!PLAIN || kPlainFuse) && a.ell_next != nullptr) {
+    load_y<Mdl>(a, f, min(t, a.run_T - 1) + 1, yn);
+  } else if (kPlainFuse) {
+#pragma unroll
+    for (int d = 0; d < DY; ++d) yn[d] = 0.f;
+  }
   const int N = fv.N, M = fv.M;
   const int s = SEG >= kWave ? __builtin_amdgcn_readfirstlane(threadIdx.x / SEG) : threadIdx.x / SEG;
   const int ls = threadIdx.x % SEG;
@@ -2416,6 +2474,19 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
     load_y<Mdl>(a, f, t, y);
     Mdl::obs_pre(as_prm(a.prm), y, xn, r0);
   }
+  if constexpr (kPlainFuse) {
+    // (opaque: nothing is shared with the propagation, whose bits, and the
+    // weights', are those of the kernels on their own)
+    float xo[DX];
+#pragma unroll
+    for (int d = 0; d < DX; ++d) {
+      xo[d] = xn[d];
+      asm volatile("" : "+v"(xo[d]));
+    }
+    // (not under `if (fuse)`: products in another block than their sums would
+    // stay unfused)
+    obs_pre_weights<Mdl>(as_prm(a.prm), yn, xo, r0);
+  }
   float* zdst = a.z[dst] + (io + (long long)k * M) * DZ;
   float llv[JPT], gn[JPT];
   float zkeep[kKeepZ ? JPT : 1][DZ];
@@ -2508,7 +2579,18 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       Mdl::fz_post(as_prm(a.prm), pre, zg, nu, zn);
 #pragma unroll
       for (int d = 0; d < DZ; ++d) put32(zdst + d * M, jj, zn[d]);
-      if (!PLAIN) lv = Mdl::logpy_post(as_prm(a.prm), r0, zn);
+      if (!PLAIN) {
+        lv = Mdl::logpy_post(as_prm(a.prm), r0, zn);
+      } else if (kPlainFuse && fuse) {
+        float zo[DZ];
+#pragma unroll
+        for (int d = 0; d < DZ; ++d) {
+          zo[d] = zn[d];
+          asm volatile("" : "+v"(zo[d]));
+        }
+        lv = Mdl::logpy_post(as_prm(a.prm), r0, zo);
+        acc.add(r, lv);
+      }
       if constexpr (kKeepZ) {
 #pragma unroll
         for (int d = 0; d < DZ; ++d) zkeep[kKeepZ ? r : 0][d] = zn[d];
@@ -2622,6 +2704,33 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
       }
     }
   }
+  if constexpr (kPlainFuse) {
+    // the next step's weights and weighted sums, as k_dpf_weights forms them
+    if (fuse) {
+      const float lse = acc.get(sh);
+      const bool degw = !(lse > -INFINITY);
+      if (degw) fl |= F_DEGENERATE_INNER;
+      float* en = a.ell_next + io + (long long)(vk ? k : 0) * M;
+      float part[DZ];
+#pragma unroll
+      for (int d = 0; d < DZ; ++d) part[d] = 0.f;
+#pragma unroll
+      for (int r = 0; r < JPT; ++r) {
+        const int jj = ls + r * SEG;
+        if (vk && jj < M) {
+          en[jj] = llv[r];
+          const float q = degw ? 1.0f / (float)M : (finitef(llv[r]) ? fast_exp(llv[r] - lse) : 0.f);
+#pragma unroll
+          for (int d = 0; d < DZ; ++d) part[d] += q * (kKeepZ ? zkeep[kKeepZ ? r : 0][d] : zdst[d * M + jj]);
+        }
+      }
+      float* kp = a.kpart + (long long)(oo + k) * DZ;
+      int slot;
+      const float tot = seg_sum_vec_t<SEG, DZ>(part, reinterpret_cast<float(*)[DZ]>(&vred[0][0]), slot);
+      if (vk && slot >= 0) kp[slot] = tot;
+      if (vk && ls == 0) a.logw_next[oo + k] = degw ? -INFINITY : lse - fast_log((float)M);
+    }
+  }
   if (vk && ls == 0 && fl) atomicOr(&a.flags[f], fl);
 }
 
@@ -2630,12 +2739,13 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
 // through one L2.
 template <class Mdl, int SEG, int JPT, bool PLAIN, int ORD = 0>
 static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<Mdl>()))) void k_newcloud(StepArgs a) {
-  if (!PLAIN && (int)blockIdx.x < a.n_head) {
-    est_head<Mdl::DX, Mdl::DZ, has_yhat<Mdl>()>(a, blockIdx.x);
+  if ((int)blockIdx.x < a.n_head) {
+    if constexpr (!PLAIN) est_head<Mdl::DX, Mdl::DZ, has_yhat<Mdl>()>(a, blockIdx.x);
+    else if constexpr (!Mdl::kStreamZ) est_head_plain<Mdl::DX, Mdl::DZ>(a, blockIdx.x);
     return;
   }
-  const int b = PLAIN ? (int)blockIdx.x : (int)blockIdx.x - a.n_head;
-  const int ti = Mdl::kStreamZ ? xcd_contiguous_tile(b, (int)gridDim.x - (PLAIN ? 0 : a.n_head)) : b;
+  const int b = (int)blockIdx.x - a.n_head;
+  const int ti = Mdl::kStreamZ ? xcd_contiguous_tile(b, (int)gridDim.x - a.n_head) : b;
   newcloud_tile<Mdl, SEG, JPT, PLAIN, ORD>(a, ti);
 }
 

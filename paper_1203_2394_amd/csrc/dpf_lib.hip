@@ -623,7 +623,49 @@ static dpf_status queue_plain_step(dpf_handle* h, StepArgs a) {
   return s;
 }
 
-// One step.  fuse (look-ahead runs only): 0 a step on its own; 1 the first
+// Step of a plain run (of several): the weights, and the outer statistics where
+// a filter has several groups, come before the new-cloud kernel, which also
+// forms the next step's weights and, by its head workgroups, the step's
+// estimates.  par alternates as in queue_step.  32 filters of 1000 x 100, the
+// 4-d model: 57 us per step as four launches, 43 so.
+static dpf_status queue_plain_run_step(dpf_handle* h, StepArgs a, bool first, int par, bool last) {
+  float* e[2] = {at<float>(h, h->L.ell), at<float>(h, h->L.ell1)};
+  float* w[2] = {at<float>(h, h->L.logw), at<float>(h, h->L.logw1)};
+  float* k[2] = {at<float>(h, h->L.kpart), at<float>(h, h->L.kpart1)};
+  a.ell = e[par];
+  a.logw = w[par];
+  a.kpart = k[par];
+  set_view(h, a, par);
+  dpf_status s = phase_mark(h, 0);
+  if (s == DPF_OK && first) s = launch_classes(h, OP_DPF_WEIGHTS, a);
+  if (s == DPF_OK) s = phase_mark(h, 1);
+  if (s == DPF_OK && !h->one_group) {
+    hipLaunchKernelGGL(k_res_stats, dim3(h->L.n_rgroups), dim3(kBlock), 0, h->stream, a,
+                       at<int2>(h, h->L.rgroups), 0);
+    LAUNCH_CHECK("k_res_stats");
+  }
+  if (s == DPF_OK) s = phase_mark(h, 2);
+  set_view_after(h, a, par ^ 1);
+  a.ell_next = e[par ^ 1];
+  a.logw_next = w[par ^ 1];
+  a.kpart = k[par ^ 1];
+  a.kpart_prev = k[par];
+  a.n_head = h->F;
+  if (s == DPF_OK) s = launch_classes(h, OP_NEWCLOUD_PLAIN, a);
+  if (s == DPF_OK) s = phase_mark(h, 3);
+  if (s == DPF_OK && last && par == 0) {
+    set_view(h, a, 1);
+    set_view_after(h, a, 0);
+    hipLaunchKernelGGL(k_view_copy, dim3((h->F + kBlock - 1) / kBlock), dim3(kBlock), 0, h->stream, a);
+    LAUNCH_CHECK("k_view_copy");
+  }
+  if (s == DPF_OK) s = phase_mark(h, 4);
+  h->mom_valid = a.mom != nullptr;
+  return s;
+}
+
+// One step.  fuse (look-ahead runs, and plain ones of the models whose
+// new-cloud kernel forms the next weights): 0 a step on its own; 1 the first
 // step of a run; 2 a later one (its weights were computed by the previous
 // step's new-cloud kernel; nested weights are launched each step).  In a run, par alternates: the view, weight and
 // kpart buffers this step reads (it writes the other view and the next
@@ -652,7 +694,10 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
   a.advance = 1;
   const bool nested = h->n_comp > 0;  // (every step launches its weights)
   h->ell_sel = fuse && !nested ? par : 0;
-  if (h->algo == DPF_ALGO_PLAIN) return queue_plain_step(h, a);
+  if (h->algo == DPF_ALGO_PLAIN) {
+    if (!fuse) return queue_plain_step(h, a);
+    return queue_plain_run_step(h, a, fuse == 1, par, last);
+  }
   const bool many = many_groups(h) && !h->one_group;
   a.rgroups = at<int2>(h, h->L.rgroups);
   if (fuse) {
@@ -938,7 +983,8 @@ static dpf_status queue_run_step(dpf_handle* h, int mode, const float* d_Y, int 
   // its weights each step, and takes the rest of the run's form where that
   // needs no weights of the next step: every filter of one group; 86 us per
   // step of 256 filters of 200 x 20 with k_post and k_post_end, 79 so)
-  if (h->algo == DPF_ALGO_LOOKAHEAD && T > 1 && (h->n_comp == 0 || h->one_group))
+  const bool la = h->algo == DPF_ALGO_LOOKAHEAD;
+  if (T > 1 && (la ? h->n_comp == 0 || h->one_group : h->eng->plain_fused))
     return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt, q == 0 ? 1 : 2, q & 1, q == T - 1);
   return queue_step(h, d_Y, stride, nullptr, (const int*)d_Tf, T, xt, zt);
 }
@@ -1030,7 +1076,8 @@ static dpf_status run_steps(dpf_handle* h, int mode, const float* d_Y, int32_t T
   for (int q = 1; q + S <= T - R; q += S) HIP_TRY(hipGraphLaunch(h->gexec, h->stream));
   if (R > 0) HIP_TRY(hipGraphLaunch(h->gexec_tail, h->stream));
   // (the captured steps do not update the host's record of the buffers)
-  if (mode == 0 && h->algo == DPF_ALGO_LOOKAHEAD && h->n_comp == 0) h->ell_sel = (T - 1) & 1;
+  const bool la = h->algo == DPF_ALGO_LOOKAHEAD;
+  if (mode == 0 && (la ? h->n_comp == 0 : h->eng->plain_fused)) h->ell_sel = (T - 1) & 1;
   return DPF_OK;
 }
 

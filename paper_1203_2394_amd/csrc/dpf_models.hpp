@@ -255,6 +255,29 @@ struct NonLin {
       for (int k = 0; k < DY; ++k) r0[k] = y[k] - c * q;
     }
   }
+  // obs_pre of the plain weights, its roundings written out: the weights
+  // kernel and the new-cloud kernel of a run form them in different
+  // surroundings, where the compiler fuses different products (the first
+  // component's product is fused into its difference, the others are not).
+  __device__ static void obs_pre_plain(Prm P, const float* y, const float* x, float* r0) {
+    static_assert(DX == 2, "two components of x");
+    const float c = P[L::c];
+    float p[DX];
+    if (P[L::bmode] == 0.0f) {
+      r0[0] = __builtin_fmaf(-x[0], c * x[0], y[0]);
+#pragma unroll
+      for (int d = 0; d < DX; ++d) p[d] = c * x[d] * x[d];
+    } else {
+      const float q = __builtin_fmaf(x[0], x[0], x[1] * x[1]);
+      r0[0] = __builtin_fmaf(-c, q, y[0]);
+#pragma unroll
+      for (int d = 0; d < DX; ++d) p[d] = c * q;
+    }
+#pragma unroll
+    for (int d = 0; d < DX; ++d) asm volatile("" : "+v"(p[d]));
+#pragma unroll
+    for (int k = 1; k < DY; ++k) r0[k] = y[k] - p[k % DX];
+  }
   __device__ static float logpy_post(Prm P, const float* r0, const float* z) {
     float q = 0.f;
 #pragma unroll
