@@ -51,12 +51,21 @@ constexpr int kNumDefaultClasses = 6;
 // (narrow_model); indices from kNumClasses on, not public.  256 filters of
 // 200 x 20: 51.8 us per step in 32 lanes, 34.3 in 8 x 3; 32 of 1000 x 100: 105 us
 // in 128 lanes, 62 in 16 x 7.
+// The last three (wave classes: also for the nonlinear model) take one wave per
+// particle instead of the two of 128 lanes, or the four of 256 x 4 where at most
+// half of its places would be used, of which all but the first await its outer
+// draws.  One filter of 3805 particles of the nonlinear model: M = 303 70 us per
+// step in 256 x 4, 44 in 64 x 6; M = 90 35 us in 128, 31 in 64 x 2.
 struct NarrowShape {
-  int seg, jpt, ord;
+  int seg, jpt;
+  int ord, items;  // of the class stood in for
 };
-static constexpr NarrowShape kNarrow[] = {{8, 1, 32},  {8, 2, 32},  {8, 3, 32},  {8, 4, 32},  {16, 3, 64}, {16, 4, 64},
-                                          {16, 5, 128}, {16, 6, 128}, {16, 7, 128}, {16, 8, 128}};
-constexpr int kNumNarrow = 10;
+static constexpr NarrowShape kNarrow[] = {{8, 1, 32, 1},   {8, 2, 32, 1},   {8, 3, 32, 1},   {8, 4, 32, 1},
+                                          {16, 3, 64, 1},  {16, 4, 64, 1},  {16, 5, 128, 1}, {16, 6, 128, 1},
+                                          {16, 7, 128, 1}, {16, 8, 128, 1}, {64, 2, 128, 1}, {64, 6, 256, 4},
+                                          {64, 8, 256, 4}};
+constexpr int kNumNarrow = 13;
+constexpr int kNarrowWave = 10;  // from here on: a wave per particle
 
 struct TileClass {
   int cls;  // kClasses, then kNarrow
@@ -110,7 +119,7 @@ struct Engine {
   dpf_status (*post)(int op, const StepArgs& a, const int2* rgroups, int n_rgroups, int F, const StepEnd& e,
                      hipStream_t s);
   bool yhat;  // the look-ahead pass can form the predicted observation
-  bool narrow;  // the narrow classes are built
+  int narrow_from;  // the narrow classes from this one on are built
   bool plain_fused;  // a plain run's new-cloud kernel computes the next step's weights
 };
 

@@ -63,14 +63,15 @@ static void launch_op(int op, const StepArgs& a, int n, hipStream_t s) {
 }
 
 // Narrow classes: the small models (a segment's fixed work outweighs its inner
-// particles' there; NONLIN's eight-component clouds and the wide z gain
-// nothing).
+// particles' there; NONLIN's eight-component clouds gain nothing in 8 or 16
+// lanes, and the wide z in none).
 template <class Mdl>
-constexpr bool narrow_model() { return Mdl::DZ <= 2; }
+constexpr int narrow_from() { return Mdl::DZ <= 2 ? 0 : Mdl::DZ <= 8 ? kNarrowWave : kNumNarrow; }
 
 template <class Mdl, int K>
 static void launch_narrow(int op, const StepArgs& a, int n, hipStream_t s) {
   constexpr int SEG = kNarrow[K].seg, JPT = kNarrow[K].jpt, ORD = kNarrow[K].ord;
+  static_assert(ORD <= 128 ? kNarrow[K].items == 1 : SEG == kWave, "SegLse");
   switch (op) {
     case OP_INIT_LA:
       hipLaunchKernelGGL((k_init<Mdl, SEG, JPT, false>), dim3(n), dim3(kBlock), 0, s, a);
@@ -93,6 +94,19 @@ static void launch_narrow(int op, const StepArgs& a, int n, hipStream_t s) {
     case OP_NEWCLOUD_PLAIN:
       hipLaunchKernelGGL((k_newcloud<Mdl, SEG, JPT, true, ORD>), dim3(n), dim3(kBlock), 0, s, a);
       break;
+  }
+}
+
+// Narrow class k, of the classes K and on.
+template <class Mdl, int K>
+static bool launch_narrow_class(int k, int op, const StepArgs& a, int n, hipStream_t s) {
+  if constexpr (K < kNumNarrow) {
+    if (k != K) return launch_narrow_class<Mdl, K + 1>(k, op, a, n, s);
+    // (the small models take 16 lanes where the first wave class would do)
+    if constexpr (K != kNarrowWave || narrow_from<Mdl>() == kNarrowWave) launch_narrow<Mdl, K>(op, a, n, s);
+    return true;
+  } else {
+    return false;
   }
 }
 
@@ -132,24 +146,13 @@ static dpf_status engine_mdn_draw(const StepArgs& a, hipStream_t s) {
 template <class Mdl>
 static dpf_status engine_launch(int op, const StepArgs& a, const TileClass& tc, hipStream_t s) {
   const int n = tc.n_tiles;
-  if constexpr (narrow_model<Mdl>()) {
+  if constexpr (narrow_from<Mdl>() < kNumNarrow) {
     if (tc.cls >= kNumClasses) {
       // (the learned passes and the moments run in the public classes)
       if (op == OP_LEARNED_INNER || op == OP_MOMENTS || op == OP_LA_WEIGHTS_FALLBACK || op == OP_NEWCLOUD_FALLBACK)
         return fail(DPF_EUNSUPPORTED, "operation %d has no narrow class", op);
-      switch (tc.cls - kNumClasses) {
-        case 0: launch_narrow<Mdl, 0>(op, a, n, s); break;
-        case 1: launch_narrow<Mdl, 1>(op, a, n, s); break;
-        case 2: launch_narrow<Mdl, 2>(op, a, n, s); break;
-        case 3: launch_narrow<Mdl, 3>(op, a, n, s); break;
-        case 4: launch_narrow<Mdl, 4>(op, a, n, s); break;
-        case 5: launch_narrow<Mdl, 5>(op, a, n, s); break;
-        case 6: launch_narrow<Mdl, 6>(op, a, n, s); break;
-        case 7: launch_narrow<Mdl, 7>(op, a, n, s); break;
-        case 8: launch_narrow<Mdl, 8>(op, a, n, s); break;
-        case 9: launch_narrow<Mdl, 9>(op, a, n, s); break;
-        default: return fail(DPF_EUNSUPPORTED, "no kernel class %d", tc.cls);
-      }
+      if (!launch_narrow_class<Mdl, narrow_from<Mdl>()>(tc.cls - kNumClasses, op, a, n, s))
+        return fail(DPF_EUNSUPPORTED, "no kernel class %d", tc.cls);
       LAUNCH_CHECK("step kernel");
       return DPF_OK;
     }
@@ -245,7 +248,7 @@ static Engine make_engine(void (*derive)(const double*, std::vector<float>&)) {
                 engine_finalize<Mdl>,
                 engine_post<Mdl>,
                 has_yhat<Mdl>(),
-                narrow_model<Mdl>(),
+                narrow_from<Mdl>(),
                 !Mdl::kStreamZ};
 }
 

@@ -315,38 +315,71 @@ __device__ __forceinline__ float seg_lse_ord(const float* v, SegScratch& sh) {
 }
 
 // A segment's accumulated log-sum-exp and sum: ORD = 0 each lane's items as
-// they come (online), then the lanes; else in the order of an ORD-lane segment.
+// they come (online), then the lanes; 8 or 16 lanes in the order of an ORD-lane
+// segment with one item per lane; a wave (item j in lane j % 64) in the order
+// of ORD lanes with any: lane j % ORD's items as they come, then its wave's
+// lanes, then the waves.
 template <int SEG, int JPT, int ORD>
 struct SegLse {
-  Lse l;
-  float v[ORD ? JPT : 1];
+  static constexpr bool kOne = ORD > 0 && SEG < kWave;
+  static constexpr int NL = ORD > kWave && !kOne ? ORD / kWave : 1;
+  Lse l[NL];
+  float v[kOne ? JPT : 1];
   __device__ SegLse() {
 #pragma unroll
-    for (int r = 0; r < (ORD ? JPT : 1); ++r) v[r] = -INFINITY;
+    for (int r = 0; r < (kOne ? JPT : 1); ++r) v[r] = -INFINITY;
   }
   __device__ __forceinline__ void add(int r, float e) {
-    if constexpr (ORD == 0) l.add(e);
-    else v[r] = e;
+    if constexpr (kOne) v[r] = e;
+    else l[r % NL].add(e);
   }
   __device__ __forceinline__ float get(SegScratch& sh) const {
-    if constexpr (ORD == 0) return seg_lse<SEG>(l, sh);
-    else return seg_lse_ord<SEG, JPT, ORD>(v, sh);
+    if constexpr (kOne) {
+      return seg_lse_ord<SEG, JPT, ORD>(v, sh);
+    } else if constexpr (NL == 1) {
+      return seg_lse<SEG>(l[0], sh);
+    } else {
+      float m = l[0].m;
+#pragma unroll
+      for (int w = 1; w < NL; ++w) m = fmaxf(m, l[w].m);
+      m = seg_max<SEG>(m, sh);
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < NL; ++w) {
+        const float sw = seg_sum<SEG>((l[w].m == -INFINITY) ? 0.f : l[w].s * fast_exp(l[w].m - m), sh);
+        s = w == 0 ? sw : s + sw;
+      }
+      return (m == -INFINITY) ? -INFINITY : m + fast_log(s);
+    }
   }
 };
 template <int SEG, int JPT, int ORD>
 struct SegSum {
-  float v[ORD ? JPT : 1];
+  static constexpr bool kOne = ORD > 0 && SEG < kWave;
+  static constexpr int NL = ORD > kWave && !kOne ? ORD / kWave : 1;
+  float v[kOne ? JPT : NL];
   __device__ SegSum() {
 #pragma unroll
-    for (int r = 0; r < (ORD ? JPT : 1); ++r) v[r] = 0.f;
+    for (int r = 0; r < (kOne ? JPT : NL); ++r) v[r] = 0.f;
   }
   __device__ __forceinline__ void add(int r, float q, float h) {
-    if constexpr (ORD == 0) v[0] += q * h;
-    else v[r] = q * h;
+    if constexpr (kOne) v[r] = q * h;
+    else v[r % NL] += q * h;
   }
   __device__ __forceinline__ float get(SegScratch& sh) const {
-    if constexpr (ORD == 0) return seg_sum<SEG>(v[0], sh);
-    else return seg_sum_ord<SEG, JPT, ORD>(v);
+    if constexpr (kOne) {
+      return seg_sum_ord<SEG, JPT, ORD>(v);
+    } else if constexpr (NL == 1) {
+      return seg_sum<SEG>(v[0], sh);
+    } else {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < NL; ++w) {
+        const float sw = seg_sum<SEG>(v[w], sh);
+        s = w == 0 ? sw : s + sw;
+      }
+      return s;
+    }
   }
 };
 
