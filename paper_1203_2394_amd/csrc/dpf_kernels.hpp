@@ -1031,6 +1031,7 @@ __global__ __launch_bounds__(kBlock) void k_la_weights_nested(StepArgs a) {
 }
 
 static __device__ bool learned_rejected(const StepArgs& a, int f, int N, float* fred4, double* red4);
+static __device__ bool learned_rejected_wave(const StepArgs& a, int f, int N);
 
 // One workgroup per tile.  (A kernel that loops over tiles compiles to
 // markedly slower code for the single-tile case, so the learned step's
@@ -1062,9 +1063,21 @@ static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(m
     const bool start = have && (th == 0 || tfl[th - 1] != tl.x);
     int myrun;
     const int nr = block_compact(start, th, runs, wcnt, &myrun);
+    // a wave per filter of up to 64 groups, four filters at a time (all of the
+    // workgroup one after the other took 8 of this kernel's 12 us where none of
+    // 8 filters falls back, now 2)
+    for (int r = th / kWave; r < nr; r += kBlock / kWave) {
+      const int f = tfl[runs[r]];
+      const bool wave = a.finfo[f].ngroup <= kWave;
+      const bool rej = wave && step_active(a, f) && learned_rejected_wave(a, f, a.fN[f]);
+      if (th % kWave == 0) rejr[r] = wave ? (rej ? 1 : 0) : 2;
+    }
+    __syncthreads();
     for (int r = 0; r < nr; ++r) {
+      if (rejr[r] != 2) continue;
       const int f = tfl[runs[r]];
       const bool rej = step_active(a, f) && learned_rejected(a, f, a.fN[f], fred4, red4);
+      __syncthreads();
       if (th == 0) rejr[r] = rej ? 1 : 0;
       __syncthreads();
     }
@@ -1240,6 +1253,22 @@ static __device__ bool learned_rejected(const StepArgs& a, int f, int N, float* 
   }
   const double total = block_sum_256(T, red4);
   const double sumsq = block_sum_256(Q, red4);
+  return total * total < a.ess_frac * (double)N * sumsq;
+}
+
+// The same by one wave (the same sums: beyond 64 groups the others' are 0).
+static __device__ bool learned_rejected_wave(const StepArgs& a, int f, int N) {
+  const int l = threadIdx.x & (kWave - 1);
+  const int G = a.finfo[f].ngroup;
+  const double* gs = a.gstat + 4LL * a.finfo[f].rg_base;
+  const int lc = min(l, G - 1);
+  const double g0 = gs[4 * lc], g1 = gs[4 * lc + 1], g2 = gs[4 * lc + 2];
+  const float gm = l < G ? (float)g0 : -INFINITY;
+  const float m = seg_reduce_wave<OpMax, kWave>(gm);
+  if (!(m > -INFINITY)) return true;
+  const double c = l < G ? group_scale<LogSrc>(gm, m) : 0.0;
+  const double total = seg_reduce_wave<OpAdd, kWave>(l < G ? c * g1 : 0.0);
+  const double sumsq = seg_reduce_wave<OpAdd, kWave>(l < G ? (c * c) * g2 : 0.0);
   return total * total < a.ess_frac * (double)N * sumsq;
 }
 

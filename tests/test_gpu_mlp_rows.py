@@ -43,3 +43,20 @@ def test_state_network_row_tiles(rows):
     assert np.isfinite(got[on]).all()
     assert _rel_l2(got[on], ref[on]) < 1e-6
     assert np.abs(got[on] - ref[on]).max() <= 1e-5 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("ess_frac", [0.0, 1.0])
+def test_fallback_decision_over_many_groups(ess_frac):
+    """Filters decided by a wave each (up to 64 groups of 256) and by a whole
+    workgroup (more): none of them falls back at a threshold of 0, all at 1
+    (no filter of several particles has an ESS of exactly N)."""
+    spec = _spec()
+    Ns, Ms = [40, 17000, 300, 16384, 16385, 2], [8, 4, 16, 4, 8, 8]
+    f = dpf.Filter(spec.kind, spec.dx, spec.dz, spec.dy, spec.blob, Ns, Ms, seed=31)
+    Y = torch.tensor(np.stack([S.simulate(spec, 1, 60 + q)[2][0] for q in range(len(Ns))]), dtype=torch.float32)
+    m = _mlp(_params(15), np.zeros(26, dtype=np.float32), np.full(26, 5.0, dtype=np.float32))
+    f.set_proposal(m, ess_frac=ess_frac)
+    f.learned_step(Y)
+    fell = (f.estimate()["flags"].cpu().numpy() & dpf.FLAG_FALLBACK) != 0
+    assert fell.all() if ess_frac else not fell.any(), fell
+    assert np.isfinite(f.copy_buffer(dpf.BUF_LOGW).cpu().numpy()).all()
