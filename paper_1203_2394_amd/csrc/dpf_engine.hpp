@@ -48,7 +48,7 @@ constexpr int kNumDefaultClasses = 6;
 // lanes where M does not fill the default class.  Their log-sum-exps add in
 // the default class's order, so a filter's particles and weights are the same
 // bits in either.  Built for the models of one or two inner components
-// (narrow_model); indices from kNumClasses on, not public.  256 filters of
+// (narrow_from); indices from kNumClasses on, not public.  256 filters of
 // 200 x 20: 51.8 us per step in 32 lanes, 34.3 in 8 x 3; 32 of 1000 x 100: 105 us
 // in 128 lanes, 62 in 16 x 7.
 // The last three (wave classes: also for the nonlinear model) take one wave per

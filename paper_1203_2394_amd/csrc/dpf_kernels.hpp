@@ -15,7 +15,9 @@
 // the outer weights (filters of several resampling groups), the new-cloud
 // kernel and the step end; in a run the new-cloud kernel also computes the next
 // step's weights and the previous step's estimates, and only what the outer
-// resampling needs stands between two of them.
+// resampling needs stands between two of them.  A plain step likewise: weights,
+// statistics, new cloud and estimates on its own, statistics and new cloud in a
+// run.
 //
 // Per-particle kernels run one 256-thread workgroup per tile of 256/SEG
 // consecutive outer particles of one filter (a "segment" of SEG lanes per

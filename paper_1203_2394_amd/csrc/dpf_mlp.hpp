@@ -15,7 +15,8 @@
 // index (weight gradients), blocked by 32 batch rows: [B / 32][columns][32],
 // so that an operand fragment is 1 KB of contiguous memory.
 //
-// Row tiles: a 256-thread workgroup (4 waves) owns 16 rows of the batch;
+// Row tiles: a 256-thread workgroup (4 waves) owns 16 rows of the batch (the
+// network on a large handle's state up to four such tiles: MlpTiles);
 // wave w computes hidden columns 64 w .. 64 w + 63.
 #pragma once
 #include <hip/hip_runtime.h>
