@@ -140,6 +140,7 @@ struct StepArgs {
   const int4* ginfo;    // per resampling group: its filter's (first outer index, N, first group, groups)
   int n_commit;         // learned-step commit workgroups at the head of the launch
   int later_step;       // nested run: a step after its first
+  int finish;           // step on its own: the last workgroup of a filter finishes it
   int n_comp;           // companions per look-ahead candidate (nested estimator; 0: paired)
   // predicted observation (models with a one-dimensional y), or null: per
   // outer particle sum_j qbar h(xla, zla) of this step's look-ahead draws
@@ -2798,6 +2799,52 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   if (vk && ls == 0 && fl) atomicOr(&a.flags[f], fl);
 }
 
+// End of a step on its own where every filter has one group and the launch few
+// workgroups: a filter's last workgroup (of its tiles, and in a plain step of
+// its head workgroup) forms a look-ahead step's estimates as k_post does and
+// makes the view after the step the handle's own: a launch less (two in a plain
+// step).  Every wave releases its stores before the count; the last workgroup
+// acquires after it.
+template <class Mdl, int SEG, bool PLAIN>
+__device__ __forceinline__ void finish_step(const StepArgs& a, int f) {
+  constexpr int DX = Mdl::DX, DZ = Mdl::DZ;
+  constexpr bool YH = has_yhat<Mdl>() && !PLAIN;
+  constexpr int NV = DX + DZ + (YH ? 1 : 0);
+  constexpr int NSEG = kBlock / SEG;
+  __shared__ double part[kBlock / kWave][NV];
+  __shared__ int last;
+  const int N = a.fN[f], oo = a.ooff[f];
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicAdd(&a.fcount[f], 1) == (N + NSEG - 1) / NSEG + (PLAIN ? 1 : 0) - 1;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  const int t = a.tcur_n[f], act = a.act_n[f], cu = a.cur_n[f];
+  if (!PLAIN && (act & 2)) {
+    const int i = min((int)threadIdx.x, N - 1);
+    const double w = 1.0 / N;
+    double v[NV];
+    const float* xs = a.x[copy_of((unsigned char)cu)];
+#pragma unroll
+    for (int d = 0; d < DX; ++d) v[d] = (double)xs[(long long)d * a.NT + oo + i];
+#pragma unroll
+    for (int d = 0; d < DZ; ++d) v[DX + d] = (double)a.kpart[(long long)(oo + i) * DZ + d];
+    if constexpr (YH) v[NV - 1] = a.yp != nullptr ? (double)a.yp[oo + i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = (int)threadIdx.x < N ? w * v[q] : 0.0;
+    const double e = est_partial<NV>(v, part);
+    const int q = threadIdx.x;
+    if (q < DX + DZ || (YH && q < NV && a.yp != nullptr)) est_store<DX, DZ>(a, f, t, q, 0.0 + e);
+  }
+  if (threadIdx.x == 0) {
+    a.fcount[f] = 0;
+    a.tcur[f] = t;
+    a.cur[f] = (unsigned char)cu;
+    a.act[f] = (unsigned char)act;
+  }
+}
+
 // With the wide inner state the children of one parent (neighbouring tiles
 // after the ordered resampling) run on one XCD and read the parent's cloud
 // through one L2.
@@ -2805,12 +2852,18 @@ template <class Mdl, int SEG, int JPT, bool PLAIN, int ORD = 0>
 static __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_waves<Mdl>()))) void k_newcloud(StepArgs a) {
   if ((int)blockIdx.x < a.n_head) {
     if constexpr (!PLAIN) est_head<Mdl::DX, Mdl::DZ, has_yhat<Mdl>()>(a, blockIdx.x);
-    else if constexpr (!Mdl::kStreamZ) est_head_plain<Mdl::DX, Mdl::DZ>(a, blockIdx.x);
+    else if constexpr (!Mdl::kStreamZ) {
+      est_head_plain<Mdl::DX, Mdl::DZ>(a, blockIdx.x);
+      if (a.finish) finish_step<Mdl, SEG, PLAIN>(a, blockIdx.x);
+    }
     return;
   }
   const int b = (int)blockIdx.x - a.n_head;
   const int ti = Mdl::kStreamZ ? xcd_contiguous_tile(b, (int)gridDim.x - a.n_head) : b;
   newcloud_tile<Mdl, SEG, JPT, PLAIN, ORD>(a, ti);
+  if constexpr (!Mdl::kStreamZ) {
+    if (a.finish) finish_step<Mdl, SEG, PLAIN>(a, a.tiles[ti].x);
+  }
 }
 
 // Learned step: the new clouds of the filters that fell back only (smaller
