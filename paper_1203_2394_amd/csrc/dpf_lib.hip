@@ -700,9 +700,10 @@ static dpf_status queue_plain_run_step(dpf_handle* h, StepArgs a, bool first, in
 // One step.  fuse (look-ahead runs, and plain ones of the models whose
 // new-cloud kernel forms the next weights): 0 a step on its own; 1 the first
 // step of a run; 2 a later one (its weights were computed by the previous
-// step's new-cloud kernel; nested weights are launched each step).  In a run, par alternates: the view, weight and
-// kpart buffers this step reads (it writes the other view and the next
-// step's weights to the other pair); last: the run's last step.
+// step's new-cloud kernel; nested weights are launched each step).  In a run,
+// par alternates: the view, weight and kpart buffers this step reads (it
+// writes the other view and the next step's weights to the other pair); last:
+// the run's last step.
 //
 // Launches of a look-ahead step between its weights and the next's: the
 // new-cloud kernel, and
