@@ -726,7 +726,15 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
   const int src = copy_of(cb);
   const Key key = make_key(a.seed, (uint32_t)f);
   const int ci = vi ? (ident_slots(cb, src) ? i : a.ind[src][oo + i]) : 0;
+  // - log K: with one item per lane the compiler fuses its product into the
+  // difference, with several (where it is formed once) not; the classes that
+  // stand in for one item do as those
+  const float log2K = __builtin_amdgcn_logf((float)K);
   const float logK = fast_log((float)K);
+  auto less_log_k = [&](float v) -> float {
+    if constexpr (ORD > 0 && ORD <= 128) return __builtin_fmaf(-log2K, 0.6931471805599453f, v);
+    else return v - logK;
+  };
 
   float y[DY], x[DX];
   load_y<Mdl>(a, f, t, y);
@@ -826,7 +834,7 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
             }
           }
         }
-        const float g = (acck.m == -INFINITY) ? -INFINITY : acck.m + fast_log(acck.s) - logK;
+        const float g = (acck.m == -INFINITY) ? -INFINITY : less_log_k(acck.m + fast_log(acck.s));
         ev[r] = la_ell(lamv[r], g);
         if (want_h) hv.add(r, fast_exp(lamv[r]), hk * invK);
       }
@@ -1005,7 +1013,7 @@ __device__ __forceinline__ void la_weights_nested_tile(const StepArgs& a, int ti
             emit(bk[q], nb + q * DZ);
           }
         }
-        const float g = (acck.m == -INFINITY) ? -INFINITY : acck.m + fast_log(acck.s) - logK;
+        const float g = (acck.m == -INFINITY) ? -INFINITY : less_log_k(acck.m + fast_log(acck.s));
         ev[r] = la_ell(lamv[r], g);
         if (want_h) hv.add(r, fast_exp(lamv[r]), hk * invK);
       }

@@ -6,7 +6,6 @@
 // in FP64), builds the tile lists and queues the initialisation.  Each step
 // call queues a fixed sequence of launches on the handle's stream; nothing
 // synchronises with the host.
-#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -498,53 +497,50 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
 }
 
 // The narrow class (index from kNumClasses on) of filter f's default class and
-// inner size, of kNarrow[k0] .. kNarrow[k1 - 1]; -1: none.
-static int narrow_class(const dpf_handle* h, int f, int k0, int k1) {
+// inner size; -1: none.
+static int narrow_class(const dpf_handle* h, int f) {
   const ClassShape& c = kClasses[h->fcls[f]];
-  for (int k = std::max(k0, h->eng->narrow_from); k < k1; ++k)
+  for (int k = h->eng->narrow_from; k < kNumNarrow; ++k)
     if (kNarrow[k].ord == c.seg && kNarrow[k].items == c.jpt && h->M[f] <= kNarrow[k].seg * kNarrow[k].jpt)
       return kNumClasses + k;
   return -1;
 }
-// (a handle with companions has no wave classes: the nested weights round as
-// the compiler fuses them in each class)
-static int narrow_class(const dpf_handle* h, int f) {
-  return narrow_class(h, f, 0, h->n_comp > 0 ? kNarrowWave : kNumNarrow);
-}
 
-// Whether narrow classes stand in for the handle's default ones.  A narrow
-// wave does the work of several wide ones one after the other, so it pays once
-// the narrow waves alone fill the SIMDs (1024) with some to spare: measured
-// over runs of the small models (N = 200 to 2000, M = 10 to 100, look-ahead
-// and plain) narrow / wide speed 0.82 to 1.09 at 1000 waves, 0.92 to 1.09 at
-// 1500, 1.04 to 1.36 at 1600 to 1700, 1.05 to 1.4 at 2000, 1.16 to 1.62 at
-// 3000 and 1.5 to 2.0 beyond 6000.
+// Which narrow classes stand in for the handle's default ones.  A narrow wave
+// does the work of several wide ones one after the other, so a narrow launch
+// (one per class) pays once its waves alone fill the SIMDs (1024) with some to
+// spare: measured over runs of the small models (N = 200 to 2000, M = 10 to 100,
+// look-ahead and plain) narrow / wide speed 0.82 to 1.09 at 1000 waves, 0.92 to
+// 1.09 at 1500, 1.04 to 1.36 at 1600 to 1700, 1.05 to 1.4 at 2000, 1.16 to 1.62 at
+// 3000 and 1.5 to 2.0 beyond 6000; three classes of some 600 waves each 0.85.
 // The wave classes' line lies at 1024 (their waves count 25 / 16): over M = 65
 // to 512 0.75 to 1.06 at 256 to 700 waves, 1.00 to 1.16 at 1024, 1.04 to 1.45 at
 // 1600, 1.1 to 2.35 from 3800 on.
 constexpr long long kNarrowWaves = 1600;
 
-static bool use_narrow(const dpf_handle* h) {
-  if (h->wide) return false;
-  long long sixteenths = 0;
+static std::vector<bool> narrow_used(const dpf_handle* h) {
+  std::vector<bool> used(kNumNarrow, false);
+  if (h->wide) return used;
+  std::vector<long long> sixteenths(kNumNarrow, 0);
   for (int f = 0; f < h->F; ++f) {
-    const int c = h->fdef[f] ? narrow_class(h, f) : -1;
-    if (c < 0) continue;
-    const int per_wave = kWave / kNarrow[c - kNumClasses].seg;
-    sixteenths += (h->N[f] + per_wave - 1) / per_wave * (c - kNumClasses >= kNarrowWave ? 25LL : 16LL);
+    const int k = h->fdef[f] ? narrow_class(h, f) - kNumClasses : -1;
+    if (k < 0) continue;
+    const int per_wave = kWave / kNarrow[k].seg;
+    sixteenths[k] += (h->N[f] + per_wave - 1) / per_wave * (k >= kNarrowWave ? 25LL : 16LL);
   }
-  return sixteenths >= 16 * kNarrowWaves;
+  for (int k = 0; k < kNumNarrow; ++k) used[k] = sixteenths[k] >= 16 * kNarrowWaves;
+  return used;
 }
 
 // Tiles of every filter in its launch class, grouped by class, uploaded to the
 // workspace (room for one tile per outer particle was reserved).
 static dpf_status build_tiles(dpf_handle* h) {
   const int F = h->F;
-  const bool narrow = use_narrow(h);
+  const std::vector<bool> narrow = narrow_used(h);
   std::vector<std::vector<int4>> by(kNumClasses + kNumNarrow);
   for (int f = 0; f < F; ++f) {
-    const int nc = narrow && h->fdef[f] ? narrow_class(h, f) : -1;
-    const int c = nc >= 0 ? nc : h->fcls[f];
+    const int nc = h->fdef[f] ? narrow_class(h, f) : -1;
+    const int c = nc >= 0 && narrow[nc - kNumClasses] ? nc : h->fcls[f];
     const int segs = kBlock / (c < kNumClasses ? kClasses[c].seg : kNarrow[c - kNumClasses].seg);
     int nt = 0;
     for (int i0 = 0; i0 < h->N[f]; i0 += segs)
@@ -882,11 +878,7 @@ extern "C" dpf_status dpf_set_lookahead_companions(dpf_handle* h, int32_t n_comp
   if (h->algo != DPF_ALGO_LOOKAHEAD) return fail(DPF_ESTATE, "companions belong to the look-ahead DPF");
   if (n_comp < 0 || n_comp > kMaxCompanions)
     return fail(DPF_EINVAL, "n_comp = %d outside 0..%d", n_comp, kMaxCompanions);
-  const bool other = (h->n_comp > 0) != (n_comp > 0);
   h->n_comp = n_comp;
-  if (other)  // (tiles only where the handle has wave classes with or without companions)
-    for (int f = 0; f < h->F; ++f)
-      if (h->fdef[f] && narrow_class(h, f, kNarrowWave, kNumNarrow) >= 0) return build_tiles(h);
   return DPF_OK;
 }
 
