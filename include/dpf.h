@@ -259,7 +259,8 @@ dpf_status dpf_import_state(dpf_handle* h, const void* d_src, size_t bytes);
 
 /* Internal buffers of the last step, copied out for inspection:
  * DPF_BUF_ELL  float [sum N*M]: look-ahead (or measurement) log-weights ell
- *                               of the last step taken (also after a run)
+ *                               of each filter's last step taken (also after a
+ *                               run that some filters left early)
  * DPF_BUF_LOGW float [sum N]:   outer log-weights log w_i of that step
  * DPF_BUF_ANC  int32 [sum N]:   outer ancestors A_k
  * DPF_BUF_SEL  int32 [sum N]:   selected candidate (look-ahead) or

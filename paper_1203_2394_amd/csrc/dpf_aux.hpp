@@ -11,14 +11,15 @@
 namespace dpf {
 
 // t = 0, state in copy 0 (the plain DPF's initial proposals are written
-// there from the prior held in copy 1), flags and evidence cleared.
+// there from the prior held in copy 1), flags and evidence cleared.  keep: the
+// bits of cur that stay (where the last step's weights lie).
 static __global__ void k_reset(int* tcur, unsigned char* cur, unsigned char* act, uint32_t* flags, double* loglik,
-                        uint32_t* lflags, int* fcount, int F) {
+                        uint32_t* lflags, int* fcount, int F, int keep) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= F) return;
   tcur[f] = 0;
   fcount[f] = 0;
-  cur[f] = 6;  // copy 0; identity cloud slots in both copies
+  cur[f] = (unsigned char)(6 | (keep ? cur[f] & keep : 0));  // copy 0; identity cloud slots in both copies
   act[f] = 1;
   flags[f] = 0u;
   loglik[f] = 0.0;
@@ -150,7 +151,7 @@ static __global__ __launch_bounds__(kBlock) void k_state_io(StateIo a) {
     if (rg.y == 0 && threadIdx.x == 0) {
       if constexpr (IMPORT) {
         a.tcur[f] = et[f];
-        a.cur[f] = 6;
+        a.cur[f] = (unsigned char)(6 | (a.cur[f] & kCurPair));
         a.flags[f] = 0u;
         a.loglik[f] = 0.0;
       } else {
@@ -175,6 +176,25 @@ static __global__ __launch_bounds__(kBlock) void k_state_io(StateIo a) {
       copy_run(el + io + (long long)i * M, a.lam[c] + io + sl * M, M);
     }
   }
+}
+
+// Moves the weights of the filters whose last step's lie in the second pair
+// (kCurPair) into the first, which then holds every filter's: of the groups'
+// inner particles (inner) or of their outer ones.  Workgroups as in k_state_io.
+// Calls repeat safely: the second pair and the bits stay as they are.
+static __global__ __launch_bounds__(kBlock) void k_last_weights(const unsigned char* cur, const int2* rgroups,
+                                                                const int4* ginfo, const int* fM,
+                                                                const long long* ioff, const float* second,
+                                                                float* first, int inner) {
+  const int2 rg = rgroups[blockIdx.x];
+  const int4 gi = ginfo[blockIdx.x];
+  const int f = rg.x, oo = gi.x, N = gi.y;
+  if (!(cur[f] & kCurPair)) return;
+  const int g0 = rg.y * kResGroup, ng = min(kResGroup, N - g0);
+  const int per = (ng + gridDim.y - 1) / gridDim.y;
+  const int i0 = g0 + min(ng, (int)blockIdx.y * per), i1 = g0 + min(ng, ((int)blockIdx.y + 1) * per);
+  const long long M = inner ? fM[f] : 1, at = (inner ? ioff[f] : (long long)oo) + i0 * M;
+  copy_run(first + at, second + at, (i1 - i0) * M);
 }
 
 // ---------------------------------------------------------------- primitives

@@ -91,7 +91,8 @@ struct StepArgs {
   int advance;   // 1: a step (time advances, estimates); 0: initialisation
   uint64_t seed;
   // the filters' progress (a view): time of the state; bit 0 of cur: copy
-  // holding the state, bits 1, 2: copy 0 / copy 1 has identity cloud slots;
+  // holding the state, bits 1, 2: copy 0 / copy 1 has identity cloud slots,
+  // bit 3 (kCurPair): the last step's weights lie in the second ell / logw pair;
   // bit 0 of act: the filter takes the current step (set by the weights
   // kernel), bit 1: it took the previous one
   int* tcur;
@@ -140,6 +141,7 @@ struct StepArgs {
   const int4* ginfo;    // per resampling group: its filter's (first outer index, N, first group, groups)
   int n_commit;         // learned-step commit workgroups at the head of the launch
   int later_step;       // nested run: a step after its first
+  int pair;             // the ell / logw pair this step reads (a run alternates between two)
   int finish;           // step on its own: the last workgroup of a filter finishes it
   int n_comp;           // companions per look-ahead candidate (nested estimator; 0: paired)
   // predicted observation (models with a one-dimensional y), or null: per
@@ -175,6 +177,7 @@ struct StepArgs {
 };
 
 __device__ __forceinline__ int copy_of(unsigned char c) { return c & 1; }
+constexpr int kCurPair = 8;
 
 // Every per-filter value a tile reads, fetched together: the empty asm needs
 // them all before the early exits, so the loads go out in one round instead
@@ -1678,7 +1681,7 @@ static __device__ void res_finish(const StepArgs& a, int f, int t, int N, const 
 
 // Group statistics; with advance_time, group 0's workgroup also advances the
 // filter's time and flips its state copy (no other workgroup of this launch
-// reads them).  In the learned step's second pass (fb set) a filter that
+// reads them); such a step's weights lie in the first pair.  In the learned step's second pass (fb set) a filter that
 // kept its learned proposals keeps the statistics of the first pass.
 static __global__ __launch_bounds__(kBlock) void k_res_stats(StepArgs a, const int2* rgroups, int advance_time) {
   __shared__ ResScratch sh;
@@ -1698,7 +1701,7 @@ static __global__ __launch_bounds__(kBlock) void k_res_stats(StepArgs a, const i
   if (fbv == 0) {
     if (advance_time && rg.y == 0 && threadIdx.x == 0) {
       a.tcur[f] = tc + 1;
-      a.cur[f] = (unsigned char)(cu ^ 1);
+      a.cur[f] = (unsigned char)((cu ^ 1) & ~kCurPair);
     }
     return;
   }
@@ -1715,7 +1718,7 @@ static __global__ __launch_bounds__(kBlock) void k_res_stats(StepArgs a, const i
     if (nonf) atomicOr(&a.flags[f], (uint32_t)F_NONFINITE);
     if (advance_time && rg.y == 0) {
       a.tcur[f] = tc + 1;
-      a.cur[f] = (unsigned char)(cu ^ 1);
+      a.cur[f] = (unsigned char)((cu ^ 1) & ~kCurPair);
     }
   }
 }
@@ -2183,7 +2186,7 @@ __device__ __forceinline__ void newcloud_tile(const StepArgs& a, int ti) {
   if (before && tile.z == 0 && threadIdx.x == 0) {
     // the view after the step (the new clouds are in slot order)
     a.tcur_n[f] = act ? t : fv.t;
-    a.cur_n[f] = act ? (unsigned char)(cb | (2 << dst)) : (unsigned char)fv.cur;
+    a.cur_n[f] = act ? (unsigned char)((cb & ~kCurPair) | (2 << dst) | (a.pair ? kCurPair : 0)) : (unsigned char)fv.cur;
     a.act_n[f] = act ? (unsigned char)(2 | (next ? 1 : 0)) : (unsigned char)0;
   }
   if (!act) return;

@@ -228,9 +228,6 @@ struct dpf_handle {
   bool has_proposal = false;  // a network blob was set
   bool mom_valid = false;     // mom holds the moments of the current state
   double ess_frac = 0.1;
-  // which weight buffers (0: ell/logw, 1: ell1/logw1) hold the weights of
-  // the last step taken
-  int ell_sel = 0;
   // the last call that changed the state was dpf_lookahead_step (what
   // dpf_estimate_rb needs)
   bool rb_ready = false;
@@ -381,12 +378,13 @@ static void set_view_after(dpf_handle* h, StepArgs& a, int v) {
   a.act_n = at<unsigned char>(h, v ? h->L.act1 : h->L.act);
 }
 
-static dpf_status queue_init(dpf_handle* h) {
+static dpf_status queue_init(dpf_handle* h, int keep_cur) {
   h->rb_ready = false;
   const bool plain = h->algo == DPF_ALGO_PLAIN;
   hipLaunchKernelGGL(k_reset, dim3((h->F + 255) / 256), dim3(256), 0, h->stream, at<int>(h, h->L.tcur),
                      at<unsigned char>(h, h->L.cur), at<unsigned char>(h, h->L.act), at<uint32_t>(h, h->L.flags),
-                     at<double>(h, h->L.loglik), at<uint32_t>(h, h->L.lflags), at<int>(h, h->L.fcount), h->F);
+                     at<double>(h, h->L.loglik), at<uint32_t>(h, h->L.lflags), at<int>(h, h->L.fcount), h->F,
+                     keep_cur);
   LAUNCH_CHECK("k_reset");
   h->mom_valid = false;
   StepArgs a = make_args(h);
@@ -487,7 +485,7 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
     delete h;
     return st;
   }
-  st = queue_init(h);
+  st = queue_init(h, 0);
   if (st != DPF_OK) {
     delete h;
     return st;
@@ -601,7 +599,8 @@ extern "C" dpf_status dpf_set_tiling(dpf_handle* h, const int32_t* h_cls) {
 
 extern "C" dpf_status dpf_reset(dpf_handle* h) {
   if (!h) return fail(DPF_EINVAL, "handle is NULL");
-  return queue_init(h);
+  // (a plain handle's initialisation writes the first pair)
+  return queue_init(h, h->algo == DPF_ALGO_PLAIN ? 0 : kCurPair);
 }
 
 extern "C" dpf_status dpf_destroy(dpf_handle* h) {
@@ -664,6 +663,7 @@ static dpf_status queue_plain_run_step(dpf_handle* h, StepArgs a, bool first, in
   a.ell = e[par];
   a.logw = w[par];
   a.kpart = k[par];
+  a.pair = par;
   set_view(h, a, par);
   dpf_status s = phase_mark(h, 0);
   if (s == DPF_OK && first) s = launch_classes(h, OP_DPF_WEIGHTS, a);
@@ -723,7 +723,6 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
   a.trace_z = trace_z;
   a.advance = 1;
   const bool nested = h->n_comp > 0;  // (every step launches its weights)
-  h->ell_sel = fuse && !nested ? par : 0;
   if (h->algo == DPF_ALGO_PLAIN) {
     if (!fuse) return queue_plain_step(h, a);
     return queue_plain_run_step(h, a, fuse == 1, par, last);
@@ -735,6 +734,7 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
     float* w[2] = {at<float>(h, h->L.logw), at<float>(h, h->L.logw1)};
     float* k[2] = {at<float>(h, h->L.kpart), at<float>(h, h->L.kpart1)};
     if (!nested) {
+      a.pair = par;
       a.ell = e[par];
       a.logw = w[par];
       a.ell_next = e[par ^ 1];
@@ -814,7 +814,6 @@ static dpf_status queue_learned_step(dpf_handle* h, const float* Y, long long y_
   if (s != DPF_OK) return s;
   if (!h->mom_valid && !mdn_given) s = queue_moments(h, nullptr, nullptr);
   if (s != DPF_OK) return s;
-  h->ell_sel = 0;
   StepArgs a = make_args(h);
   a.Y = Y;
   a.y_tstride = y_tstride;
@@ -903,8 +902,7 @@ extern "C" dpf_status dpf_estimate_rb(dpf_handle* h, float* d_xrb) {
   if (!h || !d_xrb) return fail(DPF_EINVAL, "handle and d_xrb are required");
   if (!h->rb_ready) return fail(DPF_ESTATE, "dpf_estimate_rb follows a dpf_lookahead_step call");
   StepArgs a = make_args(h);
-  a.ell = at<float>(h, h->ell_sel ? h->L.ell1 : h->L.ell);
-  a.logw = at<float>(h, h->ell_sel ? h->L.logw1 : h->L.logw);
+  // (a step on its own leaves its weights in the first pair)
   return h->eng->rb(a, at<double>(h, h->L.xrb), d_xrb, h->stream);
 }
 
@@ -1106,9 +1104,6 @@ static dpf_status run_steps(dpf_handle* h, int mode, const float* d_Y, int32_t T
   }
   for (int q = 1; q + S <= T - R; q += S) HIP_TRY(hipGraphLaunch(h->gexec, h->stream));
   if (R > 0) HIP_TRY(hipGraphLaunch(h->gexec_tail, h->stream));
-  // (the captured steps do not update the host's record of the buffers)
-  const bool la = h->algo == DPF_ALGO_LOOKAHEAD;
-  if (mode == 0 && (la ? h->n_comp == 0 : h->eng->plain_fused)) h->ell_sel = (T - 1) & 1;
   return DPF_OK;
 }
 
@@ -1139,6 +1134,12 @@ extern "C" size_t dpf_state_bytes(const dpf_handle* h) {
 // particle of a group.
 constexpr int kStateIoBlocks = 4096;
 
+static dim3 state_grid(const dpf_handle* h) {
+  int shares = (kStateIoBlocks + h->L.n_rgroups - 1) / h->L.n_rgroups;
+  if (shares > kResGroup) shares = kResGroup;
+  return dim3(h->L.n_rgroups, shares);
+}
+
 static dpf_status state_io(dpf_handle* h, char* ext, int dir) {
   if (dir == 1) h->rb_ready = false;
   StateIo a;
@@ -1165,9 +1166,7 @@ static dpf_status state_io(dpf_handle* h, char* ext, int dir) {
   a.dx = h->dx;
   a.dz = h->dz;
   a.NMT = h->L.NMT;
-  int shares = (kStateIoBlocks + h->L.n_rgroups - 1) / h->L.n_rgroups;
-  if (shares > kResGroup) shares = kResGroup;
-  const dim3 grid(h->L.n_rgroups, shares);
+  const dim3 grid = state_grid(h);
   if (dir == 0)
     hipLaunchKernelGGL(k_state_io<false>, grid, dim3(kBlock), 0, h->stream, a);
   else
@@ -1191,10 +1190,10 @@ extern "C" dpf_status dpf_import_state(dpf_handle* h, const void* d_src, size_t 
 
 extern "C" dpf_status dpf_copy_buffer(dpf_handle* h, int32_t which, void* d_dst, size_t bytes) {
   if (!h || !d_dst) return fail(DPF_EINVAL, "handle and destination are required");
-  size_t off = 0, need = 0;
+  size_t off = 0, need = 0, second = 0;
   switch (which) {
-    case DPF_BUF_ELL: off = h->ell_sel ? h->L.ell1 : h->L.ell; need = (size_t)h->L.NMT * 4; break;
-    case DPF_BUF_LOGW: off = h->ell_sel ? h->L.logw1 : h->L.logw; need = (size_t)h->L.NT * 4; break;
+    case DPF_BUF_ELL: off = h->L.ell; second = h->L.ell1; need = (size_t)h->L.NMT * 4; break;
+    case DPF_BUF_LOGW: off = h->L.logw; second = h->L.logw1; need = (size_t)h->L.NT * 4; break;
     case DPF_BUF_ANC: off = h->L.anc; need = (size_t)h->L.NT * 4; break;
     case DPF_BUF_SEL: off = h->L.sel; need = (size_t)h->L.NT * 4; break;
     case DPF_BUF_MDN: off = h->L.mdn; need = (size_t)h->L.NT * kMlpOut * 4; break;
@@ -1212,6 +1211,13 @@ extern "C" dpf_status dpf_copy_buffer(dpf_handle* h, int32_t which, void* d_dst,
     default: return fail(DPF_EINVAL, "unknown buffer %d", which);
   }
   if (bytes < need) return fail(DPF_EINVAL, "buffer %d needs %zu bytes", which, need);
+  if (second) {
+    hipLaunchKernelGGL(k_last_weights, state_grid(h), dim3(kBlock), 0, h->stream, at<unsigned char>(h, h->L.cur),
+                       at<int2>(h, h->L.rgroups), at<int4>(h, h->L.ginfo), at<int>(h, h->L.fM),
+                       at<long long>(h, h->L.ioff), at<float>(h, second), at<float>(h, off),
+                       which == DPF_BUF_ELL ? 1 : 0);
+    LAUNCH_CHECK("k_last_weights");
+  }
   HIP_TRY(hipMemcpyAsync(d_dst, h->ws + off, need, hipMemcpyDeviceToDevice, h->stream));
   return DPF_OK;
 }
