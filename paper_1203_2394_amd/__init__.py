@@ -577,9 +577,29 @@ class MLP:
 
     def train_batches(self, X, xt, idx, lr=1e-3, loss=None):
         """Adam steps on the consecutive batches of row indices idx [k batch]
-        (int32, on the device) into the set (X [n][32], xt [n][2]); loss: an
-        optional device tensor for the k batches' mean NLLs."""
-        k = idx.numel() // self.batch
+        (whole numbers; int32 on the device is taken as it is) into the set
+        (X [n][32], xt [n][2]), k whole batches; an index outside the set gives
+        a row of NaNs.  loss: an optional contiguous float32 device tensor of at
+        least k elements for the batches' mean NLLs."""
+        torch = _torch()
+        X = torch.as_tensor(X, dtype=torch.float32, device=self.device).contiguous()
+        xt = torch.as_tensor(xt, dtype=torch.float32, device=self.device).contiguous()
+        if X.dim() != 2 or X.shape[1] != MLP_IN or xt.dim() != 2 or xt.shape[1] != 2 or xt.shape[0] < X.shape[0]:
+            raise DPFError("need features [n][%d] and targets [n][2], got %s and %s"
+                           % (MLP_IN, tuple(X.shape), tuple(xt.shape)))
+        idx = torch.as_tensor(idx, device=self.device)
+        if idx.dtype not in (torch.int8, torch.uint8, torch.int16, torch.int32, torch.int64):
+            raise DPFError("row indices must be whole numbers, got %s" % idx.dtype)
+        if idx.dtype == torch.int64:  # (beyond 32 bits: outside the set, as negative ones are)
+            idx = torch.where((idx < 0) | (idx > 0x7fffffff), -1, idx)
+        idx = idx.to(torch.int32).contiguous()
+        k, rest = divmod(idx.numel(), self.batch)
+        if rest:
+            raise DPFError("%d row indices are not whole batches of %d" % (idx.numel(), self.batch))
+        if loss is not None and (loss.dtype != torch.float32 or loss.device != self.state.device
+                                 or not loss.is_contiguous() or loss.numel() < k):
+            raise DPFError("loss must be a contiguous float32 tensor on %s of at least %d elements"
+                           % (self.state.device, k))
         _check(lib().dpf_mlp_train_batches(_ptr(self.state), _ptr(self.blob), _ptr(X), _ptr(xt), int(X.shape[0]),
                                            _ptr(idx), k, self.batch, float(lr), self.adam_t, _ptr(self._ws),
                                            self._ws.numel(), _ptr(loss), self._stream()))
