@@ -1415,10 +1415,11 @@ extern "C" dpf_status dpf_mlp_forward(const void* d_blob, const float* d_X, int3
 }
 
 // One training step: the batch's forward and backward pass, the weight
-// gradients, Adam.  idx (optional): the batch's rows of X and xt.
+// gradients, Adam.  idx (optional): the batch's rows of X and xt.  first: of the
+// call (its forward weights are the blob's; later ones take the copies).
 static dpf_status train_step(float* d_state, void* d_blob, const float* d_X, const float* d_xt, const int32_t* d_idx,
                              int64_t n_src, int32_t B, float lr, int32_t adam_t, void* d_train_ws, size_t ws_bytes,
-                             float* d_loss, float* d_grad, hipStream_t s) {
+                             float* d_loss, float* d_grad, hipStream_t s, bool first = true) {
   if (!d_state || !d_blob || !d_X || !d_xt || !d_train_ws) return fail(DPF_EINVAL, "null buffer");
   if (B < 32 || B % 32 != 0 || B > kMaxTrainBatch)
     return fail(DPF_EINVAL, "batch %d must be a positive multiple of 32 up to %d", B, kMaxTrainBatch);
@@ -1450,7 +1451,8 @@ static dpf_status train_step(float* d_state, void* d_blob, const float* d_X, con
   t.b3_part = (float*)(ws + w.b3p);
   t.loss_part = (double*)(ws + w.lossp);
   t.B = B;
-  hipLaunchKernelGGL(k_mlp_train<2>, dim3(w.tiles), dim3(kTrainThreads), 0, s, t);
+  if (first) hipLaunchKernelGGL((k_mlp_train<2, true>), dim3(w.tiles), dim3(kTrainThreads), 0, s, t);
+  else hipLaunchKernelGGL((k_mlp_train<2, false>), dim3(w.tiles), dim3(kTrainThreads), 0, s, t);
   LAUNCH_CHECK("k_mlp_train");
   AdamArgs ad;
   ad.p = d_state;
@@ -1497,7 +1499,7 @@ extern "C" dpf_status dpf_mlp_train_batches(float* d_state, void* d_blob, const 
   for (int b = 0; b < n_batches; ++b) {
     const dpf_status st = train_step(d_state, d_blob, d_X, d_xt, d_idx + (size_t)b * B, n_rows, B, lr,
                                      adam_t0 + b + 1, d_train_ws, ws_bytes, d_loss ? d_loss + b : nullptr, nullptr,
-                                     (hipStream_t)hip_stream);
+                                     (hipStream_t)hip_stream, b == 0);
     if (st != DPF_OK) return st;
   }
   return DPF_OK;

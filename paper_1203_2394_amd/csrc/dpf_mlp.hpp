@@ -571,7 +571,11 @@ __device__ __forceinline__ void mlp_back_layer(const bf16_t (*in)[SIN], const bf
   }
 }
 
-template <int DX>
+// BLOB: the forward pass takes its weights from the caller's blob, which between
+// calls is the caller's to rewrite; else from the workspace's fragment-order
+// copies, which the step before in the same call has just written (batch 4096:
+// 23 us a step from the blob's rows, 21 from the copies).
+template <int DX, bool BLOB>
 static __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpTrainArgs p) {
   __shared__ MlpShared sh;
   __shared__ float g_sh[kMlpRows][kMlpOut + 1];
@@ -602,7 +606,8 @@ static __global__ __launch_bounds__(kTrainThreads) void k_mlp_train(MlpTrainArgs
     tv = r >= 0 ? p.xt[(size_t)r * DX + th % DX] : NAN;
   }
   MlpFrags<NT> fr;
-  mlp_load_frags<NT, true>(p.W1, p.W2, p.W3, p.blob, fr);
+  if constexpr (BLOB) mlp_load_blob<NT, false>(p.blob, fr);
+  else mlp_load_frags<NT, true>(p.W1, p.W2, p.W3, p.blob, fr);
 #pragma unroll
   for (int q = 0; q < NX; ++q) {
     const int e = th + q * kTrainThreads;
