@@ -65,7 +65,7 @@ struct Layout {
   size_t prm, fN, fM, ooff, ooff64, ioff, finfo, tcur, cur, act, tiles, rgroups, ginfo, x0, x1, z0, z1, l0, l1, ell,
       logw, anc, sel, kpart, gstat, fstat, ess, dlogz, loglik, flags, est_x, est_z;
   // slot indirection and learned-proposal buffers
-  size_t ind0, ind1, mom, mlp, mdn, xtmp, logq, kpart_tmp, mom_tmp, fb, lflags;
+  size_t ind0, ind1, mom, mlp, mlp_in, mdn, xtmp, logq, kpart_tmp, mom_tmp, fb, lflags;
   // second weight buffers: a look-ahead run alternates between the two
   size_t ell1, logw1;
   // step-end kernel: per-group partial estimates, per-filter counters
@@ -170,6 +170,7 @@ static dpf_status plan(const dpf_config* c, const Engine*& eng, Layout& L) {
   L.ind1 = carve(cur, NT * 4);
   L.mom = carve(cur, NT * 2 * dz * 4);
   L.mlp = carve(cur, MlpBlobLayout::bytes);
+  L.mlp_in = carve(cur, MlpBlobLayout::bytes);
   L.mdn = carve(cur, NT * kMlpOut * 4);
   L.xtmp = carve(cur, NT * dx * 4);
   L.logq = carve(cur, NT * 4);
@@ -925,8 +926,10 @@ extern "C" dpf_status dpf_set_proposal(dpf_handle* h, const void* d_blob, size_t
   if (bytes != MlpBlobLayout::bytes) return fail(DPF_EINVAL, "blob has %zu bytes, expected %zu", bytes,
                                                  (size_t)MlpBlobLayout::bytes);
   if (!(ess_frac >= 0.0 && ess_frac <= 1.0)) return fail(DPF_EINVAL, "ess_frac must lie in [0, 1]");
+  // (the runtime copies the blob: any memory and alignment that it can read)
+  HIP_TRY(hipMemcpyAsync(h->ws + h->L.mlp_in, d_blob, bytes, hipMemcpyDeviceToDevice, h->stream));
   hipLaunchKernelGGL(k_mlp_to_handle, dim3(kMlpHid * kMlpHid / kBlock), dim3(kBlock), 0, h->stream,
-                     (const unsigned char*)d_blob, at<unsigned char>(h, h->L.mlp));
+                     at<unsigned char>(h, h->L.mlp_in), at<unsigned char>(h, h->L.mlp));
   LAUNCH_CHECK("k_mlp_to_handle");
   h->has_proposal = true;
   h->ess_frac = ess_frac;

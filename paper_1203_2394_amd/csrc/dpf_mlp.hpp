@@ -912,8 +912,8 @@ static __global__ void k_mlp_pack(const float* params, const float* fmean, const
   }
 }
 
-// A caller's blob -> a handle's: the weights in fragment order, the rest as
-// it is.
+// A blob (in the workspace) -> a handle's: the weights in fragment order, the
+// rest as it is.
 static __global__ void k_mlp_to_handle(const unsigned char* src, unsigned char* dst) {
   using BL = MlpBlobLayout;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
