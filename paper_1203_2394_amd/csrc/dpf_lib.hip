@@ -201,6 +201,7 @@ struct dpf_handle {
   int model, algo, dx, dz, dy, F;
   uint64_t seed;
   hipStream_t stream;
+  int device;  // current when the handle was created
   Layout L;
   char* ws;
   std::vector<int> N, M, ooff;
@@ -425,6 +426,7 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
   h->F = cfg->n_filters;
   h->seed = cfg->seed;
   h->stream = (hipStream_t)hip_stream;
+  if (hipGetDevice(&h->device) != hipSuccess) h->device = -1;
   h->L = L;
   h->ws = (char*)d_workspace;
   const int F = h->F;
@@ -964,17 +966,19 @@ extern "C" dpf_status dpf_features(dpf_handle* h, const float* d_y, float* d_fea
   return queue_moments(h, d_y, d_feat);
 }
 
-// Whether p is memory that a kernel on this device can write (device, managed
-// or pinned); anything else is left to the runtime's copy.
-static bool kernel_may_write(const void* p) {
+// Whether p is memory that a kernel on the handle's device can write (its own,
+// managed or pinned); anything else, or another device being current, is left
+// to the runtime's copy.
+static bool kernel_may_write(const dpf_handle* h, const void* p) {
   hipPointerAttribute_t at;
   if (hipPointerGetAttributes(&at, p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
   int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  return at.devicePointer == p && (at.type != hipMemoryTypeDevice || at.device == dev);
+  if (hipGetDevice(&dev) != hipSuccess || dev != h->device || at.devicePointer != p) return false;
+  return at.type == hipMemoryTypeDevice ? at.device == dev
+                                        : at.type == hipMemoryTypeHost || at.type == hipMemoryTypeManaged;
 }
 
 extern "C" dpf_status dpf_estimate(dpf_handle* h, float* d_xmean, float* d_zmean, float* d_ess,
@@ -992,7 +996,7 @@ extern "C" dpf_status dpf_estimate(dpf_handle* h, float* d_xmean, float* d_zmean
     e.dst[q] = (uint32_t*)dst[q];
     e.src[q] = (const uint32_t*)src[q];
     e.end[q] = n += dst[q] ? (long long)words[q] : 0;
-    kernel = kernel && (!dst[q] || kernel_may_write(dst[q]));
+    kernel = kernel && (!dst[q] || kernel_may_write(h, dst[q]));
   }
   if (kernel) {
     if (n == 0) return DPF_OK;
