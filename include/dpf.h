@@ -337,7 +337,10 @@ dpf_status dpf_set_tiling(dpf_handle* h, const int32_t* h_cls);
  * the stream has passed this call) and set the fallback threshold: a
  * filter whose learned outer weights have ESS < ess_frac * N (or no finite
  * weight) takes the look-ahead step instead (ess_frac in [0, 1]).  Queues
- * the cloud moments of the current state.  Look-ahead handles only. */
+ * the cloud moments of the current state.  Look-ahead handles only.  From
+ * then on the handle's steps keep the moments up to date, in the tile classes
+ * that the learned step runs in (the last bits of the mean estimates may
+ * differ from those of a large handle without a proposal). */
 dpf_status dpf_set_proposal(dpf_handle* h, const void* d_blob, size_t bytes, double ess_frac);
 
 /* One step with the learned proposal (importance-sampling step of Fig. 2,

@@ -78,7 +78,8 @@ struct Layout {
   size_t tcur1, cur1, act1, kpart1;
   int NT = 0;
   long long NMT = 0;
-  int n_tiles = 0, n_rgroups = 0;
+  long long n_tiles = 0;
+  int n_rgroups = 0;
 };
 
 static size_t carve(size_t& cursor, size_t bytes) {
@@ -115,7 +116,9 @@ static dpf_status plan(const dpf_config* c, const Engine*& eng, Layout& L) {
   L.NT = 0;
   L.NMT = 0;
   L.n_rgroups = 0;
-  L.n_tiles = 0;  // room for any class: at most one tile per outer particle
+  // room for any class (at most one tile per outer particle) and for the narrow
+  // class's tiles beside it (at least kBlock / kWave particles each)
+  L.n_tiles = 0;
   for (int f = 0; f < F; ++f) {
     if (c->N[f] < 1 || c->N[f] > 65536) return fail(DPF_EUNSUPPORTED, "N[%d] = %d outside 1..65536", f, c->N[f]);
     const int cls = class_of(c->M[f]);
@@ -123,7 +126,7 @@ static dpf_status plan(const dpf_config* c, const Engine*& eng, Layout& L) {
     if ((long long)L.NT + c->N[f] > 0x7fffffffLL) return fail(DPF_EUNSUPPORTED, "total N too large");
     L.NT += c->N[f];
     L.NMT += (long long)c->N[f] * c->M[f];
-    L.n_tiles += c->N[f];  // at most one tile per outer particle (SEG = 256)
+    L.n_tiles += c->N[f] + (c->N[f] + kBlock / kWave - 1) / (kBlock / kWave);
     const int G = (c->N[f] + kResGroup - 1) / kResGroup;
     L.n_rgroups += G;
   }
@@ -211,11 +214,11 @@ struct dpf_handle {
   std::vector<int4> ginfo_h;  // per group: the filter's (first outer index, N, first group, groups)
   std::vector<FilterInfo> finfo_h;
   std::vector<float> prm_h;
-  std::vector<TileClass> classes;
+  std::vector<TileClass> classes;       // of ordinary launches: narrow classes stand in
+  std::vector<TileClass> classes_wide;  // without them (learned passes, cloud moments)
   std::vector<int> fcls;  // tile class of each filter
   bool one_group = false;  // every filter has one resampling group
   std::vector<char> fdef;  // whether the filter's class is the default (a narrow class may stand in)
-  bool wide = false;       // no narrow classes from here on (learned passes, moments)
   // multi-step graph cache
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -326,10 +329,19 @@ static StepArgs make_args(dpf_handle* h) {
   return a;
 }
 
+// The classes of an operation's launches.  The learned passes and the cloud
+// moments have no narrow class; while a proposal is set, steps keep the moments up
+// to date for it, in the classes that the learned steps form them in.
+static const std::vector<TileClass>& classes_for(const dpf_handle* h, int op) {
+  const bool learned = op == OP_LEARNED_INNER || op == OP_MOMENTS || op == OP_LA_WEIGHTS_FALLBACK ||
+                       op == OP_NEWCLOUD_FALLBACK;
+  return learned || h->has_proposal ? h->classes_wide : h->classes;
+}
+
 // grid_cap > 0: at most grid_cap workgroups per class, looping over the
 // tiles (for launches that most tiles skip).
 static dpf_status launch_classes(dpf_handle* h, int op, StepArgs a, int grid_cap = 0) {
-  for (const TileClass& tc : h->classes) {
+  for (const TileClass& tc : classes_for(h, op)) {
     a.tiles = tc.d_tiles;
     a.n_tiles = tc.n_tiles;
     TileClass g = tc;
@@ -521,7 +533,6 @@ constexpr long long kNarrowWaves = 1600;
 
 static std::vector<bool> narrow_used(const dpf_handle* h) {
   std::vector<bool> used(kNumNarrow, false);
-  if (h->wide) return used;
   std::vector<long long> sixteenths(kNumNarrow, 0);
   for (int f = 0; f < h->F; ++f) {
     const int k = h->fdef[f] ? narrow_class(h, f) - kNumClasses : -1;
@@ -533,44 +544,48 @@ static std::vector<bool> narrow_used(const dpf_handle* h) {
   return used;
 }
 
-// Tiles of every filter in its launch class, grouped by class, uploaded to the
-// workspace (room for one tile per outer particle was reserved).
+// Tiles of every filter, grouped by class, uploaded to the workspace once for both
+// kinds of launch: a public class's tiles begin with the filters that it serves in
+// ordinary launches, those that a narrow class stands in for follow, and the
+// narrow classes' own come after (no call but dpf_set_tiling rewrites what a
+// graph captured by the caller may hold).
 static dpf_status build_tiles(dpf_handle* h) {
   const int F = h->F;
   const std::vector<bool> narrow = narrow_used(h);
-  std::vector<std::vector<int4>> by(kNumClasses + kNumNarrow);
+  std::vector<std::vector<int4>> by(kNumClasses + kNumNarrow), stood(kNumClasses);
   for (int f = 0; f < F; ++f) {
     const int nc = h->fdef[f] ? narrow_class(h, f) : -1;
-    const int c = nc >= 0 && narrow[nc - kNumClasses] ? nc : h->fcls[f];
-    const int segs = kBlock / (c < kNumClasses ? kClasses[c].seg : kNarrow[c - kNumClasses].seg);
-    int nt = 0;
-    for (int i0 = 0; i0 < h->N[f]; i0 += segs)
-      by[c].push_back(make_int4(f, i0, nt++, h->finfo_h[f].rg_base));
+    const bool in = nc >= 0 && narrow[nc - kNumClasses];
+    auto tiles = [&](std::vector<int4>& out, int segs) {
+      int nt = 0;
+      for (int i0 = 0; i0 < h->N[f]; i0 += segs) out.push_back(make_int4(f, i0, nt++, h->finfo_h[f].rg_base));
+    };
+    tiles(in ? stood[h->fcls[f]] : by[h->fcls[f]], kBlock / kClasses[h->fcls[f]].seg);
+    if (in) tiles(by[nc], kBlock / kNarrow[nc - kNumClasses].seg);
   }
   h->tiles_h.clear();
   h->classes.clear();
-  for (int k = 0; k < kNumClasses + kNumNarrow; ++k) {
-    if (by[k].empty()) continue;
+  h->classes_wide.clear();
+  auto list = [&](std::vector<TileClass>& out, int k, size_t first, size_t n) {
+    if (n == 0) return;
     TileClass tc;
     tc.cls = k;
-    tc.n_tiles = (int)by[k].size();
-    tc.d_tiles = at<int4>(h, h->L.tiles) + h->tiles_h.size();
+    tc.n_tiles = (int)n;
+    tc.d_tiles = at<int4>(h, h->L.tiles) + first;
+    out.push_back(tc);
+  };
+  for (int k = 0; k < kNumClasses + kNumNarrow; ++k) {
+    const size_t first = h->tiles_h.size();
     h->tiles_h.insert(h->tiles_h.end(), by[k].begin(), by[k].end());
-    h->classes.push_back(tc);
+    list(h->classes, k, first, by[k].size());
+    if (k >= kNumClasses) continue;
+    h->tiles_h.insert(h->tiles_h.end(), stood[k].begin(), stood[k].end());
+    list(h->classes_wide, k, first, by[k].size() + stood[k].size());
   }
-  if ((int)h->tiles_h.size() > h->L.n_tiles) return fail(DPF_EINVAL, "internal: tile room exceeded");
+  if ((long long)h->tiles_h.size() > h->L.n_tiles) return fail(DPF_EINVAL, "internal: tile room exceeded");
   HIP_TRY(hipMemcpyAsync(h->ws + h->L.tiles, h->tiles_h.data(), h->tiles_h.size() * sizeof(int4),
                          hipMemcpyHostToDevice, h->stream));
   drop_graphs(h);
-  return DPF_OK;
-}
-
-// Before a learned pass or the cloud moments, which have no narrow class.
-static dpf_status use_wide(dpf_handle* h) {
-  if (h->wide) return DPF_OK;
-  h->wide = true;
-  for (const TileClass& tc : h->classes)
-    if (tc.cls >= kNumClasses) return build_tiles(h);
   return DPF_OK;
 }
 
@@ -624,7 +639,7 @@ constexpr int kFinishTiles = 32;
 static bool finish_in_newcloud(const dpf_handle* h) {
   if (!h->one_group || !h->eng->plain_fused) return false;
   int n = 0;
-  for (const TileClass& tc : h->classes) n += tc.n_tiles;
+  for (const TileClass& tc : classes_for(h, OP_NEWCLOUD_LA)) n += tc.n_tiles;
   return n <= kFinishTiles;
 }
 
@@ -796,8 +811,6 @@ static dpf_status queue_step(dpf_handle* h, const float* Y, long long y_tstride,
 // step's features; with feat, also the raw feature rows for y.
 static dpf_status queue_moments(dpf_handle* h, const float* y, float* feat) {
   if (!h->eng->moments) return fail(DPF_EUNSUPPORTED, "cloud moments are not built for this model");
-  const dpf_status w = use_wide(h);
-  if (w != DPF_OK) return w;
   StepArgs a = make_args(h);
   a.mom = at<float>(h, h->L.mom);
   g_mom_args = MomArgs{y, feat};
@@ -813,8 +826,7 @@ static dpf_status queue_learned_step(dpf_handle* h, const float* Y, long long y_
                                      const unsigned char* active, const int* run_Tf, int run_T, float* trace_x,
                                      float* trace_z, const float* mdn_given) {
   h->rb_ready = false;
-  dpf_status s = use_wide(h);
-  if (s != DPF_OK) return s;
+  dpf_status s = DPF_OK;
   if (!h->mom_valid && !mdn_given) s = queue_moments(h, nullptr, nullptr);
   if (s != DPF_OK) return s;
   StepArgs a = make_args(h);
