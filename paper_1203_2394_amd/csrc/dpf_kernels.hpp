@@ -281,8 +281,8 @@ __device__ __forceinline__ float at32(const float* p, int i) {
 // A lane's JPT consecutive items from row[j0] on, in loads of up to 16 bytes
 // (item by item, each load of a wave would touch every line of the segment's
 // row again).  j0 is clamped into the row of n items, so up to JPT - 1 floats
-// after the row are read too -- the next row, or the array that follows in the
-// workspace; the caller masks items by ls JPT + r < n.
+// after the row are read too -- the next row, or the room that the workspace
+// leaves after the last one; the caller masks items by ls JPT + r < n.
 template <int JPT>
 struct Items {
   float v[JPT];

@@ -88,6 +88,26 @@ static size_t carve(size_t& cursor, size_t bytes) {
   return off;
 }
 
+// An array whose rows the kernels read in whole vectors (load_items): the lane
+// with the last row's last item reads up to its class's items per lane on, less
+// one, so that much of the array's own room follows the row.
+constexpr int kRowPad = 16;
+constexpr int max_items() {
+  int m = 0;
+  // per lane of the class, and per lane of one wave over the class's items
+  // (select_w0, which reads chunks of more than 16 one by one)
+  auto add = [&](int seg, int jpt) {
+    const int wave = (seg * jpt + kWave - 1) / kWave;
+    if (jpt > m) m = jpt;
+    if (wave <= 16 && wave > m) m = wave;
+  };
+  for (const ClassShape& c : kClasses) add(c.seg, c.jpt);
+  for (const NarrowShape& c : kNarrow) add(c.seg, c.jpt);
+  return m;
+}
+static_assert(max_items() - 1 <= kRowPad, "rows are read past their end by up to the items per lane, less one");
+static size_t carve_rows(size_t& cursor, size_t floats) { return carve(cursor, (floats + kRowPad) * 4); }
+
 static dpf_status plan(const dpf_config* c, const Engine*& eng, Layout& L) {
   if (!c) return fail(DPF_EINVAL, "config is NULL");
   if (c->abi_version != DPF_ABI_VERSION)
@@ -148,13 +168,13 @@ static dpf_status plan(const dpf_config* c, const Engine*& eng, Layout& L) {
   L.ginfo = carve(cur, (size_t)L.n_rgroups * sizeof(int4));
   L.x0 = carve(cur, NT * dx * 4);
   L.x1 = carve(cur, NT * dx * 4);
-  L.z0 = carve(cur, NMT * dz * 4);
-  L.z1 = carve(cur, NMT * dz * 4);
-  L.l0 = carve(cur, NMT * 4);
-  L.l1 = carve(cur, NMT * 4);
-  L.ell = carve(cur, NMT * 4);
+  L.z0 = carve_rows(cur, NMT * dz);
+  L.z1 = carve_rows(cur, NMT * dz);
+  L.l0 = carve_rows(cur, NMT);
+  L.l1 = carve_rows(cur, NMT);
+  L.ell = carve_rows(cur, NMT);
   L.logw = carve(cur, NT * 4);
-  L.ell1 = carve(cur, NMT * 4);
+  L.ell1 = carve_rows(cur, NMT);
   L.logw1 = carve(cur, NT * 4);
   L.anc = carve(cur, NT * 4);
   L.sel = carve(cur, NT * 4);
