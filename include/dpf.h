@@ -252,7 +252,7 @@ dpf_status dpf_estimate_rb(dpf_handle* h, float* d_xrb);
  * float x[dx][sum N], float z[sum_f N_f*dz*M_f] (filter blocks in order,
  * each [N][dz][M]), float lam[sum_f N_f*M_f] (log qbar, [N][M] per filter).
  * For DPF_ALGO_PLAIN, x and z are the proposals for the next step and lam
- * is unused.  Import resets the flags and the cumulative evidence. */
+ * is unused (zeros unless a state with other values was imported).  Import resets the flags and the cumulative evidence. */
 size_t dpf_state_bytes(const dpf_handle* h);
 dpf_status dpf_export_state(dpf_handle* h, void* d_dst, size_t bytes);
 dpf_status dpf_import_state(dpf_handle* h, const void* d_src, size_t bytes);

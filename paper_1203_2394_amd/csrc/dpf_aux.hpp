@@ -26,6 +26,10 @@ static __global__ void k_reset(int* tcur, unsigned char* cur, unsigned char* act
   lflags[f] = 0u;
 }
 
+static __global__ __launch_bounds__(kBlock) void k_zero(float* p, long long n) {
+  for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < n; e += (long long)gridDim.x * kBlock) p[e] = 0.f;
+}
+
 // Element e of an array of per-filter segments: find the filter by binary
 // search over the offsets (the arrays are sized by the host).
 __device__ __forceinline__ int filter_of(const long long* off, int F, long long e) {

@@ -520,6 +520,19 @@ extern "C" dpf_status dpf_create(const dpf_config* cfg, void* d_workspace, size_
     delete h;
     return st;
   }
+  // a plain handle's lam is exported and imported with the state, but no step
+  // writes it
+  if (h->algo == DPF_ALGO_PLAIN) {
+    const long long n = L.NMT, blocks = (n + kBlock - 1) / kBlock;
+    for (size_t off : {L.l0, L.l1})
+      hipLaunchKernelGGL(k_zero, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(kBlock), 0, h->stream,
+                         at<float>(h, off), n);
+    const hipError_t ez = hipGetLastError();
+    if (ez != hipSuccess) {
+      delete h;
+      return fail(DPF_EDEVICE, "launch of k_zero failed: %s", hipGetErrorString(ez));
+    }
+  }
   st = queue_init(h, 0);
   if (st != DPF_OK) {
     delete h;
