@@ -289,7 +289,8 @@ dpf_status dpf_copy_buffer(dpf_handle* h, int32_t which, void* d_dst, size_t byt
  * a graph) records the next 5 events on the handle's stream: before the
  * weight kernels, after them, after the outer resampling, after the
  * new-cloud kernels and after the estimates, until the array is used up.
- * Elapsed times between consecutive events give each phase's duration. */
+ * Elapsed times between consecutive events give each phase's duration (in a
+ * run most of the weights and estimates ride in new-cloud launches). */
 dpf_status dpf_set_phase_events(dpf_handle* h, void* const* hip_events, int32_t n_events);
 
 /* Message for the last non-OK status returned on this thread. */

@@ -18,11 +18,13 @@ namespace {
 // Memory-bound work (8 flops per value); what decides is how many loads are
 // in flight.  With scratch (k_stats_part, k_stats_final) the rows are split
 // over up to kStatChunks workgroups, each summing its chunk twice (the second
-// pass reads the chunk from L2) about its own mean; the chunks are joined by
+// pass about its own mean; the chunks in flight, 13 MB an XCD at the size below,
+// are larger than its L2, so it reads them again mostly from the Infinity
+// Cache); the chunks are joined by
 //   M2 = sum_c M2_c + sum_c n_c (mean_c - mean)^2
 // (exact in exact arithmetic; every term non-negative).  1e6 x 26 values:
-// 70.3 ms with one 256-thread workgroup for all columns, 37 us (2.8 TB/s) with 1024
-// chunks.
+// 70.3 ms with one 256-thread workgroup for all columns, 37 us with 1024 chunks
+// (2.8 TB/s counting the values once, 5.6 both passes).
 constexpr int kStatThreads = 256;
 constexpr int kStatCols = 32;                          // columns handled at once
 constexpr int kStatRowLanes = kStatThreads / kStatCols;  // rows in flight per column

@@ -67,7 +67,6 @@ typedef unsigned short bf16_t;
 // Round to nearest even; NaN stays NaN (the card's own conversion; by integer
 // arithmetic it was a third of a hidden layer's vector instructions).
 __device__ __forceinline__ bf16_t f2bf(float v) { return __builtin_bit_cast(bf16_t, (__bf16)v); }
-__device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 __device__ __forceinline__ bf16x8 ld8(const bf16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
