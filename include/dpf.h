@@ -194,7 +194,9 @@ dpf_status dpf_estimate(dpf_handle* h, float* d_xmean, float* d_zmean, float* d_
  * weights, eq:weightsMC) inside step t's new-cloud launch, from the clouds
  * it has just built, and the outer-weight statistics of step t+1 inside step
  * t's step-end launch: results are bit-identical to T dpf_lookahead_step
- * calls with the same activity (per-filter horizons included). */
+ * calls with the same activity (per-filter horizons included).  Exception:
+ * DPF_MODEL_TWODIM_ZFIRST, whose look-ahead log-weights may differ in their
+ * last bits between the two (the same expressions, fused differently). */
 dpf_status dpf_run(dpf_handle* h, const float* d_Y, int32_t T, const int32_t* d_Tf,
                    float* d_xtrace, float* d_ztrace, int32_t use_graph);
 
@@ -226,7 +228,7 @@ dpf_status dpf_set_lookahead_companions(dpf_handle* h, int32_t n_comp);
  * candidate's companions); h the noise-free observation.  enable != 0: every
  * following look-ahead step (dpf_lookahead_step, dpf_run) forms it from
  * its own look-ahead draws; d_ytrace [T][F] float (or NULL) receives it at
- * row t-1 as y_t is consumed.  Built for models with a one-dimensional y
+ * row t-1 as y_t is consumed (T: the last time stepped to while it is set).  Built for models with a one-dimensional y
  * (LINGAUSS, TWODIM, TWODIM_ZFIRST, FOURDIM; else DPF_EUNSUPPORTED); look-ahead
  * handles only (DPF_ESTATE); not formed by the learned step. */
 dpf_status dpf_set_prediction(dpf_handle* h, int32_t enable, float* d_ytrace);
